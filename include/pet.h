@@ -125,14 +125,16 @@ pet_status pet_fwd(pet_geom g, int subset, const float *x, const float *mult, co
  * the preconditioner of eq. (preconditioner)): x_out (+)= P_subset^T (mult * sino).
  * sino NULL means all ones (so pet_back(g, -1, NULL, mult, sens, 0, ...) gives
  * the sensitivity A^T 1).  accumulate = 0 overwrites x_out.  algo:
- *   PET_BACK_SCATTER  line-driven scatter: each sample of each LOR adds its two
- *                     axial interpolation shares to an LDS sheet of its line
- *                     with FP64 LDS atomics;
+ *   PET_BACK_SCATTER  the line kernels of the fused gradients: with TOF, each
+ *                     sample of each LOR adds its two axial interpolation shares
+ *                     to an LDS sheet of its line with FP64 LDS atomics; without
+ *                     TOF, and for the sensitivity, the cells of the sheet gather
+ *                     the shares of each segment's planes;
  *   PET_BACK_GATHER   cell-driven gather: each sheet cell sums, without
  *                     atomics, the shares of the samples that land on it,
  *                     found from each segment's affine axial map (TOF weights
  *                     from the tabulated bin-integrated Gaussian);
- *   PET_BACK_AUTO     the scatter, measured faster on every workload here.
+ *   PET_BACK_AUTO     PET_BACK_SCATTER, measured faster on every workload here.
  * Both spread the sheets over the transaxial neighbours with global float
  * atomics, so the sum order is not deterministic; both give the same
  * (sample, weight) pairs.  PET_E_ARG for PET_BACK_GATHER when the per-plane

@@ -56,6 +56,15 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.G0 = g->G0;
     a.G1 = g->G1;
     a.tof = g->tof;
+    a.gather = g->gather;
+    a.gchunk = g->gchunk;
+    a.n_gchunk = g->n_gchunk;
+    a.gather_two = g->gather_two;
+    a.kappa = (float)g->kappa;
+    a.inv_kappa = 1.0 / g->kappa;
+    a.rho0 = g->ring0 + 1.0;
+    a.pitch2 = (float)(g->d.ring_pitch_mm * g->d.ring_pitch_mm);
+    a.k_max = (float)g->d.max_ring_diff;
     a.order = g->line_order + g->order_off[subset < 0 ? g->d.n_subsets : subset];
     return a;
 }

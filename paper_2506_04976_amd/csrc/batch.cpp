@@ -210,7 +210,7 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         // LDS of the line bodies: sheets, plus one TOF table per wave
         const int rz = g->d.nz + 2 * PADZ;
         const size_t sheet = ((size_t)g->rows_max * rz + 3) & ~(size_t)3;
-        b->lds_base.push_back(3 * sheet * sizeof(float));
+        b->lds_base.push_back(std::max(3 * sheet, sheet + (m.is_tof ? 0 : (size_t)g->q_floats)) * sizeof(float));
         size_t pw = 0;
         if (m.is_tof) {
             const int e1 = g->tof_ws > 4 ? g->tof_ws - 4 : 0;

@@ -136,7 +136,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
         hplanes[p].zb = (float)((z1[p] - O[2]) / V[2]);
         hplanes[p].zs = (float)((z2[p] - z1[p]) / V[2]);
         hplanes[p].dz2 = (float)((z2[p] - z1[p]) * (z2[p] - z1[p]));
-        hplanes[p].seg = planes[p].seg;
+        hplanes[p].q = 0;
     }
 
     // line table
@@ -284,6 +284,67 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     }
     // the plain segment list in plane order (the gather adjoint walks it)
     const std::vector<SegP> gsegs = hsegs;
+    // Axial gather of the adjoint: segments in parts of at most GATHER_PLANES
+    // planes, in chunks whose factors fit the LDS beside the image sheet.  The
+    // cap holds every plane of any scanner here (2204 planes take 9 KB); it
+    // never exceeds what the two FP64 sheets' worth of LDS checked below leaves.
+    if (d.kind == PET_SCANNER_CYLINDER) {
+        g->kappa = d.ring_pitch_mm / d.vz;
+        g->ring0 = -(-0.5 * (d.n_rings - 1) * d.ring_pitch_mm - O[2]) / d.ring_pitch_mm;
+    }
+    std::vector<GatherSeg> hgather;
+    std::vector<GatherChunk> hchunks;
+    {
+        const size_t sheet_f = ((size_t)rows_max * (d.nz + 2 * PADZ) + 3) & ~(size_t)3;
+        const int cap = (int)std::max<size_t>(2 * sheet_f, 12288);
+        struct Part {
+            int p0, np, k, off;  // first plane, planes, ring difference, ranks before the first
+        };
+        std::vector<Part> part;
+        auto flush = [&]() {
+            if (part.empty()) return;
+            GatherChunk c{};
+            c.s0 = (int)hgather.size();
+            c.p0 = part.front().p0;
+            c.p1 = part.back().p0 + part.back().np;
+            int at = 1;  // (a zero before the first part; two after each)
+            std::vector<int> qb(part.size());
+            for (size_t i = 0; i < part.size(); ++i) {
+                for (int j = 0; j < part[i].np; ++j) hplanes[part[i].p0 + j].q = at + j;
+                qb[i] = at - 1 - part[i].off;
+                at += part[i].np + 2;
+            }
+            c.n_q = at;
+            for (int neg = 0; neg < 2; ++neg) {
+                if (neg) c.s_neg = (int)hgather.size();
+                for (size_t i = 0; i < part.size(); ++i) {
+                    if ((part[i].k < 0) != (neg == 1)) continue;
+                    hgather.push_back({(float)std::abs(part[i].k), (float)part[i].off,
+                                       (float)(part[i].off + part[i].np + 1), qb[i]});
+                }
+            }
+            c.s1 = (int)hgather.size();
+            hchunks.push_back(c);
+            g->q_floats = std::max(g->q_floats, (at + 3) & ~3);
+            part.clear();
+        };
+        int used = 1;
+        for (const SegP &sg : gsegs)
+            for (int off = 0; off < sg.np; off += GATHER_PLANES) {
+                const int np = std::min(GATHER_PLANES, sg.np - off);
+                if (used + np + 2 > cap) {
+                    flush();
+                    used = 1;
+                }
+                part.push_back({sg.p0 + off, np, planes[sg.p0].r2 - planes[sg.p0].r1, off});
+                used += np + 2;
+            }
+        flush();
+    }
+    g->n_gchunk = (int)hchunks.size();
+    g->gather_two = (float)g->kappa >= 1.f;
+    for (const SegP &sg : gsegs)
+        if (sg.np > GATHER_PLANES) g->gather_two = 0;
     if (d.n_tof > 1) {
         // segments -k and +k (adjacent in the plane order) have the same
         // oblique length and so the same TOF weight table: one segment wave
@@ -413,6 +474,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     bool ok = alloc((void **)&g->lines, sizeof(LineP) * nl) && alloc((void **)&g->planes, sizeof(PlaneP) * planes.size()) &&
               alloc((void **)&g->segs, sizeof(SegP) * hsegs.size()) &&
               alloc((void **)&g->gsegs, sizeof(SegP) * gsegs.size()) &&
+              alloc((void **)&g->gather, sizeof(GatherSeg) * hgather.size()) &&
+              alloc((void **)&g->gchunk, sizeof(GatherChunk) * hchunks.size()) &&
               alloc((void **)&g->views_dev, sizeof(int) * hviews.size()) &&
               alloc((void **)&g->line_order, sizeof(int) * horder.size()) &&
               alloc((void **)&g->T0, sizeof(float) * g->t0_elems) && alloc((void **)&g->T1, sizeof(float) * g->t1_elems) &&
@@ -434,6 +497,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     if (e == hipSuccess) e = hipMemcpy(g->segs, hsegs.data(), sizeof(SegP) * hsegs.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->gsegs, gsegs.data(), sizeof(SegP) * gsegs.size(), hipMemcpyHostToDevice);
     g->n_gseg = (int)gsegs.size();
+    if (e == hipSuccess) e = hipMemcpy(g->gather, hgather.data(), sizeof(GatherSeg) * hgather.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(g->gchunk, hchunks.data(), sizeof(GatherChunk) * hchunks.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->views_dev, hviews.data(), sizeof(int) * hviews.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->line_order, horder.data(), sizeof(int) * horder.size(), hipMemcpyHostToDevice);
     // TOF weight table (FP64 nodes): W at NW_TAB + 1 nodes over |d| <= D = bin/2 + nsig sigma
@@ -484,7 +549,7 @@ extern "C" pet_status pet_geom_destroy(pet_geom g) {
     }
     void *ptrs[] = {g->lines, g->planes, g->segs, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
                     g->grad, g->hess, g->num, g->sensi, g->partial, g->dscratch, g->fscratch, g->psf_a, g->psf_b,
-                    g->check_counts, g->wtab, g->wtabf, g->gsegs};
+                    g->check_counts, g->wtab, g->wtabf, g->gsegs, g->gather, g->gchunk};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete g;

@@ -44,7 +44,7 @@ static_assert(sizeof(LineP) == 32, "LineP layout");
 // One plane (ring pair): z index coordinate of a sample is zb + lambda zs.
 struct PlaneP {
     float zb, zs, dz2;
-    int32_t seg;
+    int32_t q;  // LDS position of the plane's factor in the gather adjoint (within its chunk's region)
 };
 
 // One segment (ring difference): planes p0 .. p0 + np - 1, all with the same
@@ -54,6 +54,33 @@ struct SegP {
     float dz2;
     int32_t pad;
 };
+
+// ---- axial gather of the adjoint (line_sheets.h) ----------------------------
+// Plane (r1, r1 + d) crosses row i of a line at axial position
+//     u = (z_ring0 - z_voxel0) / vz + kappa (r1 + lambda(i) d),  kappa = ring pitch / vz,
+// so in ring units the planes of a segment sit at consecutive integers and a
+// voxel z at t = z / kappa - ring0 - r1_min - lambda d, where it receives the
+// share max(0, 1 - kappa |t - rank|) of each plane.  r1_min is 0 for d >= 0 and
+// -d below, so t = z / kappa - ring0 - Lambda |d| with Lambda = lambda or
+// 1 - lambda.
+//
+// One segment, or at most GATHER_PLANES planes of one: its factors lie in LDS at
+// Qs[qb + lo + 1 ..], zeros around them (one before, two after); positions are
+// shifted by one, so that a truncation is the floor.
+struct GatherSeg {
+    float k;       // |d|
+    float lo, hi;  // clamp of the shifted position: one before its planes, one past them
+    int32_t qb;    // the planes around shifted position t' are Qs[qb + (int)t'] and the next
+};
+static_assert(sizeof(GatherSeg) == 16, "GatherSeg layout");
+// Segments whose factors are in LDS together: all of them unless the planes are
+// very many.  Those with d >= 0 are [s0, s_neg), those below [s_neg, s1).
+struct GatherChunk {
+    int32_t s0, s_neg, s1;
+    int32_t p0, p1;  // their planes
+    int32_t n_q;     // floats of their LDS region
+};
+constexpr int GATHER_PLANES = 1024;
 
 // TOF interval table.  The t axis (signed distance from the LOR centre) is cut
 // at every support edge t_b -/+ (bin/2 + nsig sigma) of a bin's weight; inside
@@ -95,6 +122,14 @@ struct ProjArgs {
     // non-TOF line kernel, M_BACK on a TOF geometry: each sample weighted by
     // the sum of its TOF bins' weights (the backprojection of mult alone)
     int tof_fold;
+    // axial gather
+    const GatherSeg *gather;
+    const GatherChunk *gchunk;
+    int n_gchunk;
+    int gather_two;             // two planes per voxel and segment at most, segments whole (see gather_two)
+    float kappa;                // ring pitch / vz
+    double inv_kappa, rho0;     // shifted position of voxel z before the segment's part: z inv_kappa + rho0
+    float pitch2, k_max;        // squared ring pitch, largest ring difference
 };
 
 // ---- zero-count-aware data term (counts.hip) --------------------------------
@@ -202,6 +237,10 @@ struct pet_geom_s {
     pet::SegP *segs = nullptr;
     pet::SegP *gsegs = nullptr;         // plain segments in plane order (gather adjoint)
     int n_gseg = 0;
+    pet::GatherSeg *gather = nullptr;   // axial gather of the adjoint: segments by chunk, and the chunks
+    pet::GatherChunk *gchunk = nullptr;
+    int n_gchunk = 0, gather_two = 0, q_floats = 0;     // chunks; LDS floats of the largest one's factors
+    double kappa = 1.0, ring0 = 0.0;    // ring pitch / vz; position of voxel 0 in rings, negated
     int n_seg = 0, rows_max = 0, tof_ws = 0, tof_tstride = 0, tof_waves = 0;
     int nt_threads = pet::NT_BLOCK;     // non-TOF line kernel: threads per workgroup
     int *views_dev = nullptr;           // [n_subsets + 1][max(max_views, n_views)]; last row: all views
@@ -217,7 +256,7 @@ struct pet_geom_s {
     float2 *wtab = nullptr;   // TOF weight table: (W_k, W_{k+1} - W_k) at NW_TAB nodes (gather adjoint)
     float *wtabf = nullptr;   // and W at the NW_TAB + 1 nodes (counts kernels)
     float wD = 0.f;
-    size_t lds_bytes = 0;
+    size_t lds_bytes = 0;               // LDS of the TOF line kernels (and the limit checked at creation)
     size_t max_lds = 0;                 // the device's LDS limit per workgroup
     // scratch arena
     float *T0 = nullptr, *T1 = nullptr, *G0 = nullptr, *G1 = nullptr;

@@ -10,9 +10,10 @@
 //      transposed copy of the image so the loads are coalesced;
 //   2. threads take the planes (ring pairs) of the line and walk the samples
 //      with one linear interpolation in z from LDS per sample;
-//   3. the adjoint accumulates Z[i][z] in LDS with LDS atomics and finally
-//      spreads the sheet back over the two transaxial neighbours with global
-//      atomics into a z-contiguous transposed gradient image.
+//   3. the adjoint forms the cells Z[i][z] of the sheet (non-TOF: gathered from
+//      the planes' factors; TOF: accumulated with LDS atomics) and spreads them
+//      over the two transaxial neighbours with global atomics into a
+//      z-contiguous transposed gradient image.
 // TOF: all planes of one ring-difference segment share |u|, hence the signed
 // distance t(i) of every sample and its TOF weights.  One wave takes one
 // segment (one plane per lane), fills a table with the weights of the line's
@@ -21,6 +22,7 @@
 // image in the two non-principal axes, line integral = step length * sum.
 #include "line_sheets.h"
 
+#include <algorithm>
 #include <climits>
 
 namespace pet {
@@ -73,8 +75,6 @@ __device__ __forceinline__ int cut_count(float e, float len, float lam0, float d
 
 // ---------------------------------------------------------------------------
 // Non-TOF: threads over planes (dense), one line per workgroup.
-// One transaxial line (all its planes) of a non-TOF geometry, by the whole
-// workgroup; returns this thread's FP64 partial (KL or sample count).
 __device__ __forceinline__ float clamped_erf(float u, float inv_s, float c) {
     return erff(fminf(fmaxf(u * inv_s, -c), c));
 }
@@ -84,128 +84,168 @@ __device__ __forceinline__ float clamped_erf(float u, float inv_s, float c) {
 // w/2, t_last + w/2] without gaps, so the sum of 1/2 [E(t_b + w/2 - t) -
 // E(t_b - w/2 - t)] telescopes to 1/2 [E(hi - t) - E(lo - t)]; where both
 // ends are clamped (t at least nsig sigma inside [lo, hi]) it is erf(c).
-struct TofFold {
-    float lo, hi, inv_s, c, inside;
+struct LineFold {
+    float lo, hi, inv_s, c, full;
+    float lt2, pitch2, t_in, len_max;
+
+    __device__ __forceinline__ LineFold(const ProjArgs &a, const LineP &L) {
+        const TofTable &T = a.tof;
+        lo = T.tb[0] - T.half_bin;
+        hi = T.tb[T.n_tof - 1] + T.half_bin;
+        inv_s = T.inv_sqrt2_sigma;
+        c = T.erf_clamp;
+        full = erff(c);
+        lt2 = L.lt2;
+        pitch2 = a.pitch2;
+        // |t| up to which both ends are clamped (a margin for its rounding), and
+        // the longest |u| of the line
+        t_in = fminf(hi, -lo) * (1.f - 1e-5f) - c / inv_s;
+        len_max = sqrtf(fmaf(a.k_max * a.k_max, pitch2, lt2)) * (1.f + 1e-5f);
+    }
+    // the samples of the row lie where the sum is `inside` in every segment
+    __device__ __forceinline__ bool constant(float lam) const { return fabsf(lam - 0.5f) * len_max <= t_in; }
+    __device__ __forceinline__ float inside() const { return full; }
+    __device__ __forceinline__ float weight(float lam, float k) const {
+        const float t = (lam - 0.5f) * __builtin_amdgcn_sqrtf(fmaf(k * k, pitch2, lt2));
+        const float e1 = (hi - t) * inv_s, e0 = (lo - t) * inv_s;
+        if (e1 >= c && e0 <= -c) return full;
+        return 0.5f * (erff(fminf(fmaxf(e1, -c), c)) - erff(fminf(fmaxf(e0, -c), c)));
+    }
 };
 
-__device__ __forceinline__ TofFold tof_fold_of(const TofTable &T) {
-    const float h = T.half_bin;
-    return {T.tb[0] - h, T.tb[T.n_tof - 1] + h, T.inv_sqrt2_sigma, T.erf_clamp, erff(T.erf_clamp)};
-}
-
-__device__ __forceinline__ float tof_fold_weight(const TofFold &f, float t) {
-    const float e1 = (f.hi - t) * f.inv_s, e0 = (f.lo - t) * f.inv_s;
-    if (e1 >= f.c && e0 <= -f.c) return f.inside;
-    return 0.5f * (erff(fminf(fmaxf(e1, -f.c), f.c)) - erff(fminf(fmaxf(e0, -f.c), f.c)));
-}
-
+// One transaxial line of a non-TOF geometry, by the whole workgroup; returns
+// this thread's FP64 partial (KL or sample count).
+//
+// Forward: one thread per plane walks the samples of its LOR through the image
+// sheet X.  Adjoint: the planes' factors go to LDS (9 KB for 2204 planes) and
+// the cells of the sheet gather them (gather_cells).
 template <int MODE>
 __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, float *smem, int64_t g_off = 0) {
     constexpr bool NEED_X = MODE != M_BACK && MODE != M_COUNT;
     constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
+    __shared__ int s_special;  // some factor is not finite
     const LineP L = a.lines[line];
     const int nrow = L.i_hi - L.i_lo + 1;
     const int rz = a.rz;
     const int sheet = (a.rows_max * rz + 3) & ~3;
     float *X = smem;
-    double *Z = reinterpret_cast<double *>(smem + (NEED_X ? sheet : 0));
-    if (nrow > 0 && MODE != M_COUNT) build_sheets<NEED_X, NEED_Z>(a, L, nrow, X, Z);
-    __syncthreads();
+    float *Qs = smem + (NEED_X ? sheet : 0);
+    // (a line that misses the image: no adjoint; forward values and terms stay)
+    if (MODE == M_BACK && nrow <= 0) return 0.0;
+    if (nrow > 0 && MODE != M_COUNT) build_sheets<NEED_X, false>(a, L, nrow, X, nullptr);
 
-    // planes in rounds of blockDim threads; the planes of a last, partial round
-    // take c threads each (c a power of two: the threads of a plane are lanes of
-    // one wave), which split its rows and add their forward sums by shuffles
-    const int nb = blockDim.x;
-    const int full = a.n_planes / nb * nb;
-    const int rem = a.n_planes - full;
-    int c = 1;
-    while (rem > 0 && c < 64 && rem * (2 * c) <= nb) c *= 2;
     double kl = 0.0;
-    for (int base = 0; base < a.n_planes; base += nb) {
-        const bool tail = base >= full;
-        const int cc = tail ? c : 1;
-        const int p = base + (tail ? (int)threadIdx.x / c : (int)threadIdx.x);
-        const int ch = tail ? (int)threadIdx.x % c : 0;
-        const bool act = p < a.n_planes;
-        const PlaneP P = a.planes[act ? p : 0];
-        const int64_t lor = (int64_t)line * a.n_planes + p;
-        const float len = sqrtf(L.lt2 + P.dz2);
-        const float ell = L.vm_um * len;
-        int is = 0, ie = -1;
-        if (act && nrow > 0) z_clip(L, P, a.nz, is, ie);
-        if constexpr (MODE == M_COUNT) {
-            if (ch == 0 && ie >= is) kl += (double)(ie - is + 1);
-            continue;
+    const int nb = blockDim.x;
+    for (int ic = 0; ic < (MODE == M_COUNT ? 1 : a.n_gchunk); ++ic) {
+        GatherChunk ch{0, 0, 0, 0, a.n_planes, 0};
+        if (MODE != M_COUNT) ch = a.gchunk[ic];
+        if (NEED_Z) {
+            // (the zeros around the segments; the previous chunk's cells are done)
+            if (ic > 0) __syncthreads();
+            for (int k = threadIdx.x; k < ch.n_q; k += nb) Qs[k] = 0.f;
+            if (threadIdx.x == 0) s_special = 0;
         }
-        // padded axial cell of sample i: u = zA i + zB = z + PADZ, clamped to
-        // [0, nz + 2] (the clamp only guards the LDS bounds; z-clipped samples
-        // lie inside), where truncation is the floor
-        const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
-        const float umax = (float)(a.nz + PADZ);
-        float s = 0.f;
-        if (NEED_X) {
-            const float *xr = X + (is + ch - L.i_lo) * rz;
-            for (int i = is + ch; i <= ie; i += cc, xr += cc * rz) {
-                const float u = __builtin_amdgcn_fmed3f(fmaf((float)i, zA, zB), 0.f, umax);
-                const int j = (int)u;
-                const float x0 = xr[j], x1 = xr[j + 1];
-                s += fmaf(__builtin_amdgcn_fractf(u), x1 - x0, x0);
-            }
-            for (int o = 1; o < cc; o <<= 1) s += __shfl_xor(s, o, 64);
-        }
-        if (!act) continue;
-        const float m = a.mult ? a.mult[lor] : 1.f;
-        float Q = 0.f;
-        if constexpr (MODE == M_BACK) {
-            Q = (a.sino ? a.sino[lor] : 1.f) * m * ell;
-        } else if constexpr (MODE == M_HVP) {
-            // data-term Hessian: mult^2 y / ybar^2 (P v), then back
-            const float yv = load_y(a.y, a.y_dtype, lor);
-            const float yb = a.ybar[lor];
-            Q = yv != 0.f ? m * m * yv / (yb * yb) * (s * ell) * ell : 0.f;
-        } else {
-            float ybar = fmaf(m, s * ell, a.add ? a.add[lor] : 0.f);
-            if constexpr (MODE == M_FWD) {
-                if (ch == 0) a.out[lor] = ybar;
+        if (NEED_Z || (NEED_X && ic == 0)) __syncthreads();
+
+        // planes in rounds of blockDim threads; the planes of a last, partial
+        // round take c threads each (c a power of two: the threads of a plane are
+        // lanes of one wave), which split its rows and add their forward sums by
+        // shuffles
+        const int np = ch.p1 - ch.p0;
+        const int full = NEED_X ? np / nb * nb : np;
+        const int rem = np - full;
+        int c = 1;
+        while (rem > 0 && c < 64 && rem * (2 * c) <= nb) c *= 2;
+        for (int base = 0; base < np; base += nb) {
+            const bool tail = base >= full;
+            const int cc = tail ? c : 1;
+            const int rank = base + (tail ? (int)threadIdx.x / c : (int)threadIdx.x);
+            const int cs = tail ? (int)threadIdx.x % c : 0;
+            const bool act = rank < np;
+            const int p = ch.p0 + (act ? rank : 0);
+            const PlaneP P = a.planes[p];
+            const int64_t lor = (int64_t)line * a.n_planes + p;
+            const float len = sqrtf(L.lt2 + P.dz2);
+            const float ell = L.vm_um * len;
+            int is = 0, ie = -1;
+            if ((NEED_X || MODE == M_COUNT) && act && nrow > 0) z_clip(L, P, a.nz, is, ie);
+            if constexpr (MODE == M_COUNT) {
+                if (cs == 0 && ie >= is) kl += (double)(ie - is + 1);
                 continue;
+            }
+            float s = 0.f;
+            if (NEED_X) {
+                // padded axial cell of sample i: u = zA i + zB = z + PADZ, clamped
+                // to [0, nz + 2] (the clamp only guards the LDS bounds; z-clipped
+                // samples lie inside), where truncation is the floor; two samples
+                // per iteration, their LDS reads in flight together
+                const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
+                const float umax = (float)(a.nz + PADZ);
+                const float fc = (float)cc, fie = (float)ie;
+                const int step = cc * rz;
+                const float *xr = X + (is + cs - L.i_lo) * rz;
+                float fi = (float)(is + cs), s1 = 0.f;
+                for (; fi + fc <= fie; fi += 2.f * fc, xr += 2 * step) {
+                    const float u0 = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
+                    const float u1 = __builtin_amdgcn_fmed3f(fmaf(fi + fc, zA, zB), 0.f, umax);
+                    const int j0 = (int)u0, j1 = (int)u1;
+                    const float a0 = xr[j0], b0 = xr[j0 + 1], a1 = xr[step + j1], b1 = xr[step + j1 + 1];
+                    s += fmaf(__builtin_amdgcn_fractf(u0), b0 - a0, a0);
+                    s1 += fmaf(__builtin_amdgcn_fractf(u1), b1 - a1, a1);
+                }
+                if (fi <= fie) {
+                    const float u = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
+                    const int j = (int)u;
+                    const float x0 = xr[j], x1 = xr[j + 1];
+                    s += fmaf(__builtin_amdgcn_fractf(u), x1 - x0, x0);
+                }
+                s += s1;
+                for (int o = 1; o < cc; o <<= 1) s += __shfl_xor(s, o, 64);
+            }
+            if (!act || cs != 0) continue;
+            const float m = a.mult ? a.mult[lor] : 1.f;
+            float Q = 0.f;
+            if constexpr (MODE == M_BACK) {
+                Q = (a.sino ? a.sino[lor] : 1.f) * m * ell;
+            } else if constexpr (MODE == M_HVP) {
+                // data-term Hessian: mult^2 y / ybar^2 (P v), then back
+                const float yv = load_y(a.y, a.y_dtype, lor);
+                const float yb = a.ybar[lor];
+                Q = yv != 0.f ? m * m * yv / (yb * yb) * (s * ell) * ell : 0.f;
             } else {
-                float yv = load_y(a.y, a.y_dtype, lor);
-                if (a.partial && ch == 0) kl += kl_term(ybar, yv);
-                // a bin without counts has d(s, 0) = s: derivative 1 and EM ratio 0,
-                // also where ybar = 0 (no 0 * inf)
-                if constexpr (MODE == M_GRAD) Q = m * (yv != 0.f ? 1.f - yv / ybar : 1.f) * ell;
-                if constexpr (MODE == M_EM) Q = yv != 0.f ? m * (yv / ybar) * ell : 0.f;
+                const float ybar = fmaf(m, s * ell, a.add ? a.add[lor] : 0.f);
+                if constexpr (MODE == M_FWD) {
+                    a.out[lor] = ybar;
+                } else {
+                    const float yv = load_y(a.y, a.y_dtype, lor);
+                    if (a.partial) kl += kl_term(ybar, yv);
+                    // a bin without counts has d(s, 0) = s: derivative 1 and EM ratio 0,
+                    // also where ybar = 0 (no 0 * inf)
+                    if constexpr (MODE == M_GRAD) Q = m * (yv != 0.f ? 1.f - yv / ybar : 1.f) * ell;
+                    if constexpr (MODE == M_EM) Q = yv != 0.f ? m * (yv / ybar) * ell : 0.f;
+                }
+            }
+            if (NEED_Z) {
+                Qs[P.q] = Q;
+                if (!(fabsf(Q) < INFINITY)) s_special = 1;
             }
         }
-        if constexpr (NEED_Z) {
-            double *zr = Z + (is + ch - L.i_lo) * rz;
-            if (MODE == M_BACK && a.tof_fold) {
-                // TOF: sample i at t = (lambda(i) - 1/2) |u| carries the sum of
-                // its bins' weights (uniform branch)
-                const TofFold F = tof_fold_of(a.tof);
-                for (int i = is + ch; i <= ie; i += cc, zr += cc * rz) {
-                    const float u = __builtin_amdgcn_fmed3f(fmaf((float)i, zA, zB), 0.f, umax);
-                    const int j = (int)u;
-                    const float t = (fmaf((float)i, L.dlam, L.lam0) - 0.5f) * len;
-                    const float q = Q * tof_fold_weight(F, t);
-                    const float a1 = q * __builtin_amdgcn_fractf(u);
-                    atomicAdd(&zr[j], (double)(q - a1));
-                    atomicAdd(&zr[j + 1], (double)a1);
-                }
-            } else {
-                for (int i = is + ch; i <= ie; i += cc, zr += cc * rz) {
-                    const float u = __builtin_amdgcn_fmed3f(fmaf((float)i, zA, zB), 0.f, umax);
-                    const int j = (int)u;
-                    const float a1 = Q * __builtin_amdgcn_fractf(u);
-                    atomicAdd(&zr[j], (double)(Q - a1));
-                    atomicAdd(&zr[j + 1], (double)a1);
-                }
-            }
-        }
-    }
-    if (NEED_Z && nrow > 0) {
+        if (!NEED_Z) continue;
         __syncthreads();
-        scatter_sheet(a, L, nrow, Z, g_off);
+        if (nrow <= 0) continue;
+        const bool many = s_special || !a.gather_two;  // (uniform)
+        const LineFold F(a, L);
+        if (MODE == M_BACK && a.tof_fold) {
+            if (many)
+                gather_cells<true, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F);
+            else
+                gather_cells<false, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F);
+        } else {
+            if (many)
+                gather_cells<true, false>(a, L, nrow, Qs, ch, g_off, F);
+            else
+                gather_cells<false, false>(a, L, nrow, Qs, ch, g_off, F);
+        }
     }
     return kl;
 }
@@ -763,13 +803,22 @@ __global__ void __launch_bounds__(64 * TOF_MAX_WAVES) k_line_batched(const BMemb
     }
 }
 
+// LDS of the non-TOF line kernel: the image sheet (modes that project) and the
+// planes' factors (modes that backproject).
+template <int MODE>
+size_t nt_lds(const pet_geom_s *g) {
+    if (MODE == M_COUNT) return 0;
+    const size_t sheet = ((size_t)g->rows_max * (g->d.nz + 2 * PADZ) + 3) & ~(size_t)3;
+    const bool x = MODE != M_BACK, q = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
+    return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0));
+}
+
 template <int MODE>
 hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
-    const size_t lds = MODE == M_COUNT ? 0 : g->lds_bytes;
     if (g->d.n_tof > 1)
-        hipLaunchKernelGGL((k_line_tof<MODE>), grid, dim3(64 * g->tof_waves), lds, s, a);
+        hipLaunchKernelGGL((k_line_tof<MODE>), grid, dim3(64 * g->tof_waves), MODE == M_COUNT ? 0 : g->lds_bytes, s, a);
     else
-        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(g->nt_threads), lds, s, a);
+        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(g->nt_threads), nt_lds<MODE>(g), s, a);
     return hipGetLastError();
 }
 
@@ -793,19 +842,17 @@ void set_lds_attr(size_t need) {
 }
 
 // TOF backprojection of mult alone (the sensitivity P^T mult, no sinogram):
-// with the bins' weights summed per sample, the non-TOF walk does it, one
-// sample loop per LOR instead of one per TOF bin.  Its FP64 gradient sheet
-// (rows_max x rz) is the only LDS it needs, less than the TOF kernels'.
+// with the bins' weights summed per sample, the non-TOF kernel does it, one
+// share per LOR and cell instead of one per TOF bin.
 hipError_t launch_back_fold(const pet_geom_s *g, dim3 grid, const ProjArgs &a0, hipStream_t s) {
     ProjArgs a = a0;
     a.tof_fold = 1;
-    const size_t lds = sizeof(double) * (((size_t)g->rows_max * (g->d.nz + 2 * PADZ) + 3) & ~(size_t)3);
-    hipLaunchKernelGGL((k_line_nt<M_BACK>), grid, dim3(g->nt_threads), lds, s, a);
+    hipLaunchKernelGGL((k_line_nt<M_BACK>), grid, dim3(g->nt_threads), nt_lds<M_BACK>(g), s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_line_kernel_impl(const pet_geom_s *g, int mode, dim3 grid, const ProjArgs &a, hipStream_t s) {
-    set_lds_attr(g->lds_bytes);
+    set_lds_attr(std::max(g->lds_bytes, nt_lds<M_GRAD>(g)));
     switch (mode) {
         case M_FWD: return launch_mode<M_FWD>(g, grid, a, s);
         case M_BACK:
