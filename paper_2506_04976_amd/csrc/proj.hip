@@ -250,8 +250,13 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
     return kl;
 }
 
+// (Eight waves per SIMD, for the scalar registers: left alone the compiler takes
+// 106 of them, which lets seven waves onto a SIMD and so one workgroup of 1024 on
+// a CU; with 78 there are two, and one walks while the other waits: a 3D subset
+// gradient of 128 x 128 x 71 voxels and 2204 planes 387 -> 304 us, its sensitivity
+// over all views 3785 -> 3380 us.)
 template <int MODE>
-__global__ void __launch_bounds__(NT_BLOCK) k_line_nt(ProjArgs a) {
+__global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
     extern __shared__ float4 smem4[];
     // one line per workgroup, the launch's lines longest first
     const double kl = line_nt_body<MODE>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4));
