@@ -125,11 +125,9 @@ pet_status pet_fwd(pet_geom g, int subset, const float *x, const float *mult, co
  * the preconditioner of eq. (preconditioner)): x_out (+)= P_subset^T (mult * sino).
  * sino NULL means all ones (so pet_back(g, -1, NULL, mult, sens, 0, ...) gives
  * the sensitivity A^T 1).  accumulate = 0 overwrites x_out.  algo:
- *   PET_BACK_SCATTER  the line kernels of the fused gradients: with TOF, each
- *                     sample of each LOR adds its two axial interpolation shares
- *                     to an LDS sheet of its line with FP64 LDS atomics; without
- *                     TOF, and for the sensitivity, the cells of the sheet gather
- *                     the shares of each segment's planes;
+ *   PET_BACK_SCATTER  the line kernels of the fused gradients: the cells of each
+ *                     line's sheet collect the planes' (with TOF, the bins')
+ *                     factors, row by row, and are spread transaxially
  *   PET_BACK_GATHER   cell-driven gather: each sheet cell sums, without
  *                     atomics, the shares of the samples that land on it,
  *                     found from each segment's affine axial map (TOF weights

@@ -40,11 +40,7 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.lines = g->lines;
     a.planes = g->planes;
     a.views = views_of(g, subset);
-    a.segs = g->segs;
-    a.n_seg = g->n_seg;
     a.rows_max = g->rows_max;
-    a.ws = g->tof_ws;
-    a.tstride = g->tof_tstride;
     a.n_rad = g->d.n_rad;
     a.n_planes = g->n_planes;
     a.nx = g->d.nx;
@@ -65,6 +61,20 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.rho0 = g->ring0 + 1.0;
     a.pitch2 = (float)(g->d.ring_pitch_mm * g->d.ring_pitch_mm);
     a.k_max = (float)g->d.max_ring_diff;
+    a.units = g->units;
+    a.n_units = g->n_units;
+    a.bins_blk = g->bins_blk;
+    a.q_units = g->q_units;
+    a.unit_floats = g->unit_floats;
+    a.x_stride = g->x_stride;
+    a.inv_nt = (65536 + g->d.n_tof - 1) / g->d.n_tof;
+    a.etab = g->etab;
+    a.n_etab = g->n_etab;
+    a.e_scale = g->e_scale;
+    a.e_mid = 0.5f * (float)g->n_etab;
+    a.dpos = (float)(g->d.tof_bin_mm * g->e_scale);
+    a.dpos_hi = high_part(a.dpos);
+    a.dpos_lo = (float)((double)g->d.tof_bin_mm * g->e_scale - a.dpos_hi);
     a.order = g->line_order + g->order_off[subset < 0 ? g->d.n_subsets : subset];
     return a;
 }

@@ -25,14 +25,14 @@ struct pet_batch_s {
     std::vector<pet_svrg_state *> states;
     std::vector<float *> slots;
     std::vector<int *> sub_nviews;
-    std::vector<size_t> lds_base, lds_per_wave;  // per member: sheets + one wave's table
-    std::vector<int> tof_waves;
+    std::vector<size_t> lds_base, lds_per_wave;  // per member: sheets and factors, and what each wave adds
     std::vector<double> line_cost;
+    BatchForm form;
     BMember *d_mem = nullptr;
     BStep *d_steps = nullptr, *h_steps = nullptr;
     int max_steps = 0;
     int *d_order = nullptr, *d_counter = nullptr;
-    int blocks = 0, waves = TOF_MAX_WAVES, order_kind = 0;
+    int blocks = 0, waves = MAX_WAVES, order_kind = 0;
     int psf_max = 0;  // most resolution-model passes of any member
     hipStream_t stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -45,7 +45,7 @@ namespace {
 
 size_t batch_lds(const pet_batch_s *b, int waves) {
     size_t m = 0;
-    for (int r = 0; r < b->n; ++r) m = std::max(m, b->lds_base[r] + (size_t)std::min(b->tof_waves[r], waves) * b->lds_per_wave[r]);
+    for (int r = 0; r < b->n; ++r) m = std::max(m, b->lds_base[r] + (size_t)waves * b->lds_per_wave[r]);
     return m;
 }
 
@@ -67,7 +67,7 @@ void drop_graph(pet_batch_s *b) {
 hipError_t enqueue_step(pet_batch_s *b, int j, hipStream_t s) {
     hipError_t e = launch_b_prep(b->d_mem, b->n, j, b->d_counter, b->psf_max, s);
     if (e == hipSuccess)
-        e = launch_line_batched(b->d_mem, b->d_order, b->n, j, b->d_counter, b->blocks, b->waves,
+        e = launch_line_batched(b->form, b->d_mem, b->d_order, b->n, j, b->d_counter, b->blocks, b->waves,
                                 batch_lds(b, b->waves), s);
     if (e == hipSuccess) e = launch_b_gather(b->d_mem, b->n, j, b->psf_max, s);
     if (e == hipSuccess) e = launch_b_step(b->d_mem, b->n, j, s);
@@ -177,7 +177,11 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         m.n_sub = g->d.n_subsets;
         m.n_views = g->d.n_views;
         m.is_tof = g->d.n_tof > 1;
-        m.tof_waves = m.is_tof ? g->tof_waves : 1;
+        if (m.is_tof) {
+            b->form.n_tof = std::max(b->form.n_tof, (int)g->d.n_tof);
+            b->form.nz = std::max(b->form.nz, (int)g->d.nz);
+            b->form.gather_two &= m.pa.gather_two != 0;
+        }
         m.nx = g->d.nx;
         m.ny = g->d.ny;
         m.nz = g->d.nz;
@@ -207,17 +211,10 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         m.psf_b = g->psf_b;
         b->psf_max = std::max(b->psf_max, g->psf_passes);
         if (g->psf_passes && slot < 2 * (int64_t)g->n_vox) e = hipErrorInvalidValue;
-        // LDS of the line bodies: sheets, plus one TOF table per wave
-        const int rz = g->d.nz + 2 * PADZ;
-        const size_t sheet = ((size_t)g->rows_max * rz + 3) & ~(size_t)3;
-        b->lds_base.push_back(std::max(3 * sheet, sheet + (m.is_tof ? 0 : (size_t)g->q_floats)) * sizeof(float));
-        size_t pw = 0;
-        if (m.is_tof) {
-            const int e1 = g->tof_ws > 4 ? g->tof_ws - 4 : 0;
-            pw = (((size_t)g->rows_max * (4 + e1) + tof_cuts_pad(g->tof.n_int) + 3) & ~(size_t)3) * sizeof(float);
-        }
-        b->lds_per_wave.push_back(pw);
-        b->tof_waves.push_back(m.tof_waves);
+        // LDS of the line bodies
+        const size_t sheet = ((size_t)g->rows_max * (g->d.nz + 2 * PADZ) + 3) & ~(size_t)3;
+        b->lds_base.push_back(m.is_tof ? tof_lds_bytes(g, true, g->q_units, 0) : (sheet + (size_t)g->q_floats) * sizeof(float));
+        b->lds_per_wave.push_back(m.is_tof ? TOF_STAGE_FLOATS * sizeof(float) : 0);
         b->line_cost.push_back((double)g->n_planes * g->rows_max * (m.is_tof ? 4.0 : 1.0));
     }
     if (e == hipSuccess) e = hipMalloc(&b->d_steps, sizeof(BStep) * (size_t)n_members * b->max_steps);
@@ -241,7 +238,7 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         destroy(b);
         return fail(PET_E_ARG, "pet_batch_create: a member's line sheets exceed the LDS");
     }
-    if (e == hipSuccess) e = prime_line_batched(batch_lds(b, b->waves));
+    if (e == hipSuccess) e = prime_line_batched(b->form, batch_lds(b, b->waves));
     if (e != hipSuccess) {
         destroy(b);
         return hip_check(e, "pet_batch_create");
@@ -357,7 +354,7 @@ extern "C" pet_status pet_batch_autotune(pet_batch b, int *config_out, double *b
                     e = launch_b_prep(b->d_mem, b->n, 0, b->d_counter, b->psf_max, b->stream);
                     if (e == hipSuccess) e = hipEventRecord(b->ev_t0, b->stream);
                     if (e == hipSuccess)
-                        e = launch_line_batched(b->d_mem, b->d_order, b->n, 0, b->d_counter, b->blocks, b->waves,
+                        e = launch_line_batched(b->form, b->d_mem, b->d_order, b->n, 0, b->d_counter, b->blocks, b->waves,
                                                 batch_lds(b, b->waves), b->stream);
                     if (e == hipSuccess) e = hipEventRecord(b->ev_t1, b->stream);
                     if (e == hipSuccess) e = hipEventSynchronize(b->ev_t1);
@@ -397,7 +394,7 @@ extern "C" pet_status pet_batch_autotune(pet_batch b, int *config_out, double *b
 
 extern "C" pet_status pet_batch_set_launch(pet_batch b, int workgroups, int waves, int order) {
     if (!b) return fail(PET_E_ARG, "pet_batch_set_launch: null batch");
-    if (workgroups < 1 || waves < 1 || waves > TOF_MAX_WAVES || (order != 0 && order != 1))
+    if (workgroups < 1 || waves < 1 || waves > MAX_WAVES || (order != 0 && order != 1))
         return fail(PET_E_ARG, "pet_batch_set_launch: workgroups >= 1, 1 <= waves <= 16, order 0 or 1");
     int max_lds = 0;
     hipError_t e = hipSetDevice(b->device);

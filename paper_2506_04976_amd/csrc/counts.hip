@@ -299,7 +299,7 @@ __device__ __forceinline__ void scatter_rows_parity(const ProjArgs &a, const Lin
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
     if (rz <= (int)blockDim.x) {
-        const SheetWalk w = sheet_walk(rz);
+        const SheetWalk w = sheet_walk(rz, threadIdx.x);
         if (!w.on) return;
         for (int k = w.r0; k < nh; k += w.R) {
             const float val = packed_cell_value<SIGNED>(Zu, k * rz + w.zp, w.zp, inv_scale, finite);
@@ -330,16 +330,16 @@ __device__ __forceinline__ int lanes_per_bin(int n_c) {
 constexpr int CNT_SHEET_ROWS = 8;
 
 // Image sheet X of a line (rows [0, nrow), padded axial positions [0, rz)):
-// the transaxial interpolation of the transposed image, as build_sheets.
+// the transaxial interpolation of the transposed image, as build_sheet.
 __device__ __forceinline__ void build_x(const ProjArgs &a, const LineP &L, int nrow, float *X) {
     const int rz = a.rz;
     if (rz > (int)blockDim.x) {
-        build_sheets<true, false>(a, L, nrow, X, nullptr);
+        build_sheet(a, L, nrow, X, rz, threadIdx.x);
         return;
     }
     const float *T = L.axis ? a.T1 : a.T0;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
-    const SheetWalk sw = sheet_walk(rz);
+    const SheetWalk sw = sheet_walk(rz, threadIdx.x);
     if (!sw.on) return;
     for (int rb = sw.r0; rb < nrow; rb += CNT_SHEET_ROWS * sw.R) {
         float t0[CNT_SHEET_ROWS], t1[CNT_SHEET_ROWS], tf[CNT_SHEET_ROWS];

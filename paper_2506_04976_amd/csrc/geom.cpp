@@ -277,13 +277,11 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     }
 
     // segments (contiguous plane ranges of equal ring difference)
-    std::vector<SegP> hsegs;
+    std::vector<SegP> gsegs;
     for (size_t p = 0; p < planes.size(); ++p) {
-        if (hsegs.empty() || planes[p].seg != planes[p - 1].seg) hsegs.push_back({(int)p, 0, hplanes[p].dz2, 0});
-        hsegs.back().np++;
+        if (gsegs.empty() || planes[p].seg != planes[p - 1].seg) gsegs.push_back({(int)p, 0, hplanes[p].dz2, 0});
+        gsegs.back().np++;
     }
-    // the plain segment list in plane order (the gather adjoint walks it)
-    const std::vector<SegP> gsegs = hsegs;
     // Axial gather of the adjoint: segments in parts of at most GATHER_PLANES
     // planes, in chunks whose factors fit the LDS beside the image sheet.  The
     // cap holds every plane of any scanner here (2204 planes take 9 KB); it
@@ -345,49 +343,23 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     g->gather_two = (float)g->kappa >= 1.f;
     for (const SegP &sg : gsegs)
         if (sg.np > GATHER_PLANES) g->gather_two = 0;
-    if (d.n_tof > 1) {
-        // segments -k and +k (adjacent in the plane order) have the same
-        // oblique length and so the same TOF weight table: one segment wave
-        // takes both when their planes fit in its 64 lanes
-        std::vector<SegP> merged;
-        for (const SegP &sg : hsegs) {
-            const int k = std::abs(planes[sg.p0].r2 - planes[sg.p0].r1);
-            if (!merged.empty()) {
-                SegP &m = merged.back();
-                // (the last group must still be a single segment)
-                if (k > 0 && std::abs(planes[m.p0].r2 - planes[m.p0].r1) == k && m.p0 + m.np == sg.p0 &&
-                    planes[m.p0].seg == planes[m.p0 + m.np - 1].seg && m.np + sg.np <= 64) {
-                    m.np += sg.np;
-                    continue;
-                }
-            }
-            merged.push_back(sg);
-        }
-        hsegs.swap(merged);
-    }
-    g->n_seg = (int)hsegs.size();
     g->rows_max = rows_max;
     // non-TOF: one thread per plane, in as many waves as the planes need (up to
     // 16; more resident waves hide the LDS latency of the sample loop)
     g->nt_threads = std::min(NT_BLOCK, std::max(64, (g->n_planes + 63) / 64 * 64));
+    int ws = 1;
     if (d.n_tof > 1) {
-        for (auto &sg : hsegs)
+        for (const SegP &sg : gsegs)
             if (sg.np > 64) {
                 delete g;
                 return fail(PET_E_ARG, "pet_geom_create: TOF needs at most 64 planes per segment (one wave)");
             }
-        int ws = 1;
         for (int s = 0; s < T.n_int; ++s) ws = std::max(ws, T.na[s]);
-        g->tof_ws = ws;
-        // as many segment waves as the LDS holds (up to 16): the line body
-        // waits on LDS latency, and more resident waves hide it better than an
-        // even number of segments per wave saves
-        g->tof_waves = std::min(g->n_seg, TOF_MAX_WAVES);
     }
 
-    // LDS need of the line kernels: image sheet (float) + gradient sheet
-    // (double) + per-wave TOF tables (weights [rows][4] + [rows][ws - 4] +
-    // interval cuts).  Fewer TOF waves are used if the tables do not fit.
+    // Largest image served: three sheets of floats in LDS and, with TOF, four
+    // to eight floats per row and the bins' support edges (the line kernels
+    // themselves need less).
     int rz = d.nz + 2 * PADZ;
     size_t sheet = ((size_t)rows_max * rz + 3) & ~(size_t)3;
     int max_lds = 0;
@@ -395,70 +367,80 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     if (max_lds <= 0) max_lds = 64 * 1024;
     g->max_lds = (size_t)max_lds;
     size_t need = 3 * sheet * sizeof(float);
-    if (d.n_tof > 1) {
-        int e1 = g->tof_ws > 4 ? g->tof_ws - 4 : 0;
-        size_t per_wave = (((size_t)rows_max * (4 + e1) + tof_cuts_pad(g->tof.n_int) + 3) & ~(size_t)3) * sizeof(float);
-        if (need + per_wave <= (size_t)max_lds) {
-            int fit = (int)(((size_t)max_lds - need) / per_wave);
-            if (fit < g->tof_waves) g->tof_waves = fit;
-        } else {
-            g->tof_waves = 1;
-        }
-        need += (size_t)g->tof_waves * per_wave;
-    }
-    g->lds_bytes = need;
-    // Segment order of the TOF line kernel, whose wave w takes entries w,
-    // w + W, w + 2W, ... (W waves): the two halves -k and +k of a pair of
-    // single segments have the same oblique length and so the same weight
-    // table, and go to consecutive rounds of one wave, which then fills the
-    // table once (both carry the same squared axial extent).  The other
-    // entries keep their relative order.
-    if (d.n_tof > 1 && g->tof_waves > 1) {
-        const int W = g->tof_waves, ns = (int)hsegs.size();
-        auto ring_k = [&](const SegP &sg) { return std::abs(planes[sg.p0].r2 - planes[sg.p0].r1); };
-        auto single = [&](const SegP &sg) { return planes[sg.p0].seg == planes[sg.p0 + sg.np - 1].seg; };
-        std::vector<int> cap(W);
-        for (int w = 0; w < W; ++w) cap[w] = ns / W + (w < ns % W ? 1 : 0);
-        std::vector<std::vector<int>> lists(W);
-        std::vector<int> rest;
-        int w = 0;
-        for (int i = 0; i < ns; ++i) {
-            const bool pair = i + 1 < ns && single(hsegs[i]) && single(hsegs[i + 1]) && ring_k(hsegs[i]) > 0 &&
-                              ring_k(hsegs[i]) == ring_k(hsegs[i + 1]);
-            if (!pair) {
-                rest.push_back(i);
-                continue;
-            }
-            hsegs[i + 1].dz2 = hsegs[i].dz2;
-            int tries = 0;
-            while (tries < W && (int)lists[w].size() + 2 > cap[w]) {
-                w = (w + 1) % W;
-                ++tries;
-            }
-            if (tries < W) {
-                lists[w].push_back(i);
-                lists[w].push_back(i + 1);
-                w = (w + 1) % W;
-            } else {
-                rest.push_back(i);
-                rest.push_back(i + 1);
-            }
-            ++i;
-        }
-        // the remaining entries fill the free slots in position order
-        size_t next = 0;
-        for (int r = 0; r <= ns / W; ++r)
-            for (int v = 0; v < W; ++v)
-                if (r < cap[v] && r >= (int)lists[v].size()) lists[v].push_back(rest[next++]);
-        std::vector<SegP> ordered(ns);
-        for (int v = 0; v < W; ++v)
-            for (size_t r = 0; r < lists[v].size(); ++r) ordered[r * W + v] = hsegs[lists[v][r]];
-        hsegs.swap(ordered);
-    }
-    if (g->lds_bytes > (size_t)max_lds) {
+    if (d.n_tof > 1)
+        need += (((size_t)rows_max * std::max(4, ws) + ((T.n_int + 1 + 3) & ~3) + 3) & ~(size_t)3) * sizeof(float);
+    if (need > (size_t)max_lds) {
         delete g;
         return fail(PET_E_ARG, "pet_geom_create: image too large for the LDS sheets of the line kernels (" +
-                                   std::to_string(g->lds_bytes) + " > " + std::to_string(max_lds) + " bytes)");
+                                   std::to_string(need) + " > " + std::to_string(max_lds) + " bytes)");
+    }
+
+    // TOF line kernels: units, LDS split, table of the halved clamped erf
+    std::vector<TofUnit> hunits;
+    std::vector<float4> hetab;
+    if (d.n_tof > 1) {
+        auto ring_d = [&](const SegP &sg) { return planes[sg.p0].r2 - planes[sg.p0].r1; };
+        int max_np = 0;
+        for (const SegP &sg : gsegs) {
+            const int k = std::abs(ring_d(sg)), neg = ring_d(sg) < 0;
+            if (!hunits.empty()) {
+                // segments -k and +k are adjacent in the plane order; they have
+                // the same oblique length, so a pair that fits 64 lanes is one
+                // unit (its weights are formed once)
+                TofUnit &m = hunits.back();
+                if (k > 0 && m.n1 == m.np && (int)m.k == k && m.p0 + m.np == sg.p0 && m.np + sg.np <= 64) {
+                    m.np = (uint8_t)(m.np + sg.np);
+                    max_np = std::max(max_np, (int)m.np);
+                    continue;
+                }
+            }
+            hunits.push_back({sg.p0, (uint8_t)sg.np, (uint8_t)sg.np, (uint8_t)neg, 0, sg.dz2, (float)k});
+            max_np = std::max(max_np, sg.np);
+        }
+        g->n_units = (int)hunits.size();
+        g->bins_blk = d.n_tof <= 16 ? d.n_tof : (d.n_tof + 1) / 2;
+        g->unit_floats = (max_np + 15) / 16 * 16 * d.n_tof;
+        // E(x) = erf(x) on [-c, c], c the kernel's truncation (erf is constant in
+        // 32 bits past 4.2): cubics between nodes at most 1/32 apart, from the
+        // values and slopes there (error at most h^4 / 384 times the fourth
+        // derivative, below 1e-8)
+        const double c = std::min(d.tof_nsigma / std::sqrt(2.0), 4.2);
+        const int N = 32 * (int)std::ceil(2.0 * c);
+        g->n_etab = N;
+        g->e_scale = N / (2.0 * c) / (std::sqrt(2.0) * d.tof_sigma_mm);
+        const double h = 2.0 * c / N;
+        for (int k = 0; k <= N; ++k) {
+            const double x0 = -c + k * h, x1 = x0 + h;
+            const double e0 = 0.5 * std::erf(x0), e1 = 0.5 * std::erf(x1);
+            const double s0 = h * std::exp(-x0 * x0) / std::sqrt(M_PI), s1 = h * std::exp(-x1 * x1) / std::sqrt(M_PI);
+            if (k == N)
+                hetab.push_back(make_float4((float)e0, 0.f, 0.f, 0.f));
+            else
+                hetab.push_back(make_float4((float)e0, (float)s0, (float)(3.0 * (e1 - e0) - 2.0 * s0 - s1),
+                                            (float)(s0 + s1 - 2.0 * (e1 - e0))));
+        }
+        // (the filled rows where they take at most half of the LDS)
+        g->x_stride = tof_x_stride(rz);
+        if (sizeof(float) * (size_t)tof_x_floats(rows_max, g->x_stride) > (size_t)max_lds / 2) g->x_stride = rz;
+        // Units whose factors are in LDS together: as many as let two workgroups
+        // share a CU if that is four or more, else as many as fit (with room for
+        // a batch's sixteen waves); then evenly over the rounds.  (One workgroup
+        // per CU with all units at once: 1276 us against 863 for a subset gradient
+        // of 128 x 128 x 71 voxels and 13 bins, 915 against 601 with 161 x 161 x 33
+        // and 25: its waves wait for each other at the ends of the phases.)
+        const size_t unit = sizeof(float) * (size_t)g->unit_floats, stage = sizeof(float) * TOF_STAGE_FLOATS;
+        const size_t fixed = sizeof(float) * (size_t)tof_x_floats(rows_max, g->x_stride) +
+                             sizeof(float4) * (size_t)(N + 1 + 2 * g->n_units);
+        auto fit = [&](size_t lds, size_t waves) {
+            const size_t used = fixed + waves * stage + 512;
+            return lds > used ? (int)((lds - used) / unit) : 0;
+        };
+        const int most = fit((size_t)max_lds, MAX_WAVES);
+        int q = fit(CU_LDS_BYTES / 2, TOF_BLOCK / 64);
+        if (q < std::min(4, g->n_units)) q = most;
+        q = std::max(1, std::min({q, most, g->n_units}));
+        const int rounds = (g->n_units + q - 1) / q;
+        g->q_units = (g->n_units + rounds - 1) / rounds;
     }
 
     // device allocations
@@ -472,7 +454,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     // line-kernel partials (2 per line) or two per image block (BB dots)
     g->n_partial = std::max<size_t>(2 * (size_t)nl, 2 * (size_t)((g->n_vox + IMG_BLOCK - 1) / IMG_BLOCK)) + 64;
     bool ok = alloc((void **)&g->lines, sizeof(LineP) * nl) && alloc((void **)&g->planes, sizeof(PlaneP) * planes.size()) &&
-              alloc((void **)&g->segs, sizeof(SegP) * hsegs.size()) &&
+              alloc((void **)&g->units, sizeof(TofUnit) * hunits.size()) &&
+              alloc((void **)&g->etab, sizeof(float4) * hetab.size()) &&
               alloc((void **)&g->gsegs, sizeof(SegP) * gsegs.size()) &&
               alloc((void **)&g->gather, sizeof(GatherSeg) * hgather.size()) &&
               alloc((void **)&g->gchunk, sizeof(GatherChunk) * hchunks.size()) &&
@@ -494,7 +477,10 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     }
     hipError_t e = hipMemcpy(g->lines, hlines.data(), sizeof(LineP) * nl, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->planes, hplanes.data(), sizeof(PlaneP) * planes.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(g->segs, hsegs.data(), sizeof(SegP) * hsegs.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !hunits.empty())
+        e = hipMemcpy(g->units, hunits.data(), sizeof(TofUnit) * hunits.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !hetab.empty())
+        e = hipMemcpy(g->etab, hetab.data(), sizeof(float4) * hetab.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->gsegs, gsegs.data(), sizeof(SegP) * gsegs.size(), hipMemcpyHostToDevice);
     g->n_gseg = (int)gsegs.size();
     if (e == hipSuccess) e = hipMemcpy(g->gather, hgather.data(), sizeof(GatherSeg) * hgather.size(), hipMemcpyHostToDevice);
@@ -547,7 +533,7 @@ extern "C" pet_status pet_geom_destroy(pet_geom g) {
         (void)hipEventDestroy(e.first);
         (void)hipEventDestroy(e.second);
     }
-    void *ptrs[] = {g->lines, g->planes, g->segs, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
+    void *ptrs[] = {g->lines, g->planes, g->units, g->etab, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
                     g->grad, g->hess, g->num, g->sensi, g->partial, g->dscratch, g->fscratch, g->psf_a, g->psf_b,
                     g->check_counts, g->wtab, g->wtabf, g->gsegs, g->gather, g->gchunk};
     for (void *p : ptrs)

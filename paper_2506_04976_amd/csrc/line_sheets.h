@@ -6,6 +6,13 @@
 #include "pet_internal.h"
 
 namespace pet {
+
+// A table entry that no kernel writes, by scalar loads (its address is uniform).
+template <typename T>
+__device__ __forceinline__ const T &scalar_ref(const T &t) {
+    return *(const T *)(const T __attribute__((address_space(4))) *)(uintptr_t)&t;
+}
+
 namespace {
 
 // Sample range [is, ie] of a LOR restricted to samples whose z coordinate can
@@ -40,11 +47,11 @@ struct SheetWalk {
     bool on;
 };
 
-__device__ __forceinline__ SheetWalk sheet_walk(int rz) {
+__device__ __forceinline__ SheetWalk sheet_walk(int rz, int tid) {
     SheetWalk w;
     w.R = (int)blockDim.x / rz;
-    w.r0 = (int)threadIdx.x / rz;
-    w.zp = (int)threadIdx.x - w.r0 * rz;
+    w.r0 = tid / rz;
+    w.zp = tid - w.r0 * rz;
     w.on = w.r0 < w.R;
     return w;
 }
@@ -66,57 +73,49 @@ __device__ __forceinline__ SheetRow sheet_row(const LineP &L, int i, int other_s
     return s;
 }
 
-// Block prologue: image sheet X (transaxial interpolation of the transposed
-// image) and / or zeroed gradient sheet Z.  Z accumulates in FP64: LDS FP64
-// atomic adds run at full rate on gfx950, FP32 ones do not.
+// Image sheet X of a line (transaxial interpolation of the transposed image),
+// xs floats between its rows, by the whole workgroup (thread tid).
 // The loads of SHEET_UNROLL rows per thread are issued before any of them is
 // used, so that a workgroup waits for memory a few times per line rather than
 // once per element it builds.
 constexpr int SHEET_UNROLL = 8;
 
-template <bool NEED_X, bool NEED_Z>
-__device__ __forceinline__ void build_sheets(const ProjArgs &a, const LineP &L, int nrow, float *X, double *Z) {
+__device__ __forceinline__ void build_sheet(const ProjArgs &a, const LineP &L, int nrow, float *X, int xs, int tid) {
     const int rz = a.rz;
-    const int n = nrow * rz;
-    if (NEED_X) {
-        const float *T = L.axis ? a.T1 : a.T0;
-        const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
-        if (rz <= (int)blockDim.x) {
-            const SheetWalk w = sheet_walk(rz);
-            if (w.on) {
-                for (int rb = w.r0; rb < nrow; rb += SHEET_UNROLL * w.R) {
-                    float t0[SHEET_UNROLL], t1[SHEET_UNROLL], f[SHEET_UNROLL];
+    const float *T = L.axis ? a.T1 : a.T0;
+    const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
+    if (rz > (int)blockDim.x) {
+        for (int e = tid; e < nrow * rz; e += blockDim.x) {
+            const int r = e / rz;
+            const int zp = e - r * rz;
+            const SheetRow sr = sheet_row(L, L.i_lo + r, other_stride, rz);
+            const float *src = T + sr.base + zp;
+            X[r * xs + zp] = fmaf(sr.f, src[rz] - src[0], src[0]);
+        }
+        return;
+    }
+    const SheetWalk w = sheet_walk(rz, tid);
+    if (!w.on) return;
+    for (int rb = w.r0; rb < nrow; rb += SHEET_UNROLL * w.R) {
+        float t0[SHEET_UNROLL], t1[SHEET_UNROLL], f[SHEET_UNROLL];
 #pragma unroll
-                    for (int u = 0; u < SHEET_UNROLL; ++u) {
-                        const int r = rb + u * w.R;
-                        t0[u] = t1[u] = f[u] = 0.f;
-                        if (r < nrow) {
-                            const SheetRow sr = sheet_row(L, L.i_lo + r, other_stride, rz);
-                            f[u] = sr.f;
-                            const float *src = T + sr.base + w.zp;
-                            t0[u] = src[0];
-                            t1[u] = src[rz];
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < SHEET_UNROLL; ++u) {
-                        const int r = rb + u * w.R;
-                        if (r < nrow) X[r * rz + w.zp] = fmaf(f[u], t1[u] - t0[u], t0[u]);
-                    }
-                }
-            }
-        } else {
-            for (int e = threadIdx.x; e < n; e += blockDim.x) {
-                const int r = e / rz;
-                const int zp = e - r * rz;
+        for (int u = 0; u < SHEET_UNROLL; ++u) {
+            const int r = rb + u * w.R;
+            t0[u] = t1[u] = f[u] = 0.f;
+            if (r < nrow) {
                 const SheetRow sr = sheet_row(L, L.i_lo + r, other_stride, rz);
-                const float *src = T + sr.base + zp;
-                X[e] = fmaf(sr.f, src[rz] - src[0], src[0]);
+                f[u] = sr.f;
+                const float *src = T + sr.base + w.zp;
+                t0[u] = src[0];
+                t1[u] = src[rz];
             }
         }
+#pragma unroll
+        for (int u = 0; u < SHEET_UNROLL; ++u) {
+            const int r = rb + u * w.R;
+            if (r < nrow) X[r * xs + w.zp] = fmaf(f[u], t1[u] - t0[u], t0[u]);
+        }
     }
-    if (NEED_Z)
-        for (int e = threadIdx.x; e < n; e += blockDim.x) Z[e] = 0.0;
 }
 
 // One sheet cell's value spread over the two transaxial neighbours.
@@ -124,30 +123,6 @@ __device__ __forceinline__ void spread_cell(float *Gout, const SheetRow &sr, int
     const float a1 = val * sr.f;
     atomicAdd(&Gout[sr.base + zp], val - a1);
     atomicAdd(&Gout[sr.base + zp + rz], a1);
-}
-
-// Block epilogue: spread the gradient sheet over the two transaxial neighbours.
-__device__ __forceinline__ void scatter_sheet(const ProjArgs &a, const LineP &L, int nrow, const double *Z,
-                                              int64_t g_off = 0) {
-    const int rz = a.rz;
-    float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
-    const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
-    if (rz <= (int)blockDim.x) {
-        const SheetWalk w = sheet_walk(rz);
-        if (!w.on) return;
-        for (int r = w.r0; r < nrow; r += w.R) {
-            const float val = (float)Z[r * rz + w.zp];
-            if (val == 0.f) continue;
-            spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), w.zp, rz, val);
-        }
-    } else {
-        for (int e = threadIdx.x; e < nrow * rz; e += blockDim.x) {
-            const float val = (float)Z[e];
-            if (val == 0.f) continue;
-            const int r = e / rz;
-            spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), e - r * rz, rz, val);
-        }
-    }
 }
 
 // Uniform loads of the gather's segment list through the scalar cache (a
@@ -203,14 +178,14 @@ __device__ __forceinline__ float gather_many(const float *Qs, const GatherSeg &G
 // one constant; elsewhere it is evaluated per share.
 template <bool MANY, bool FOLD, typename Fold>
 __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, int nrow, const float *Qs,
-                                             const GatherChunk &ch, int64_t g_off, const Fold &fold) {
+                                             const GatherChunk &ch, int64_t g_off, const Fold &fold, int tid) {
     const int nz = a.nz, rz = a.rz;
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
     const GatherSegList segs = (GatherSegList)(uintptr_t)a.gather;
     const float kappa = a.kappa, omk = 1.f - a.kappa;
     const int dr = (int)blockDim.x / nz, dz = (int)blockDim.x - dr * nz;
-    int r = (int)threadIdx.x / nz, z = (int)threadIdx.x - r * nz;
+    int r = tid / nz, z = tid - r * nz;
     while (r < nrow) {
         const float lam = fmaf((float)(L.i_lo + r), L.dlam, L.lam0);
         const float rho = (float)fma((double)z, a.inv_kappa, a.rho0);
@@ -247,19 +222,20 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
 
 // Block sums of two doubles into partial[blockIdx.x] (and, for the work counts,
 // partial[gridDim.x + blockIdx.x]).
-__device__ __forceinline__ void block_sums(double v0, double v1, double *partial, bool two) {
-    __shared__ double red[2][TOF_MAX_WAVES];
+__device__ __forceinline__ void block_sums(double v0, double v1, double *partial, bool two,
+                                           int tid = threadIdx.x) {
+    __shared__ double red[2][MAX_WAVES];
     for (int off = 32; off > 0; off >>= 1) {
         v0 += __shfl_down(v0, off, 64);
         v1 += __shfl_down(v1, off, 64);
     }
     const int nw = blockDim.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = v0;
-        red[1][threadIdx.x >> 6] = v1;
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = v0;
+        red[1][tid >> 6] = v1;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double s0 = 0.0, s1 = 0.0;
         for (int w = 0; w < nw; ++w) {
             s0 += red[0][w];

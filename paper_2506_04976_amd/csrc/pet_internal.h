@@ -19,14 +19,11 @@ namespace pet {
 constexpr int PADA = 2;
 constexpr int PADZ = 2;
 constexpr int NT_MAX = 32;     // TOF bins supported
-constexpr int NT_BLK = 16;     // TOF bins a lane holds in registers at once
 constexpr int NINT_MAX = 2 * NT_MAX - 1;  // intervals between the 2 n_tof window edges
 constexpr int NT_BLOCK = 1024;  // non-TOF line kernel: most threads per workgroup (16 waves)
 constexpr int IMG_BLOCK = 256;  // image-space kernels: threads per workgroup
-constexpr int TOF_MAX_WAVES = 16;  // TOF line kernel: at most 16 segment waves
+constexpr int MAX_WAVES = 16;  // waves per workgroup of the line kernels, at most
 constexpr int WS_MAX = 8;       // TOF bins overlapping one point
-// per-wave TOF interval cut indices: n_int + 1 of them, padded to 4
-__host__ __device__ inline int tof_cuts_pad(int n_int) { return (n_int + 1 + 3) & ~3; }
 
 // One transaxial line (view, radial): sample i along the principal axis m sits
 // at lambda(i) = lam0 + i dlam on the LOR; its coordinate along the other
@@ -82,6 +79,30 @@ struct GatherChunk {
 };
 constexpr int GATHER_PLANES = 1024;
 
+// ---- TOF line kernels --------------------------------------------------------
+// One unit of a TOF line: a segment, or a pair -k, +k whose planes fit in 64
+// lanes (same |u|, so the same TOF weights).  Its first n1 planes are the first
+// segment (all of them if it has one); in a staged row of the adjoint they are
+// columns 1 .. n1, the second segment's n1 + 3 .., zeros between.
+struct TofUnit {
+    int32_t p0;
+    uint8_t np, n1, neg, pad;  // planes; of the first segment; its ring difference is negative
+    float dz2, k;              // squared axial extent; |ring difference|
+};
+static_assert(sizeof(TofUnit) == 16, "TofUnit layout");
+constexpr int TOF_BLOCK = 512;                // threads per workgroup
+constexpr int TOF_STAGE_FLOATS = 4 * 80;      // LDS floats of a wave's staged rows
+// Floats between the rows of the image sheet in LDS: 16 mod 32, so that the four
+// rows that a wave reads at once start 16 banks apart
+__host__ __device__ inline int tof_x_stride(int rz) { return (rz + 15) / 32 * 32 + 16; }
+// LDS floats of the image sheet (rows in fours)
+__host__ __device__ inline int tof_x_floats(int rows_max, int x_stride) { return ((rows_max + 3) & ~3) * x_stride; }
+
+// v with its last 12 bits off (products with integers below 4096 are exact).
+__host__ __device__ inline float high_part(float v) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) & 0xfffff000u);
+}
+
 // TOF interval table.  The t axis (signed distance from the LOR centre) is cut
 // at every support edge t_b -/+ (bin/2 + nsig sigma) of a bin's weight; inside
 // interval s the bins with nonzero weight are bf[s] .. bf[s] + na[s] - 1.
@@ -103,9 +124,8 @@ struct ProjArgs {
     const LineP *lines;
     const PlaneP *planes;
     const int *views;
-    const SegP *segs;
     int n_rad, n_planes, nx, ny, nz, rz;
-    int n_seg, rows_max, ws, tstride;  // TOF: segments, sheet rows (max), bins per point, table row stride
+    int rows_max;              // sheet rows (max)
     // transposed padded images: T[0] principal x: [nx][ny+4][nz+4]; T[1] principal y: [ny][nx+4][nz+4]
     const float *T0, *T1;
     float *G0, *G1;
@@ -130,6 +150,17 @@ struct ProjArgs {
     float kappa;                // ring pitch / vz
     double inv_kappa, rho0;     // shifted position of voxel z before the segment's part: z inv_kappa + rho0
     float pitch2, k_max;        // squared ring pitch, largest ring difference
+    // TOF line kernels: units; bins per block of 16 matrix rows; units whose
+    // factors are in LDS together and the floats of each; cubics of the halved
+    // clamped erf, [0, n_etab] (position = distance * e_scale + e_mid, one bin
+    // = dpos = dpos_hi + dpos_lo, dpos_hi with 12 bits)
+    const TofUnit *units;
+    int n_units, bins_blk, q_units, unit_floats, x_stride;
+    int inv_nt;  // ceil(2^16 / n_tof)
+    const float4 *etab;
+    int n_etab;
+    double e_scale;
+    float e_mid, dpos, dpos_hi, dpos_lo;
 };
 
 // ---- zero-count-aware data term (counts.hip) --------------------------------
@@ -199,7 +230,7 @@ struct BMember {
     ProjArgs pa;               // geometry tables, image sheets, data; G0/G1 = slot 0
     const int *views;          // [n_sub + 1][views_stride] view lists (last row: all views)
     const int *sub_nviews;     // views per subset
-    int views_stride, n_sub, n_views, is_tof, tof_waves, nx, ny, nz;
+    int views_stride, n_sub, n_views, is_tof, nx, ny, nz;
     int64_t n_vox, g_slot;     // voxels; floats per gradient-sheet slot (G1 = G0 + t0 within a slot)
     int64_t t0_elems;
     // SVRG state (Algorithm 1)
@@ -234,14 +265,17 @@ struct pet_geom_s {
     // device tables
     pet::LineP *lines = nullptr;
     pet::PlaneP *planes = nullptr;
-    pet::SegP *segs = nullptr;
     pet::SegP *gsegs = nullptr;         // plain segments in plane order (gather adjoint)
     int n_gseg = 0;
     pet::GatherSeg *gather = nullptr;   // axial gather of the adjoint: segments by chunk, and the chunks
     pet::GatherChunk *gchunk = nullptr;
     int n_gchunk = 0, gather_two = 0, q_floats = 0;     // chunks; LDS floats of the largest one's factors
     double kappa = 1.0, ring0 = 0.0;    // ring pitch / vz; position of voxel 0 in rings, negated
-    int n_seg = 0, rows_max = 0, tof_ws = 0, tof_tstride = 0, tof_waves = 0;
+    int rows_max = 0;
+    pet::TofUnit *units = nullptr;      // TOF line kernels
+    float4 *etab = nullptr;
+    int n_units = 0, bins_blk = 0, q_units = 0, unit_floats = 0, n_etab = 0, x_stride = 0;
+    double e_scale = 0.0;
     int nt_threads = pet::NT_BLOCK;     // non-TOF line kernel: threads per workgroup
     int *views_dev = nullptr;           // [n_subsets + 1][max(max_views, n_views)]; last row: all views
     int views_stride = 0;
@@ -256,7 +290,6 @@ struct pet_geom_s {
     float2 *wtab = nullptr;   // TOF weight table: (W_k, W_{k+1} - W_k) at NW_TAB nodes (gather adjoint)
     float *wtabf = nullptr;   // and W at the NW_TAB + 1 nodes (counts kernels)
     float wD = 0.f;
-    size_t lds_bytes = 0;               // LDS of the TOF line kernels (and the limit checked at creation)
     size_t max_lds = 0;                 // the device's LDS limit per workgroup
     // scratch arena
     float *T0 = nullptr, *T1 = nullptr, *G0 = nullptr, *G1 = nullptr;
@@ -307,11 +340,23 @@ pet_status hip_check(hipError_t e, const char *what);
 
 // projector launches (proj.hip)
 hipError_t launch_line_kernel(pet_geom_s *g, int mode, int subset, const ProjArgs &a, hipStream_t s);
+// LDS of the TOF line kernels: image sheet (x), factors of `slots` units, staged
+// rows of `waves` waves, tables
+inline size_t tof_lds_bytes(const pet_geom_s *g, bool x, int slots, int waves) {
+    return sizeof(float) * ((x ? (size_t)tof_x_floats(g->rows_max, g->x_stride) : 0) +
+                            (size_t)slots * g->unit_floats + (size_t)waves * TOF_STAGE_FLOATS) +
+           sizeof(float4) * ((size_t)g->n_etab + 1 + 2 * g->n_units);
+}
 // persistent batched subset-gradient line kernel over the work items of one step
-hipError_t launch_line_batched(const BMember *mem, const int *order, int n_mem, int step, int *counter, int blocks,
-                               int waves, size_t lds, hipStream_t s);
+// (f: what its TOF members need at most)
+struct BatchForm {
+    int n_tof = 1, nz = 1;
+    bool gather_two = true;
+};
+hipError_t launch_line_batched(const BatchForm &f, const BMember *mem, const int *order, int n_mem, int step,
+                               int *counter, int blocks, int waves, size_t lds, hipStream_t s);
 // raise the batched kernel's dynamic-LDS limit (outside any stream capture)
-hipError_t prime_line_batched(size_t lds);
+hipError_t prime_line_batched(const BatchForm &f, size_t lds);
 // line-kernel argument block of a geometry (all views), and of one subset (-1: all views)
 ProjArgs geom_proj_args(pet_geom_s *g);
 ProjArgs subset_proj_args(pet_geom_s *g, int subset);

@@ -10,14 +10,12 @@
 //      transposed copy of the image so the loads are coalesced;
 //   2. threads take the planes (ring pairs) of the line and walk the samples
 //      with one linear interpolation in z from LDS per sample;
-//   3. the adjoint forms the cells Z[i][z] of the sheet (non-TOF: gathered from
-//      the planes' factors; TOF: accumulated with LDS atomics) and spreads them
-//      over the two transaxial neighbours with global atomics into a
+//   3. the adjoint gathers the cells of the sheet from the planes and spreads
+//      them over the two transaxial neighbours with global atomics into a
 //      z-contiguous transposed gradient image.
 // TOF: all planes of one ring-difference segment share |u|, hence the signed
-// distance t(i) of every sample and its TOF weights.  One wave takes one
-// segment (one plane per lane), fills a table with the weights of the line's
-// samples (increasing-t order) once, and the lanes read it by broadcast.
+// distance t(i) of every sample and its TOF weights, so that the sums over rows
+// and over bins are small matrix products (see line_tof_body).
 // The arithmetic is Joseph's: sample value = bilinear interpolation of the
 // image in the two non-principal axes, line integral = step length * sum.
 #include "line_sheets.h"
@@ -34,20 +32,12 @@ __device__ __forceinline__ float load_y(const void *y, int dt, int64_t idx) {
     return ((const float *)y)[idx];
 }
 
-// The nt values src[base .. base + nt) of one LOR (one block of at most
-// NT_BLK TOF bins), all loads issued before the first use (zero above nt).
-template <typename T>
-__device__ __forceinline__ void load_row(const T *src, int64_t base, int nt, float (&v)[NT_BLK]) {
-#pragma unroll
-    for (int b = 0; b < NT_BLK; ++b) v[b] = b < nt ? (float)src[base + b] : 0.f;
-}
-__device__ __forceinline__ void load_y_row(const void *y, int dt, int64_t base, int nt, float (&v)[NT_BLK]) {
-    if (dt == PET_Y_U8)
-        load_row((const uint8_t *)y, base, nt, v);
-    else if (dt == PET_Y_U16)
-        load_row((const uint16_t *)y, base, nt, v);
-    else
-        load_row((const float *)y, base, nt, v);
+// The lane index, opaque: what follows from it is formed where it is used and not
+// kept in registers across the other phases (which need all 128 of them).
+__device__ __forceinline__ int lane_here() {
+    int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane));
+    return lane;
 }
 
 // Poisson deviance term d(ybar, y) of the KL data fidelity, FP64.
@@ -55,6 +45,35 @@ __device__ __forceinline__ double kl_term(float ybar, float yv) {
     double s = ybar, t = yv;
     if (t > 0.0) return s - t + t * log(t / s);
     return s;
+}
+
+// The same term where registers are short: the logarithm from
+// log(m 2^e) = e log 2 + 2 artanh((m - 1) / (m + 1)), m in [sqrt(1/2), sqrt 2], the
+// artanh series to s^21 (remainder below 1e-18), its coefficients read from
+// constant memory at each use (as literals they would be kept in registers for
+// the whole kernel).
+__constant__ double LOG_SERIES[11] = {2.0,        2.0 / 3.0,  2.0 / 5.0,  2.0 / 7.0,  2.0 / 9.0, 2.0 / 11.0,
+                                      2.0 / 13.0, 2.0 / 15.0, 2.0 / 17.0, 2.0 / 19.0, 2.0 / 21.0};
+
+__device__ __forceinline__ double kl_term_lean(float ybar, float yv) {
+    const double s = ybar, t = yv;
+    if (!(t > 0.0)) return s;
+    const double x = t / s;
+    if (!(x > 0.0 && x < (double)INFINITY)) return s - t + t * (x == (double)INFINITY ? x : (double)__builtin_nanf(""));
+    typedef const double __attribute__((address_space(4))) *Coefs;
+    Coefs c = (Coefs)(uintptr_t)LOG_SERIES;
+    asm volatile("" : "+s"(c));
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    if (m < 0.70710678118654752) {
+        m *= 2.0;
+        e -= 1;
+    }
+    const double r = (m - 1.0) / (m + 1.0), z = r * r;
+    double p = c[10];
+#pragma unroll
+    for (int k = 9; k >= 0; --k) p = fma(p, z, c[k]);
+    return s - t + t * fma((double)e, 0.69314718055994531, r * p);
 }
 
 // Number of samples of [is, ie] (in increasing-t order) with t < e.
@@ -75,10 +94,6 @@ __device__ __forceinline__ int cut_count(float e, float len, float lam0, float d
 
 // ---------------------------------------------------------------------------
 // Non-TOF: threads over planes (dense), one line per workgroup.
-__device__ __forceinline__ float clamped_erf(float u, float inv_s, float c) {
-    return erff(fminf(fmaxf(u * inv_s, -c), c));
-}
-
 // Sum over all TOF bins of the weights of a sample at signed distance t from
 // the LOR centre.  The bins [t_b - w/2, t_b + w/2] tile [lo, hi] = [t_first -
 // w/2, t_last + w/2] without gaps, so the sum of 1/2 [E(t_b + w/2 - t) -
@@ -120,19 +135,20 @@ struct LineFold {
 // sheet X.  Adjoint: the planes' factors go to LDS (9 KB for 2204 planes) and
 // the cells of the sheet gather them (gather_cells).
 template <int MODE>
-__device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, float *smem, int64_t g_off = 0) {
+__device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, float *smem, int tid, int64_t g_off = 0) {
     constexpr bool NEED_X = MODE != M_BACK && MODE != M_COUNT;
     constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
     __shared__ int s_special;  // some factor is not finite
-    const LineP L = a.lines[line];
+    const LineP L = scalar_ref(a.lines[line]);
     const int nrow = L.i_hi - L.i_lo + 1;
     const int rz = a.rz;
     const int sheet = (a.rows_max * rz + 3) & ~3;
     float *X = smem;
     float *Qs = smem + (NEED_X ? sheet : 0);
-    // (a line that misses the image: no adjoint; forward values and terms stay)
-    if (MODE == M_BACK && nrow <= 0) return 0.0;
-    if (nrow > 0 && MODE != M_COUNT) build_sheets<NEED_X, false>(a, L, nrow, X, nullptr);
+    // (a line that misses the image has no adjoint; its forward values and
+    // likelihood terms stay)
+    if (nrow <= 0 && (MODE == M_BACK || MODE == M_HVP || ((MODE == M_GRAD || MODE == M_EM) && !a.partial))) return 0.0;
+    if (NEED_X && nrow > 0) build_sheet(a, L, nrow, X, rz, tid);
 
     double kl = 0.0;
     const int nb = blockDim.x;
@@ -142,8 +158,8 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         if (NEED_Z) {
             // (the zeros around the segments; the previous chunk's cells are done)
             if (ic > 0) __syncthreads();
-            for (int k = threadIdx.x; k < ch.n_q; k += nb) Qs[k] = 0.f;
-            if (threadIdx.x == 0) s_special = 0;
+            for (int k = tid; k < ch.n_q; k += nb) Qs[k] = 0.f;
+            if (tid == 0) s_special = 0;
         }
         if (NEED_Z || (NEED_X && ic == 0)) __syncthreads();
 
@@ -159,8 +175,8 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         for (int base = 0; base < np; base += nb) {
             const bool tail = base >= full;
             const int cc = tail ? c : 1;
-            const int rank = base + (tail ? (int)threadIdx.x / c : (int)threadIdx.x);
-            const int cs = tail ? (int)threadIdx.x % c : 0;
+            const int rank = base + (tail ? tid / c : tid);
+            const int cs = tail ? tid % c : 0;
             const bool act = rank < np;
             const int p = ch.p0 + (act ? rank : 0);
             const PlaneP P = a.planes[p];
@@ -237,14 +253,14 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         const LineFold F(a, L);
         if (MODE == M_BACK && a.tof_fold) {
             if (many)
-                gather_cells<true, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F);
+                gather_cells<true, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F, tid);
             else
-                gather_cells<false, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F);
+                gather_cells<false, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F, tid);
         } else {
             if (many)
-                gather_cells<true, false>(a, L, nrow, Qs, ch, g_off, F);
+                gather_cells<true, false>(a, L, nrow, Qs, ch, g_off, F, tid);
             else
-                gather_cells<false, false>(a, L, nrow, Qs, ch, g_off, F);
+                gather_cells<false, false>(a, L, nrow, Qs, ch, g_off, F, tid);
         }
     }
     return kl;
@@ -259,501 +275,818 @@ template <int MODE>
 __global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
     extern __shared__ float4 smem4[];
     // one line per workgroup, the launch's lines longest first
-    const double kl = line_nt_body<MODE>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4));
+    const double kl = line_nt_body<MODE>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), threadIdx.x);
     if (MODE != M_FWD && MODE != M_BACK && a.partial) block_sums(kl, kl, a.partial, MODE == M_COUNT);
 }
 
 // ---------------------------------------------------------------------------
-// TOF: one wave per segment, one plane per lane, shared per-segment table.
+// TOF: matrix products over the TOF weights.
 //
-// Per wave the LDS holds, for the segment being processed:
-//   cuts[s]  (s = 0 .. n_int)   first sample (t order) at or beyond edge s;
-//   w4[q], w1[q]                the TOF weights of the bins active at sample q
-//                               (first four in a float4, the rest after).
-// Samples q are numbered in increasing t along the LOR; the sample index,
-// lambda and the sheet row follow from q and are the same for all lanes.
+// All planes of one ring difference share |u|, hence the signed distance t of
+// every row and its TOF weights W[row][bin].  So, per unit (a segment, or a pair
+// -k, +k of at most 64 planes together),
+//     forward   A[bin][plane] = sum_row W[bin][row] V[row][plane],
+//     adjoint   Q[row][plane] = sum_bin W[row][bin] F[bin][plane],
+// with V the axially interpolated samples and F the factors mult (1 - y / ybar)
+// ell (and the like): both run on the f32 matrix instruction 16x16x4.
+//
+//  * Forward: one wave takes a unit; a step covers 4 rows x 64 planes (four
+//    samples per lane) and multiplies them by the weights of the 4 rows x 16
+//    bins (one weight per lane) into one 16 x 16 tile per 16 planes.
+//  * The factors of q_units units go to LDS, [16-plane tile][bin][plane].
+//  * Adjoint: one wave takes 16 rows.  Per unit it forms the 16 rows x 64 planes
+//    of Q (only the groups of four bins that reach those rows), passes them
+//    through its own LDS rows, four at a time, and its lanes (4 rows x 16
+//    voxels) gather the axial shares of their cells (gather_two), in FP64
+//    registers over all units.  No LDS atomics, no sheet of doubles.
+//
+// The weight of bin b at t is 1/2 [E(hi_b - t) - E(lo_b - t)], E the clamped erf,
+// from a table of cubics in LDS (error below 1e-8, see pet_geom_create).
+//
+// What bounds it: vector instructions (57% of the cycles of a subset gradient of
+// 128 x 128 x 71 voxels, 2204 planes and 13 bins; 12 per gathered cell and unit,
+// 6 to 8 per sample), then the matrix cores (151 us of the 784) and the data's
+// loads.  A wave per segment with FP64 LDS adds per sample took 1026 us for it;
+// 945 -> 612 us with 161 x 161 x 33 voxels and 25 bins, and a forward projection
+// of 96 x 96 x 32 voxels 694 -> 255 us.
+//
+// Lane layouts of the 16x16x4 instruction: A[m][k] in lane 16 k + m, B[k][n] in
+// lane 16 k + n, D[m][n] in register m mod 4 of lane 16 (m / 4) + n.
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef const TofUnit __attribute__((address_space(4))) *TofUnitList;
 
-// erf of u / (sqrt2 sigma) with the argument clamped to the truncation window.
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
-// Per-wave TOF weight table of one LOR (one segment of the line): lane s
-// computes the cut cuts[s] (rows before interval s in t order) and returns it;
-// each row q of a non-empty interval gets the weights of its na bins.
-__device__ __forceinline__ int fill_table(const ProjArgs &a, const LineP &L, float len, int *cuts, float *w4,
-                                          float *w1) {
-    const int lane = threadIdx.x & 63;
-    const int nq = L.i_hi - L.i_lo + 1;
-    const int e1 = a.ws > 4 ? a.ws - 4 : 0;
-    int *sid = reinterpret_cast<int *>(w4);  // interval of row q, parked in w4[q].x
-    int cut = 0;
-    if (lane <= a.tof.n_int) {
-        cut = cut_count(a.tof.edge[lane], len, L.lam0, L.dlam, L.i_lo, L.i_hi);
-        cuts[lane] = cut;
+__device__ __forceinline__ float cubic_at(const float4 &c, float f) {
+    return fmaf(fmaf(fmaf(c.w, f, c.z), f, c.y), f, c.x);
+}
+
+// 1/2 E at table position pos (clamped to the table: E is constant outside).
+__device__ __forceinline__ float half_erf_at(const float4 *tab, float pos, float last) {
+    const float p = __builtin_amdgcn_fmed3f(pos, 0.f, last);
+    const float f = __builtin_amdgcn_fractf(p);
+    return cubic_at(tab[(int)p], f);
+}
+
+// Table position of the lower edge of bin b at row j of a line (rows counted
+// from i_lo) in a unit: pA j + pB + b dpos; the step length of its samples.
+struct TofPos {
+    float pA, pB, ell;
+    // the same in parts that the forward adds up without loss: pA = a_hi + a_lo,
+    // and the table's middle (lower edge of bin 0) lies at row j0 - b0 / pA
+    float a_hi, a_lo, b0, j0, pad;
+};
+static_assert(sizeof(TofPos) == 32, "two 16-byte LDS reads");
+
+// Forward tiles of one unit: NPB tiles of 16 planes, MB blocks of bins.  Lanes
+// past the unit's planes have zA = zB = 0 (they read the zero padding); rows
+// past the line's are zeros in X.  The next step's weights are looked up while
+// this step's samples are under way.
+template <int MB, int NPB, int TILES>
+__device__ __forceinline__ void tof_fwd_rows(const ProjArgs &a, const float4 *tab, const float *X, int j_lo, int j_hi,
+                                             int i_lo, int lane, const TofPos &tp, const float (&zA)[TILES],
+                                             const float (&zB)[TILES], f32x4 (&D)[MB][TILES]) {
+    const int xs = a.x_stride;
+    const float umax = (float)(a.nz + PADZ), last = (float)a.n_etab;
+    const int jr = lane >> 4;
+    const bool full = a.bins_blk == 16;
+    float pos[MB], w[MB];
+    // p = pA rel + pos, rel the row counted from one near the bin's lower edge: p is
+    // rounded on the scale of the table, not on that of the line
+    float rel[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const float b = (float)(mb * a.bins_blk + (lane & 15));
+        const float jb = rintf(__builtin_amdgcn_fmed3f(-b * a.dpos * __builtin_amdgcn_rcpf(tp.pA), -4095.f, 4095.f));
+        pos[mb] = fmaf(jb, tp.a_hi, b * a.dpos_hi) + fmaf(jb, tp.a_lo, fmaf(b, a.dpos_lo, tp.b0)) + a.e_mid;
+        rel[mb] = (float)(j_lo + jr) - tp.j0 - jb;
     }
-    for (int q = lane; q < nq; q += 64) sid[4 * q] = -1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // lane s marks the rows of interval s
-    if (lane < a.tof.n_int && a.tof.na[lane] > 0) {
-        const int hi = cuts[lane + 1];
-        for (int q = cut; q < hi; ++q) sid[4 * q] = lane;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const float inv_s = a.tof.inv_sqrt2_sigma, c = a.tof.erf_clamp, h = a.tof.half_bin;
-    for (int q = lane; q < nq; q += 64) {
-        const int s = sid[4 * q];
-        if (s < 0) continue;
-        const int na = a.tof.na[s];
-        const int i = L.dlam > 0.f ? L.i_lo + q : L.i_hi - q;
-        const float lam = fmaf((float)i, L.dlam, L.lam0);
-        const float t = (lam - 0.5f) * len;
-        // weights of bins bf .. bf + na - 1 from shared bin edges
-        const float t0 = a.tof.tb[a.tof.bf[s]] - h - t;
-        float e_prev = clamped_erf(t0, inv_s, c);
-        float w[WS_MAX];
-        for (int j = 0; j < WS_MAX; ++j) w[j] = 0.f;
-        for (int j = 0; j < na; ++j) {
-            const float e_next = clamped_erf(t0 + (float)(j + 1) * (2.f * h), inv_s, c);
-            w[j] = 0.5f * (e_next - e_prev);
-            e_prev = e_next;
+    auto weights = [&]() {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const float p = fmaf(rel[mb], tp.pA, pos[mb]);
+            rel[mb] += 4.f;
+            const float lo = half_erf_at(tab, p, last);
+            // the upper edge is the next lane's lower one (16 bins: the last
+            // lane has no next one)
+            float hi = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, lo),
+                                                                              0x101 /* row_shl:1 */, 0xf, 0xf, true));
+            if (full) hi = half_erf_at(tab, p + a.dpos, last);
+            w[mb] = hi - lo;
         }
-        reinterpret_cast<float4 *>(w4)[q] = make_float4(w[0], w[1], w[2], w[3]);
-        for (int j = 0; j < e1; ++j) w1[q * e1 + j] = w[4 + j];
+    };
+    const float *xr = X + (j_lo + jr) * xs;
+    float fi = (float)(i_lo + j_lo + jr);
+    weights();
+    for (int j = j_lo; j <= j_hi; j += 4) {
+        float x0[NPB], x1[NPB], f[NPB], wj[MB];
+#pragma unroll
+        for (int pb = 0; pb < NPB; ++pb) {
+            const float u = __builtin_amdgcn_fmed3f(fmaf(fi, zA[pb], zB[pb]), 0.f, umax);
+            const int c = (int)u;
+            f[pb] = __builtin_amdgcn_fractf(u);
+            x0[pb] = xr[c];
+            x1[pb] = xr[c + 1];
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) wj[mb] = w[mb];
+        weights();
+#pragma unroll
+        for (int pb = 0; pb < NPB; ++pb) {
+            const float v = fmaf(f[pb], x1[pb] - x0[pb], x0[pb]);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) D[mb][pb] = mfma16(wj[mb], v, D[mb][pb]);
+        }
+        xr += 4 * xs;
+        fi += 4.f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    return cut;
 }
 
-// Weights of sample q (all lanes read the same row: broadcast reads).
-template <int NA>
-__device__ __forceinline__ void read_w(const float *w4, const float *w1, int e1, int q, float (&w)[NA]) {
-    const float4 v = reinterpret_cast<const float4 *>(w4)[q];
-    if (NA > 0) w[0] = v.x;
-    if (NA > 1) w[1] = v.y;
-    if (NA > 2) w[2] = v.z;
-    if (NA > 3) w[3] = v.w;
-#pragma unroll
-    for (int j = 4; j < NA; ++j) w[j] = w1[q * e1 + (j - 4)];
+// Weight of bin b at row j.
+__device__ __forceinline__ float tof_weight(const ProjArgs &a, const float4 *tab, const TofPos &tp, float fj, int b) {
+    const float p = fmaf((float)b, a.dpos, fmaf(fj, tp.pA, tp.pB)), last = (float)a.n_etab;
+    return half_erf_at(tab, p + a.dpos, last) - half_erf_at(tab, p, last);
 }
 
-// Sample loops of one TOF interval: n rows walked in t order from row pointer
-// xr / zr (row of the first sample, z padding skipped), principal-plane index
-// fi stepping by dfi and row stride drz, taking every wstep-th row (the line
-// kernels walk every row: wstep = 1).  The weights of a row are the same for
-// every lane that walks it (broadcast LDS reads when the whole wave does); the
-// axial position of a sample in plane i is zA * i + zB (voxel units).
-template <int NA>
-__device__ __forceinline__ void read_wq(const float *wq, const float *w1q, float (&w)[NA]) {
-    const float4 v = *reinterpret_cast<const float4 *>(wq);
-    if (NA > 0) w[0] = v.x;
-    if (NA > 1) w[1] = v.y;
-    if (NA > 2) w[2] = v.z;
-    if (NA > 3) w[3] = v.w;
-#pragma unroll
-    for (int j = 4; j < NA; ++j) w[j] = w1q[j - 4];
-}
-
-// Axial positions are taken in padded-row cells, u = z + PADZ: a sample at
-// axial position z interpolates cells floor(u) and floor(u) + 1 of its sheet
-// row (the row pointer is the row start).  u is clamped to [0, nz + 2], where
-// the truncating conversion is the floor and v_fract the fraction.
-
-// Forward: no lane predicate.  A sample outside the z-valid range
-// [-1.5, nz + 0.5] (u outside [0.5, nz + 2.5]) interpolates between two cells
-// of the zero padding and adds exactly zero, as does a lane without a plane
-// (zA = 0, zB = 0).
-template <int NA>
-__device__ __forceinline__ void tof_fwd_run(float zA, float zB, float umax, const float *xr, int drz, float fi,
-                                            float dfi, const float *wq, const float *w1q, int e1, int wstep, int n,
-                                            float *win) {
-#pragma unroll 2
-    for (; n > 0; --n) {
-        float w[NA];
-        read_wq<NA>(wq, w1q, w);
-        const float u = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
-        const int j = (int)u;
+// The forward sum of one bin of one LOR without the products of zero weights
+// (an image that is not finite must not reach the bins beyond it).
+__device__ __forceinline__ float tof_fwd_guarded(const ProjArgs &a, const float4 *tab, const float *X, const LineP &L,
+                                                 int nrow, const TofPos &tp, const PlaneP &P, int b) {
+    const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
+    const float umax = (float)(a.nz + PADZ);
+    float s = 0.f;
+#pragma unroll 1
+    for (int j = 0; j < nrow; ++j) {
+        const float w = tof_weight(a, tab, tp, (float)j, b);
+        if (!(w > 0.f)) continue;
+        const float u = __builtin_amdgcn_fmed3f(fmaf((float)(L.i_lo + j), zA, zB), 0.f, umax);
+        const int c = (int)u;
         const float f = __builtin_amdgcn_fractf(u);
-        const float x0 = xr[j], x1 = xr[j + 1];
-        const float v = fmaf(f, x1 - x0, x0);
-#pragma unroll
-        for (int b = 0; b < NA; ++b) win[b] = fmaf(v, w[b], win[b]);
-        xr += drz;
-        fi += dfi;
-        wq += 4 * wstep;
-        w1q += e1 * wstep;
+        const float x0 = X[j * a.x_stride + c], x1 = X[j * a.x_stride + c + 1];
+        s = fmaf(w, f > 0.f ? fmaf(f, x1 - x0, x0) : x0, s);
+    }
+    return s;
+}
+
+// A factor that is not finite, spread by itself: the matrix products would take
+// it to the rows and planes where its weight is 0.
+__device__ __forceinline__ void tof_back_special(const ProjArgs &a, const LineP &L, const float4 *tab, int nrow,
+                                                 const TofPos &tp, const PlaneP &P, int b, float Q, int64_t g_off) {
+    const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
+    float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
+    const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * a.rz;
+#pragma unroll 1
+    for (int j = 0; j < nrow; ++j) {
+        const float w = tof_weight(a, tab, tp, (float)j, b);
+        const float u = fmaf((float)(L.i_lo + j), zA, zB);
+        if (!(w > 0.f) || !(u > (float)PADZ - 1.f && u < (float)(a.nz + PADZ))) continue;
+        const int c = (int)u;
+        const float f = __builtin_amdgcn_fractf(u);
+        const SheetRow sr = sheet_row(L, L.i_lo + j, other_stride, a.rz);
+        if (f < 1.f && c >= PADZ) spread_cell(Gout, sr, c, a.rz, Q * (w * (1.f - f)));
+        if (f > 0.f && c + 1 < a.nz + PADZ) spread_cell(Gout, sr, c + 1, a.rz, Q * (w * f));
     }
 }
 
-// Adjoint: a lane adds its samples k = q - qlo in [0, span] only.
-template <int NA>
-__device__ __forceinline__ void tof_back_run(float zA, float zB, float umax, double *zr, int drz, float fi, float dfi,
-                                             const float *wq, const float *w1q, int e1, int wstep, int n, int k,
-                                             unsigned span, const float *win) {
-#pragma unroll 2
-    for (; n > 0; --n) {
-        float w[NA];
-        read_wq<NA>(wq, w1q, w);
-        float Q = 0.f;
+// Four consecutive bins of which the first n exist, in one load where all do
+// (the arrays need no more than their elements' alignment).
+__device__ __forceinline__ void load_bins(const float *p, int n, float (&v)[4]) {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (n >= 4) {
+        const f4 q = *reinterpret_cast<const f4 *>(p);
 #pragma unroll
-        for (int b = 0; b < NA; ++b) Q = fmaf(win[b], w[b], Q);
-        if ((unsigned)k <= span) {
-            // (the clamp only guards the LDS bounds; valid samples lie inside)
-            const float u = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
-            const int j = (int)u;
-            const float a1 = Q * __builtin_amdgcn_fractf(u);
-            atomicAdd(&zr[j], (double)(Q - a1));
-            atomicAdd(&zr[j + 1], (double)a1);
+        for (int r = 0; r < 4; ++r) v[r] = q[r];
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) v[r] = r < n ? p[r] : 0.f;
+        v[3] = 0.f;
+    }
+}
+
+__device__ __forceinline__ void store_bins(float *p, int n, const float (&v)[4]) {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (n >= 4) {
+        *reinterpret_cast<f4 *>(p) = f4{v[0], v[1], v[2], v[3]};
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (r < n) p[r] = v[r];
+    }
+}
+
+__device__ __forceinline__ void load_counts(const void *y, int dt, int64_t base, int n, float (&v)[4]) {
+    if (dt == PET_Y_U8) {
+        typedef uint32_t u4 __attribute__((aligned(1)));
+        const uint8_t *p = (const uint8_t *)y + base;
+        uint32_t q = 0;
+        if (n >= 4) {
+            q = *reinterpret_cast<const u4 *>(p);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) q |= r < n ? (uint32_t)p[r] << (8 * r) : 0u;
         }
-        zr += drz;
-        fi += dfi;
-        wq += 4 * wstep;
-        w1q += e1 * wstep;
-        k += wstep;
-    }
-}
-
-// Bin window <-> the per-bin accumulators of one block of NT_BLK bins.  The
-// window's first bin relative to the block, REL (from -(WS_MAX - 1) to
-// NT_BLK - 1), is a template argument so that every register index is static:
-// indexing a register array by a run-time value compiles to indexed register
-// moves, which the compiler may execute speculatively for indices the source
-// guards out and which then write registers past the array.
-template <int REL>
-__device__ __forceinline__ void add_window(float (&acc)[NT_BLK], const float (&win)[WS_MAX], int na) {
 #pragma unroll
-    for (int j = 0; j < WS_MAX; ++j)
-        if (REL + j >= 0 && REL + j < NT_BLK && j < na) acc[REL + j] += win[j];
-}
-
-template <int REL>
-__device__ __forceinline__ void get_window(const float (&acc)[NT_BLK], float (&win)[WS_MAX], int na) {
+        for (int r = 0; r < 4; ++r) v[r] = (float)((q >> (8 * r)) & 0xffu);
+    } else if (dt == PET_Y_U16) {
+        const uint16_t *p = (const uint16_t *)y + base;
 #pragma unroll
-    for (int j = 0; j < WS_MAX; ++j) win[j] = (REL + j >= 0 && REL + j < NT_BLK && j < na) ? acc[REL + j] : 0.f;
-}
-
-static_assert(NT_BLK == 16 && WS_MAX == 8, "the window switch below covers first bins -7 .. 15 of a block");
-#define PET_REL_SWITCH(FN, ...)                \
-    switch (rel) {                             \
-        case -7: FN<-7>(__VA_ARGS__); break;   \
-        case -6: FN<-6>(__VA_ARGS__); break;   \
-        case -5: FN<-5>(__VA_ARGS__); break;   \
-        case -4: FN<-4>(__VA_ARGS__); break;   \
-        case -3: FN<-3>(__VA_ARGS__); break;   \
-        case -2: FN<-2>(__VA_ARGS__); break;   \
-        case -1: FN<-1>(__VA_ARGS__); break;   \
-        case 0: FN<0>(__VA_ARGS__); break;     \
-        case 1: FN<1>(__VA_ARGS__); break;     \
-        case 2: FN<2>(__VA_ARGS__); break;     \
-        case 3: FN<3>(__VA_ARGS__); break;     \
-        case 4: FN<4>(__VA_ARGS__); break;     \
-        case 5: FN<5>(__VA_ARGS__); break;     \
-        case 6: FN<6>(__VA_ARGS__); break;     \
-        case 7: FN<7>(__VA_ARGS__); break;     \
-        case 8: FN<8>(__VA_ARGS__); break;     \
-        case 9: FN<9>(__VA_ARGS__); break;     \
-        case 10: FN<10>(__VA_ARGS__); break;   \
-        case 11: FN<11>(__VA_ARGS__); break;   \
-        case 12: FN<12>(__VA_ARGS__); break;   \
-        case 13: FN<13>(__VA_ARGS__); break;   \
-        case 14: FN<14>(__VA_ARGS__); break;   \
-        default: FN<15>(__VA_ARGS__); break;   \
+        for (int r = 0; r < 4; ++r) v[r] = r < n ? (float)p[r] : 0.f;
+    } else {
+        load_bins((const float *)y + base, n, v);
     }
-
-#define PET_NA_SWITCH(FN, ...)              \
-    switch (na) {                           \
-        case 1: FN<1>(__VA_ARGS__); break;  \
-        case 2: FN<2>(__VA_ARGS__); break;  \
-        case 3: FN<3>(__VA_ARGS__); break;  \
-        case 4: FN<4>(__VA_ARGS__); break;  \
-        case 5: FN<5>(__VA_ARGS__); break;  \
-        case 6: FN<6>(__VA_ARGS__); break;  \
-        case 7: FN<7>(__VA_ARGS__); break;  \
-        default: FN<8>(__VA_ARGS__); break; \
-    }
-
-// Live intervals of a segment wave as a bit mask (bit s: interval s).  With the
-// rows split over C chunks, chunk k takes the k-th set bit (-1 if there are
-// fewer), and the wave then drops the lowest C.
-__device__ __forceinline__ int kth_interval(uint64_t mk, int k) {
-    for (int i = 0; i < k && mk; ++i) mk &= mk - 1;
-    return mk ? (int)__builtin_ctzll(mk) : -1;
-}
-__device__ __forceinline__ uint64_t drop_intervals(uint64_t mk, int c) {
-    for (int i = 0; i < c && mk; ++i) mk &= mk - 1;
-    return mk;
 }
 
-// One transaxial line of a TOF geometry by the whole workgroup, segments
-// spread over the first nwaves waves (the others only help with the sheets);
-// adds this thread's FP64 partials (KL or samples, and sample-bin pairs) to
-// kl and pairs.
-template <int MODE>
-__device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float *smem, int nwaves, double &kl,
-                                              double &pairs, int64_t g_off = 0) {
-    constexpr bool NEED_X = MODE != M_BACK && MODE != M_COUNT;
-    constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
-    const int lane = threadIdx.x & 63;
-    // wave index and wave count are wave-uniform: the segment loop below runs
-    // under scalar control flow
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    nwaves = __builtin_amdgcn_readfirstlane(nwaves);
-    const LineP L = a.lines[line];
-    const int nrow = L.i_hi - L.i_lo + 1;
-    const int rz = a.rz;
+// LDS of a wave of the adjoint: 4 rows of a unit's planes (at most 64, with the
+// zeros around its two segments), 16 banks apart.
+constexpr int STAGE_COLS = 80, STAGE_ROWS = 4;
+static_assert(TOF_STAGE_FLOATS == STAGE_COLS * STAGE_ROWS, "LDS layout of the TOF line kernels");
+// Voxels along z of one pass of the adjoint: STAGE_ZB groups of 16.
+constexpr int STAGE_ZB = 5;
+static_assert(16 * STAGE_ZB <= STAGE_COLS, "the finished cells leave through the staged rows");
+// Groups of four bins whose weights a wave of the adjoint keeps for a pair of
+// segments of the same length.
+constexpr int KEEP_KK = 3;
+
+// Order of LDS accesses within a wave: its LDS instructions are carried out in
+// order, so only the compiler has to keep them so.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// What the adjoint of one block of 16 rows works on: the units [u0, u1) whose
+// factors are in LDS, the wave's staged rows, the tables, the block and the groups
+// of four bins [kk0, kk0 + nkk) that reach its rows.
+struct TofBack {
+    const float *Fs;
+    float *stage;
+    const TofPos *utab;
+    const float4 *tab;
+    int u0, u1, rb, kk0, nkk;
+};
+
+// Adjoint of one block of 16 rows over units [u0, u1): adds to the lane's cells
+// acc[h][zb] (row 4 (lane / 16) + h, voxel z0 + 16 zb + lane mod 16).  Per unit
+// the 16 rows x 64 planes of Q (one matrix product per 16 planes and group of
+// bins), which pass through the wave's four LDS rows; the products of the next
+// unit are under way while the last rows of this one are gathered.
+template <int NZB, bool MANY>
+__device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L, const TofBack &k, int z0,
+                                              double (&acc)[4][NZB]) {
+    const TofUnitList units = (TofUnitList)(uintptr_t)a.units;
     const int nt = a.tof.n_tof;
-    // LDS: X sheet (float) | Z sheet (double) | per wave: w4 [rows][4], w1 [rows][e1], cuts
-    const int sheet = (a.rows_max * rz + 3) & ~3;
-    const int ws = a.ws;  // widest bin window of any interval
-    const int e1 = ws > 4 ? ws - 4 : 0;
-    const int per_wave = a.rows_max * (4 + e1) + tof_cuts_pad(a.tof.n_int);
+    float rho[NZB];
+#pragma unroll
+    for (int zb = 0; zb < NZB; ++zb) {
+        rho[zb] = (float)fma((double)(z0 + 16 * zb + (lane_here() & 15)), a.inv_kappa, a.rho0);
+        __builtin_amdgcn_sched_barrier(0);  // (one by one: registers)
+    }
+    const float last = (float)a.n_etab, kappa = a.kappa, omk = 1.f - a.kappa;
+    float w[KEEP_KK], w_dz2 = -1.f;
+#pragma unroll
+    for (int q = 0; q < KEEP_KK; ++q) w[q] = 0.f;
+
+    // Tiles of unit u: 16 T planes, K groups of bins from the kc-th on.  Bins past
+    // the last one and planes past the unit's last tile read other factors (the
+    // LDS past the units holds finite numbers too): weight 0, or columns that
+    // nothing uses.
+    f32x4 D[4];
+    auto groups = [&](auto tiles, auto count, auto first, int u, int kc, bool fresh) {
+        constexpr int T = tiles.value, K = count.value;
+        const int lane = lane_here();
+        const float *F = k.Fs + (u - k.u0) * a.unit_floats + 64 * (k.kk0 + kc) + lane;
+        float fv[T][K];
+#pragma unroll
+        for (int pb = 0; pb < T; ++pb) {
+            const float *Fb = F + pb * nt * 16;
+#pragma unroll
+            for (int q = 0; q < K; ++q) fv[pb][q] = Fb[64 * q];
+        }
+        if (fresh) {
+            const TofPos tp = k.utab[u];
+            const int b = 4 * (k.kk0 + kc) + (lane >> 4);  // this lane's bin of the first group
+            const float p = fmaf((float)b, a.dpos, fmaf((float)(16 * k.rb + (lane & 15)), tp.pA, tp.pB));
+            float f[2 * K];
+            float4 c[2 * K];
+            // (the table reads together)
+#pragma unroll
+            for (int q = 0; q < 2 * K; ++q) {
+                const float pq = __builtin_amdgcn_fmed3f(fmaf((float)(4 * (q / 2) + q % 2), a.dpos, p), 0.f, last);
+                f[q] = __builtin_amdgcn_fractf(pq);
+                c[q] = k.tab[(int)pq];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                const float lo = cubic_at(c[2 * q], f[2 * q]), hi = cubic_at(c[2 * q + 1], f[2 * q + 1]);
+                w[q] = b + 4 * q < nt ? hi - lo : 0.f;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+#pragma unroll
+            for (int pb = 0; pb < T; ++pb)
+                D[pb] = mfma16(w[q], fv[pb][q], first.value && q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : D[pb]);
+    };
+    auto products = [&](int u) {
+        const float dz2 = units[u].dz2;
+        const bool two = units[u].np <= 32;
+        // (segments -k and +k are neighbours: the same length, the same weights)
+        const bool fresh = dz2 != w_dz2;
+        w_dz2 = dz2;
+        if (k.nkk == 2 && !two) {
+            groups(Int<4>(), Int<2>(), Int<1>(), u, 0, fresh);
+        } else if (k.nkk == 3 && !two) {
+            groups(Int<4>(), Int<3>(), Int<1>(), u, 0, fresh);
+        } else if (two) {
+            groups(Int<2>(), Int<2>(), Int<1>(), u, 0, true);
+            for (int kc = 2; kc < k.nkk; kc += 2) groups(Int<2>(), Int<2>(), Int<0>(), u, kc, true);
+            w_dz2 = -1.f;
+        } else {
+            groups(Int<4>(), Int<2>(), Int<1>(), u, 0, true);
+            for (int kc = 2; kc < k.nkk; kc += 2) groups(Int<4>(), Int<2>(), Int<0>(), u, kc, true);
+            w_dz2 = -1.f;
+        }
+    };
+
+    if ((lane_here() & 15) == 0) k.stage[(lane_here() >> 4) * STAGE_COLS] = 0.f;
+    products(k.u0);
+    for (int u = k.u0; u < k.u1; ++u) {
+        const int np = units[u].np, n1 = units[u].n1, neg = units[u].neg;
+        const float rd = units[u].k;
+        const int npb = (np + 15) >> 4;
+        const int lane = lane_here(), pl = lane & 15, g = lane >> 4;
+        float *srow = k.stage + g * STAGE_COLS;
+        // in the gather, this lane's rows are 4 g + h of the block
+        const float lam_g = fmaf((float)(L.i_lo + 16 * k.rb + 4 * g), L.dlam, L.lam0);
+        // the columns of this lane's planes (opaque: formed once per unit)
+        float *col[4];
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
+            int c = g * STAGE_COLS + 16 * pb + pl + (n1 == np || 16 * pb + pl < n1 ? 1 : 3);
+            asm volatile("" : "+v"(c));
+            col[pb] = k.stage + c;
+        }
+        wave_lds_order();
+        // The zeros between and after the segments (column 0 keeps its zero; the
+        // planes that fill up the last tile are zeros too, two of them are enough
+        // after a single segment).
+        if ((n1 < np || 16 * npb < np + 2) && pl < 4) srow[pl < 2 ? n1 + 1 + pl : np + 1 + pl] = 0.f;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            wave_lds_order();
+#pragma unroll
+            for (int pb = 0; pb < 4; ++pb)
+                if (pb < npb) *col[pb] = D[pb][h];
+            wave_lds_order();
+            __builtin_amdgcn_sched_barrier(0);
+            if (h == 3 && u + 1 < k.u1) products(u + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const float lam = fmaf((float)h, L.dlam, lam_g);
+            auto segment = [&](const GatherSeg &G, float slope) {
+                float v[NZB];
+#pragma unroll
+                for (int zb = 0; zb < NZB; ++zb) {
+                    const float t = fmaf(-slope, G.k, rho[zb]);
+                    v[zb] = MANY ? gather_many(srow, G, t, kappa) : gather_two(srow, G, t, kappa, omk);
+                }
+#pragma unroll
+                for (int zb = 0; zb < NZB; ++zb) acc[h][zb] += (double)v[zb];
+            };
+            segment({rd, 0.f, (float)(n1 + 1), 0}, neg ? 1.f - lam : lam);
+            if (n1 < np) segment({rd, 0.f, (float)(np - n1 + 1), n1 + 2}, lam);
+        }
+    }
+}
+
+// A line that misses the image: forward values and likelihood terms from the
+// additive terms alone, in memory order; it has no adjoint.
+template <int MODE>
+__device__ __forceinline__ void tof_line_outside(const ProjArgs &a, int line, int tid, double &kl) {
+    const int nt = a.tof.n_tof, n = a.n_planes * nt, nb = blockDim.x;
+    const int64_t lor0 = (int64_t)line * a.n_planes, base = lor0 * nt;
+    for (int e0 = tid; e0 < n; e0 += 4 * nb) {
+        float m[4], v[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = e0 + q * nb;
+            m[q] = v[q] = y[q] = 0.f;
+            if (e >= n) continue;
+            m[q] = a.mult ? a.mult[lor0 + e / nt] : 1.f;
+            if (a.add) v[q] = a.add[base + e];
+            if (MODE != M_FWD) y[q] = load_y(a.y, a.y_dtype, base + e);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = e0 + q * nb;
+            if (e >= n) continue;
+            const float ybar = fmaf(m[q], 0.f, v[q]);
+            if (MODE == M_FWD)
+                a.out[base + e] = ybar;
+            else
+                kl += kl_term_lean(ybar, y[q]);
+        }
+    }
+}
+
+// What the adjoint spreads of a bin: m its factor, s its projection, v the
+// additive term (M_HVP: the mean data, M_BACK: the data), y its counts.
+template <int MODE>
+__device__ __forceinline__ float tof_factor(float m, float s, float v, float y, float ell) {
+    if constexpr (MODE == M_BACK) return v * m * ell;
+    // data-term Hessian: mult^2 y / ybar^2 (P v), then back
+    if constexpr (MODE == M_HVP) return y != 0.f ? m * m * y / (v * v) * s * ell : 0.f;
+    // a bin without counts: derivative 1, EM ratio 0
+    const float ri = __builtin_amdgcn_rcpf(fmaf(m, s, v));
+    if constexpr (MODE == M_EM) return y != 0.f ? m * (y * ri) * ell : 0.f;
+    return m * (y != 0.f ? fmaf(-y, ri, 1.f) : 1.f) * ell;
+}
+
+// A value that is the same in all lanes, in a scalar register.
+__device__ __forceinline__ float uniform(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+
+// One transaxial line of a TOF geometry by the whole workgroup; adds this
+// thread's FP64 partial (KL) to kl.  The adjoint takes 16 NZB voxels along z at a
+// time; MANY: more than two planes of a segment may reach a voxel; KL: the Poisson
+// deviance is wanted as well (M_OBJ: alone); TILES: the forward takes that many tiles
+// of 16 planes at a time (16 registers of sums with four tiles or two blocks of bins).
+template <int MODE, int MB, int NZB, bool MANY, bool KL, int TILES>
+__device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float *smem, int wave, double &kl,
+                                              int64_t g_off = 0) {
+    constexpr bool NEED_X = MODE != M_BACK;
+    constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
+    const int nw = blockDim.x >> 6;
+    const LineP L = scalar_ref(a.lines[line]);
+    const int nrow = L.i_hi - L.i_lo + 1;
+    const int rz = a.rz, nt = a.tof.n_tof;
+    if (nrow <= 0) {  // (uniform)
+        if (MODE == M_FWD || KL) tof_line_outside<MODE>(a, line, 64 * wave + lane_here(), kl);
+        return;
+    }
+    const int tid = 64 * wave + lane_here();
+    // LDS: X | factors of q_units units (the objective: sums of one unit per wave)
+    // | per wave: rows of Q | units' table positions | table of E
     float *X = smem;
-    double *Z = reinterpret_cast<double *>(smem + (NEED_X ? sheet : 0));
-    float *wave_mem = smem + (NEED_X ? sheet : 0) + (NEED_Z ? 2 * sheet : 0) + wave * ((per_wave + 3) & ~3);
-    float *w4 = wave_mem;
-    float *w1 = wave_mem + 4 * a.rows_max;
-    int *cuts = (int *)(w1 + a.rows_max * e1);
-    if (nrow > 0 && MODE != M_COUNT) build_sheets<NEED_X, NEED_Z>(a, L, nrow, X, Z);
+    float *Fs = smem + (NEED_X ? tof_x_floats(a.rows_max, a.x_stride) : 0);
+    const int n_slots = NEED_Z ? a.q_units : MODE == M_OBJ ? nw : 0;
+    float *stage = Fs + n_slots * a.unit_floats + wave * TOF_STAGE_FLOATS;
+    TofPos *utab = reinterpret_cast<TofPos *>(Fs + n_slots * a.unit_floats + (NEED_Z ? nw * TOF_STAGE_FLOATS : 0));
+    float4 *tab = reinterpret_cast<float4 *>(utab + a.n_units);
+    const float lam_s = fmaf((float)L.i_lo, L.dlam, L.lam0) - 0.5f;
+    const TofUnitList units = (TofUnitList)(uintptr_t)a.units;
+    for (int k = tid; k <= a.n_etab; k += blockDim.x) tab[k] = a.etab[k];
+    for (int k = tid; k < a.n_units; k += blockDim.x) {
+        const float len = sqrtf(L.lt2 + a.units[k].dz2);
+        const double len_d = sqrt((double)L.lt2 + a.units[k].dz2), da = -L.dlam * len_d * a.e_scale;
+        const double db = ((double)a.tof.tb[0] - a.tof.half_bin - ((double)L.i_lo * L.dlam + L.lam0 - 0.5) * len_d) * a.e_scale;
+        const double j0 = rint(fmin(fmax(-db / da, -1e6), 1e6));
+        const float a_hi = high_part((float)da);
+        utab[k] = {(float)da, (float)(db + a.e_mid),
+                   L.vm_um * len, a_hi, (float)(da - a_hi), (float)fma(j0, da, db), (float)j0, 0.f};
+    }
+    if (NEED_Z)  // (read past the units' bins and planes: finite numbers)
+        for (int k = tid; k < n_slots * a.unit_floats + nw * TOF_STAGE_FLOATS; k += blockDim.x) Fs[k] = 0.f;
+    if (NEED_X) {
+        build_sheet(a, L, nrow, X, a.x_stride, tid);
+        // (the forward walks four rows at a time)
+        for (int e = nrow * a.x_stride + tid; e < ((nrow + 3) & ~3) * a.x_stride; e += blockDim.x) X[e] = 0.f;
+    }
     __syncthreads();
 
-    // lane s holds the bin count and first bin of interval s
-    const int na_l = lane < a.tof.n_int ? a.tof.na[lane] : 0;
-    const int bf_l = lane < a.tof.n_int ? a.tof.bf[lane] : 0;
-
-    // segments -k and +k have the same oblique length and so the same weight
-    // table: the segment list puts such pairs in consecutive rounds of a wave,
-    // which then fills the table once
-    float table_dz2 = -1.f;
-    for (int sg = wave; wave < nwaves && sg < a.n_seg; sg += nwaves) {
-        const SegP S = a.segs[sg];
-        // lanes: plane pl of the segment and chunk ch; a segment of at most 32
-        // planes splits its live intervals over C = 64 / np_pad chunks (np_pad
-        // the planes rounded up to a power of two)
-        int lg = 0;
-        while ((1 << lg) < S.np) ++lg;
-        lg = __builtin_amdgcn_readfirstlane(lg);
-        const int np_pad = 1 << lg, C = 64 >> lg;
-        const bool has = (lane & (np_pad - 1)) < S.np;
-        const int p = S.p0 + (has ? (lane & (np_pad - 1)) : 0);
-        const PlaneP P = a.planes[p];
-        const int64_t lor = (int64_t)line * a.n_planes + p;
-        const float len = sqrtf(L.lt2 + S.dz2);
-        const float ell = L.vm_um * len;
-        int is = 0, ie = -1;
-        if (nrow > 0 && has) z_clip<true>(L, P, a.nz, is, ie);
-        // this lane's samples in t order: q in [qlo, qhi]
-        const int qlo = L.dlam > 0.f ? is - L.i_lo : L.i_hi - ie;
-        const int qhi = L.dlam > 0.f ? ie - L.i_lo : L.i_hi - is;
-
-        if constexpr (MODE == M_COUNT) {
-            if (nrow > 0 && ie >= is && lane < np_pad) {
-                kl += (double)(ie - is + 1);
-                for (int s = 0; s < a.tof.n_int; ++s) {
-                    const int na = a.tof.na[s];
-                    if (na <= 0) continue;
-                    const int c0 = max(cut_count(a.tof.edge[s], len, L.lam0, L.dlam, L.i_lo, L.i_hi), qlo);
-                    const int c1 = min(cut_count(a.tof.edge[s + 1], len, L.lam0, L.dlam, L.i_lo, L.i_hi), qhi + 1);
-                    if (c1 > c0) pairs += (double)na * (c1 - c0);
-                }
-            }
+    // rows [j_lo, j_hi] that some bin reaches (|t| grows with the length, so the
+    // shortest LOR bounds it; one row of margin)
+    const float reach = uniform(a.tof.tb[nt - 1] + a.tof.half_bin + a.tof.erf_clamp / a.tof.inv_sqrt2_sigma);
+    const float len0 = uniform(sqrtf(L.lt2)), len1 = uniform(sqrtf(fmaf(a.k_max * a.k_max, a.pitch2, L.lt2)));
+    int j_lo = 0, j_hi = nrow - 1;
+    if (NEED_X) {
+        const float h = reach / len0, r0 = (-h - lam_s) / L.dlam, r1 = (h - lam_s) / L.dlam;
+        const float lo = fmaxf(floorf(fminf(r0, r1)) - 1.f, 0.f), hi = fminf(ceilf(fmaxf(r0, r1)) + 1.f, (float)(nrow - 1));
+        if (lo <= hi) {
+            j_lo = __builtin_amdgcn_readfirstlane((int)lo) & ~3;  // (steps of four end inside X)
+            j_hi = __builtin_amdgcn_readfirstlane((int)hi);
         } else {
-            int cut = 0;
-            if (S.dz2 != table_dz2) {
-                cut = nrow > 0 ? fill_table(a, L, len, cuts, w4, w1) : 0;
-                table_dz2 = S.dz2;
-            } else if (nrow > 0 && lane <= a.tof.n_int) {
-                cut = cuts[lane];  // kept in the table by the fill
-            }
-            // axial sample position of row i: xz = zA * i + zB
-            // padded axial cell of row i: u = zA * i + zB (z + PADZ)
-            const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
-            const float zAf = has ? zA : 0.f, zBf = has ? zB : 0.f, umax = (float)(a.nz + PADZ);
-            const int drz = L.dlam > 0.f ? rz : -rz;
-            const float dfi = L.dlam > 0.f ? 1.f : -1.f;
-            // back-projection predicate: k = q - qlo_b in [0, span]; a lane with
-            // no samples gets a base far below every row
-            const unsigned span = qlo <= qhi ? (unsigned)(qhi - qlo) : 0u;
-            const int qlo_b = qlo <= qhi ? qlo : -(1 << 30);
-            const int cut_next = __shfl_down(cut, 1, 64);
-            // intervals with bins whose rows meet some lane's sample range
-            int qa = qlo <= qhi ? qlo : INT_MAX, qb = qlo <= qhi ? qhi : -1;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                qa = min(qa, __shfl_xor(qa, o, 64));
-                qb = max(qb, __shfl_xor(qb, o, 64));
-            }
-            const bool meets = nrow > 0 && na_l > 0 && max(cut, qa) < min(cut_next, qb + 1);
-            const float m = has ? (a.mult ? a.mult[lor] : 1.f) : 0.f;
-            const int64_t base = lor * nt;
-
-            // TOF bins in blocks of NT_BLK held in registers (one block unless
-            // the geometry has more bins); an interval whose bins straddle two
-            // blocks is walked once per block
-            for (int b0 = 0; b0 < nt; b0 += NT_BLK) {
-                const int nb = min(NT_BLK, nt - b0);
-                const uint64_t live_mask = __ballot(meets && bf_l < b0 + NT_BLK && bf_l + na_l > b0);
-                float acc[NT_BLK];
-#pragma unroll
-                for (int b = 0; b < NT_BLK; ++b) acc[b] = 0.f;
-
-                // ---- forward projection ----
-                if (NEED_X) {
-                    if (C == 1) {
-                        // every lane walks the same rows of one interval at a time: a scalar loop
-                        for (uint64_t mk = live_mask; mk; mk &= mk - 1) {
-                            const int s = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mk));
-                            const int na = __builtin_amdgcn_readlane(na_l, s);
-                            const int c0 = __builtin_amdgcn_readlane(cut, s);
-                            const int c1 = __builtin_amdgcn_readlane(cut_next, s);
-                            const int rel = __builtin_amdgcn_readlane(bf_l, s) - b0;
-                            float win[WS_MAX];
-#pragma unroll
-                            for (int j = 0; j < WS_MAX; ++j) win[j] = 0.f;
-                            const int i0 = L.dlam > 0.f ? L.i_lo + c0 : L.i_hi - c0;
-                            const float *xr0 = X + (i0 - L.i_lo) * rz;
-                            PET_NA_SWITCH(tof_fwd_run, zAf, zBf, umax, xr0, drz, (float)i0, dfi, w4 + 4 * c0,
-                                          w1 + c0 * e1, e1, 1, c1 - c0, win)
-                            PET_REL_SWITCH(add_window, acc, win, na)
-                        }
-                    } else {
-                        // chunk k = lane >> lg takes all rows of the k-th of the next C live
-                        // intervals, with the geometry's widest window (the weights past an
-                        // interval's own bins are zero)
-                        for (uint64_t mk = live_mask; mk; mk = drop_intervals(mk, C)) {
-                            const int s = kth_interval(mk, lane >> lg);
-                            const int sc = s < 0 ? 0 : s;
-                            // every lane shuffles (a lane-permute reads zero from a lane that
-                            // is switched off), then selects
-                            const int c0 = __shfl(cut, sc, 64), c1 = __shfl(cut_next, sc, 64);
-                            const int nas = __shfl(na_l, sc, 64), bfs = __shfl(bf_l, sc, 64);
-                            const int rel = s < 0 ? 0 : bfs - b0;
-                            const int nl = s < 0 ? 0 : c1 - c0;
-                            float win[WS_MAX];
-#pragma unroll
-                            for (int j = 0; j < WS_MAX; ++j) win[j] = 0.f;
-                            const int i0 = L.dlam > 0.f ? L.i_lo + c0 : L.i_hi - c0;
-                            const float *xr0 = X + (i0 - L.i_lo) * rz;
-                            {
-                                const int na = ws;
-                                PET_NA_SWITCH(tof_fwd_run, zAf, zBf, umax, xr0, drz, (float)i0, dfi, w4 + 4 * c0,
-                                              w1 + c0 * e1, e1, 1, nl, win)
-                            }
-                            {
-                                const int na = s < 0 ? 0 : nas;
-                                PET_REL_SWITCH(add_window, acc, win, na)
-                            }
-                        }
-                    }
-                    // the chunks of a plane hold partial sums over their intervals
-                    for (int o = np_pad; o < 64; o <<= 1) {
-#pragma unroll
-                        for (int b = 0; b < NT_BLK; ++b) acc[b] += __shfl_xor(acc[b], o, 64);
-                    }
-                }
-
-                // ---- ratio / output ----
-                if (has) {
-                    const int64_t bb = base + b0;
-                    if constexpr (MODE == M_BACK) {
-                        float sv[NT_BLK];
-                        if (a.sino) load_row(a.sino, bb, nb, sv);
-#pragma unroll
-                        for (int b = 0; b < NT_BLK; ++b) acc[b] = (a.sino ? sv[b] : 1.f) * m * ell;
-                    } else if constexpr (MODE == M_HVP) {
-                        float yb[NT_BLK], yv[NT_BLK];
-                        load_row(a.ybar, bb, nb, yb);
-                        load_y_row(a.y, a.y_dtype, bb, nb, yv);
-#pragma unroll
-                        for (int b = 0; b < NT_BLK; ++b)
-                            acc[b] = (b < nb && yv[b] != 0.f) ? m * m * yv[b] / (yb[b] * yb[b]) * (acc[b] * ell) * ell
-                                                              : 0.f;
-                    } else {
-                        float ad[NT_BLK], yv[NT_BLK];
-#pragma unroll
-                        for (int b = 0; b < NT_BLK; ++b) ad[b] = 0.f;
-                        if (a.add) load_row(a.add, bb, nb, ad);
-                        if constexpr (MODE != M_FWD) load_y_row(a.y, a.y_dtype, bb, nb, yv);
-#pragma unroll
-                        for (int b = 0; b < NT_BLK; ++b) {
-                            if (b >= nb) continue;
-                            const float ybar = fmaf(m, acc[b] * ell, ad[b]);
-                            if constexpr (MODE == M_FWD) {
-                                if (lane < np_pad) a.out[bb + b] = ybar;
-                            } else {
-                                if (a.partial && lane < np_pad) kl += kl_term(ybar, yv[b]);
-                                if constexpr (MODE == M_GRAD)
-                                    acc[b] = m * (yv[b] != 0.f ? fmaf(-yv[b], __builtin_amdgcn_rcpf(ybar), 1.f) : 1.f) * ell;
-                                if constexpr (MODE == M_EM)
-                                    acc[b] = yv[b] != 0.f ? m * (yv[b] * __builtin_amdgcn_rcpf(ybar)) * ell : 0.f;
-                            }
-                        }
-                    }
-                }
-
-                // ---- adjoint into the LDS gradient sheet ----
-                if (NEED_Z) {
-                    if (C == 1) {
-                        for (uint64_t mk = live_mask; mk; mk &= mk - 1) {
-                            const int s = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mk));
-                            const int na = __builtin_amdgcn_readlane(na_l, s);
-                            const int c0 = __builtin_amdgcn_readlane(cut, s);
-                            const int c1 = __builtin_amdgcn_readlane(cut_next, s);
-                            const int rel = __builtin_amdgcn_readlane(bf_l, s) - b0;
-                            float win[WS_MAX];
-                            PET_REL_SWITCH(get_window, acc, win, na)
-                            const int i0 = L.dlam > 0.f ? L.i_lo + c0 : L.i_hi - c0;
-                            double *zr0 = Z + (i0 - L.i_lo) * rz;
-                            PET_NA_SWITCH(tof_back_run, zA, zB, umax, zr0, drz, (float)i0, dfi, w4 + 4 * c0,
-                                          w1 + c0 * e1, e1, 1, c1 - c0, c0 - qlo_b, span, win)
-                        }
-                    } else {
-                        // the intervals split over the chunks as in the forward pass
-                        for (uint64_t mk = live_mask; mk; mk = drop_intervals(mk, C)) {
-                            const int s = kth_interval(mk, lane >> lg);
-                            const int sc = s < 0 ? 0 : s;
-                            // every lane shuffles (a lane-permute reads zero from a lane that
-                            // is switched off), then selects
-                            const int c0 = __shfl(cut, sc, 64), c1 = __shfl(cut_next, sc, 64);
-                            const int nas = __shfl(na_l, sc, 64), bfs = __shfl(bf_l, sc, 64);
-                            const int rel = s < 0 ? 0 : bfs - b0;
-                            const int nl = s < 0 ? 0 : c1 - c0;
-                            float win[WS_MAX];
-                            {
-                                const int na = s < 0 ? 0 : nas;
-                                PET_REL_SWITCH(get_window, acc, win, na)
-                            }
-                            const int i0 = L.dlam > 0.f ? L.i_lo + c0 : L.i_hi - c0;
-                            double *zr0 = Z + (i0 - L.i_lo) * rz;
-                            {
-                                const int na = ws;
-                                PET_NA_SWITCH(tof_back_run, zA, zB, umax, zr0, drz, (float)i0, dfi, w4 + 4 * c0,
-                                              w1 + c0 * e1, e1, 1, nl, c0 - qlo_b, span, win)
-                            }
-                        }
-                    }
-                }
-            }
-            // the next segment may overwrite this wave's table
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
+            j_hi = -1;
         }
     }
-    if (NEED_Z && nrow > 0) {
-        __syncthreads();
-        scatter_sheet(a, L, nrow, Z, g_off);
+
+    const int nblk = NEED_Z ? (nrow + 15) >> 4 : 0;
+    const int nzc = (a.nz + 16 * NZB - 1) / (16 * NZB);
+    // a wave's cells stay in its registers over the groups of units if it has
+    // one block of rows and one pass along z; else they are spread per group
+    const bool keep = !KL && nblk <= nw && nzc == 1;
+    double acc[4][NZB];
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int zb = 0; zb < NZB; ++zb) acc[h][zb] = 0.0;
+
+    double *kl_w = nullptr;  // this wave's sum (in LDS: no register through the adjoint)
+    if constexpr (KL) {
+        __shared__ double s_kl[MAX_WAVES];
+        kl_w = s_kl + wave;
+        if (lane_here() == 0) *kl_w = 0.0;
     }
+    for (int u0 = 0; u0 < a.n_units; u0 += a.q_units) {
+        double kl_u = 0.0;
+        const int u1 = NEED_Z ? min(u0 + a.q_units, a.n_units) : a.n_units;
+        // ---- forward projection and factors, one unit per wave ----
+        for (int u = u0 + wave; u < u1; u += nw) {
+            const int lane = lane_here(), pl = lane & 15, g = lane >> 4;
+            const int p0 = units[u].p0, np = units[u].np;
+            const int npb = (np + 15) >> 4;
+            const TofPos tp = utab[u];
+            // Bin b of plane idx in LDS: F[(idx / 16 nt + b) 16 + idx mod 16] (the
+            // tiles are filled up with zero planes), in memory base + idx nt + b.
+            float *F = Fs + (NEED_Z ? u - u0 : wave) * a.unit_floats;
+            const int64_t lor0 = (int64_t)line * a.n_planes + p0, base = lor0 * nt;
+            auto slow = [&](int i0, int i1, auto each) {  // the bins of planes [i0, i1), one per lane and round
+#pragma unroll 1
+                for (int e = i0 * nt + lane_here(); e < i1 * nt; e += 64) {
+                    const int idx = (e * a.inv_nt) >> 16, b = e - idx * nt;  // (e < 64 n_tof <= 2048)
+                    each(e, idx, b, F + ((idx >> 4) * nt + b) * 16 + (idx & 15));
+                }
+            };
+            bool bad = false;  // a factor that is not finite
+            // (TILES tiles of 16 planes at a time)
+            for (int t0 = 0; t0 < (TILES == 4 ? 1 : npb); t0 += TILES) {
+            const int nt0 = min(TILES, npb - t0);
+            f32x4 D[MB][TILES];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < TILES; ++pb) D[mb][pb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (NEED_X) {
+                float zA[TILES], zB[TILES];
+#pragma unroll
+                for (int pb = 0; pb < TILES; ++pb) {
+                    const int idx = 16 * (t0 + pb) + pl;
+                    const PlaneP P = a.planes[p0 + min(idx, np - 1)];
+                    zA[pb] = idx < np ? P.zs * L.dlam : 0.f;
+                    zB[pb] = idx < np ? (float)fma((double)L.lam0, P.zs, P.zb + (double)PADZ) : 0.f;
+                }
+                auto rows = [&](auto tiles) {
+                    tof_fwd_rows<MB, tiles.value, TILES>(a, tab, X, j_lo, j_hi, L.i_lo, lane, tp, zA, zB, D);
+                };
+                if (nt0 == 1)
+                    rows(Int<1>());
+                else if (nt0 == 2 || TILES == 2)
+                    rows(Int<2>());
+                else if (nt0 == 3)
+                    rows(Int<(TILES > 2 ? 3 : 2)>());
+                else
+                    rows(Int<TILES>());
+            }
+            // (this lane's bins of plane idx = 16 (t0 + pb) + pl: mb bins_blk + 4 g + r)
+            const int i0 = 16 * t0, i1 = min(np, 16 * (t0 + nt0));
+            bool special = false;
+            if (MODE == M_FWD) {
+                float top = 0.f;  // (NaN and inf stay)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int pb = 0; pb < TILES; ++pb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) top += fabsf(D[mb][pb][r]);
+                special = __any(!(top < INFINITY));
+            }
+            if (KL) {
+                // D to F: the terms one per lane and round
+                const int ln = lane_here();
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int pb = 0; pb < TILES; ++pb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int b = mb * a.bins_blk + 4 * (ln >> 4) + r;
+                            if (pb < nt0 && 4 * (ln >> 4) + r < a.bins_blk && b < nt)
+                                F[((t0 + pb) * nt + b) * 16 + (ln & 15)] = D[mb][pb][r];
+                        }
+                wave_lds_order();
+                slow(i0, i1, [&](int e, int idx, int b, float *f) {
+                    float sum = *f;
+                    if (!(fabsf(sum) < INFINITY)) sum = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b);
+                    const float m = a.mult ? a.mult[lor0 + idx] : 1.f;
+                    kl_u += kl_term_lean(fmaf(m, sum * tp.ell, a.add ? a.add[base + e] : 0.f),
+                                       load_y(a.y, a.y_dtype, base + e));
+                });
+                wave_lds_order();
+            }
+            if (MODE == M_FWD && special) {
+                // (without the products of zero weights)
+                slow(i0, i1, [&](int e, int idx, int b, float *) {
+                    const float sum = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b);
+                    a.out[base + e] = fmaf(a.mult ? a.mult[lor0 + idx] : 1.f, sum * tp.ell, a.add ? a.add[base + e] : 0.f);
+                });
+                continue;
+            }
+            if (MODE == M_OBJ) continue;
+            float top = 0.f;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const int b0 = mb * a.bins_blk + 4 * g;
+                const int nb = min(a.bins_blk - 4 * g, nt - b0);  // this lane's bins of the block (at most 4 used)
+                // (two tiles' loads in flight together)
+#pragma unroll
+                for (int ph = 0; ph < TILES; ph += 2) {
+                    if (ph < nt0) {
+                float v[TILES][4], yv[TILES][4], m[TILES];
+#pragma unroll
+                for (int pb = ph; pb < ph + 2; ++pb) {
+                    const int idx = 16 * (t0 + pb) + pl;
+                    const bool has = idx < np;
+                    const int n = has ? nb : 0;
+                    const int off = idx * nt + b0;
+                    m[pb] = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[pb][r] = yv[pb][r] = 0.f;
+                    if (n <= 0) continue;
+                    m[pb] = a.mult ? a.mult[lor0 + idx] : 1.f;
+                    if constexpr (MODE == M_BACK) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[pb][r] = 1.f;
+                        if (a.sino) load_bins(a.sino + base + off, n, v[pb]);
+                    } else if constexpr (MODE == M_HVP) {
+                        load_bins(a.ybar + base + off, n, v[pb]);
+                    } else {
+                        if (a.add) load_bins(a.add + base + off, n, v[pb]);
+                    }
+                    if constexpr (MODE != M_BACK && MODE != M_FWD) load_counts(a.y, a.y_dtype, base + off, n, yv[pb]);
+                }
+#pragma unroll
+                for (int pb = ph; pb < ph + 2; ++pb) {
+                    const int idx = 16 * (t0 + pb) + pl;
+                    const bool has = idx < np;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (r >= nb || pb >= nt0) continue;
+                        const float s = D[mb][pb][r] * tp.ell;
+                        float Q = 0.f;
+                        if constexpr (MODE == M_FWD) v[pb][r] = fmaf(m[pb], s, v[pb][r]);
+                        if constexpr (NEED_Z) Q = tof_factor<MODE>(m[pb], s, v[pb][r], yv[pb][r], tp.ell);
+                        if (NEED_Z) {
+                            if (!has) Q = 0.f;
+                            top += fabsf(Q);
+                            F[((t0 + pb) * nt + b0 + r) * 16 + pl] = Q;
+                        }
+                    }
+                    if constexpr (MODE == M_FWD)
+                        if (has) store_bins(a.out + base + idx * nt + b0, nb, v[pb]);
+                }
+                }
+                }
+            }
+            bad |= !(top < INFINITY);
+            }
+            if (NEED_Z && __any(bad)) {
+                // (the products also take a bin's sum from rows, and its factor to
+                // rows and planes, where the weight is 0)
+                wave_lds_order();
+                slow(0, np, [&](int e, int idx, int b, float *f) {
+                    float Q = *f;
+                    if (fabsf(Q) < INFINITY) return;
+                    if (NEED_X) {
+                        const float s = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b) * tp.ell;
+                        const float v = MODE == M_HVP ? a.ybar[base + e] : a.add ? a.add[base + e] : 0.f;
+                        Q = tof_factor<MODE>(a.mult ? a.mult[lor0 + idx] : 1.f, s, v, load_y(a.y, a.y_dtype, base + e), tp.ell);
+                    }
+                    if (fabsf(Q) < INFINITY) {
+                        *f = Q;
+                        return;
+                    }
+                    tof_back_special(a, L, tab, nrow, tp, a.planes[p0 + idx], b, Q, g_off);
+                    *f = 0.f;
+                });
+            }
+        }
+        if (KL) {
+#pragma unroll
+            for (int k = 32; k; k >>= 1) {
+                const int from = (lane_here() ^ k) << 2;
+                kl_u += __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(kl_u)),
+                                         __builtin_amdgcn_ds_bpermute(from, __double2loint(kl_u)));
+            }
+            if (lane_here() == 0) *kl_w += kl_u;
+        }
+        if (!NEED_Z) break;
+        __syncthreads();
+
+        // ---- adjoint, one block of 16 rows per wave ----
+        for (int iz = 0; iz < nzc; ++iz) {
+            const int z0 = 16 * NZB * iz;
+            for (int rb = wave; rb < nblk; rb += nw) {
+                if (!keep) {
+#pragma unroll
+                    for (int h = 0; h < 4; ++h)
+#pragma unroll
+                        for (int zb = 0; zb < NZB; ++zb) acc[h][zb] = 0.0;
+                }
+                // the groups of four bins that reach these rows at some length
+                const float la = fmaf((float)(16 * rb), L.dlam, lam_s);
+                const float lb = fmaf((float)min(16 * rb + 15, nrow - 1), L.dlam, lam_s);
+                const float l0 = fminf(la, lb), l1 = fmaxf(la, lb);
+                const float t0 = l0 * (l0 < 0.f ? len1 : len0), t1 = l1 * (l1 < 0.f ? len0 : len1);
+                const float rbw = 0.5f / a.tof.half_bin, sup = reach - a.tof.tb[nt - 1];
+                const int b0 = (int)fmaxf(floorf((t0 - sup - a.tof.tb[0]) * rbw - 0.01f), 0.f);
+                const int b1 = (int)fmaxf(fminf(ceilf((t1 + sup - a.tof.tb[0]) * rbw + 0.01f), (float)(nt - 1)), -1.f);
+                const int kk0 = __builtin_amdgcn_readfirstlane(b0) >> 2;
+                const int nkk = (__builtin_amdgcn_readfirstlane(b1) >> 2) + 1 - kk0;
+                if (nkk > 0) {
+                    const TofBack k = {Fs, stage, utab, tab, u0, u1, rb, kk0, nkk};
+                    tof_back_rows<NZB, MANY>(a, L, k, z0, acc);
+                }
+                if (!keep || u1 == a.n_units) {
+                    // the cells to the global sheet, through the staged rows so that
+                    // consecutive lanes add to consecutive voxels
+                    const int ln = lane_here();
+                    float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
+                    const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
+                    const int nz = min(16 * NZB, a.nz - z0);
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        wave_lds_order();
+                        float *sc = stage + (ln >> 4) * STAGE_COLS + (ln & 15);
+#pragma unroll
+                        for (int zb = 0; zb < NZB; ++zb) sc[16 * zb] = (float)acc[h][zb];
+                        wave_lds_order();
+                        for (int sr = 0; sr < STAGE_ROWS; ++sr) {
+                            const int j = 16 * rb + 4 * sr + h;
+                            if (j >= nrow) break;
+                            const SheetRow row = sheet_row(L, L.i_lo + j, other_stride, rz);
+                            for (int z = ln; z < nz; z += 64) {
+                                const float val = stage[sr * STAGE_COLS + z];
+                                if (val != 0.f) spread_cell(Gout, row, z0 + z + PADZ, rz, val);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        if (u1 < a.n_units) __syncthreads();
+    }
+    if (KL && lane_here() == 0) kl += *kl_w;
 }
 
 // One line per workgroup, in the order a.order (longest first).
-template <int MODE>
-__global__ void __launch_bounds__(64 * TOF_MAX_WAVES) k_line_tof(ProjArgs a) {
+template <int MODE, int MB, int NZB, bool MANY, bool KL>
+__global__ void __launch_bounds__(TOF_BLOCK, 4) k_line_tof(ProjArgs a) {
     extern __shared__ float4 smem4[];
-    double kl = 0.0, pairs = 0.0;
-    line_tof_body<MODE>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), blockDim.x >> 6, kl, pairs);
-    if (MODE != M_FWD && MODE != M_BACK && a.partial) block_sums(kl, pairs, a.partial, MODE == M_COUNT);
+    double kl = 0.0;  // (not live through the body)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    line_tof_body<MODE, MB, NZB, MANY, KL, MB == 1 ? 4 : 2>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), wave, kl);
+    if (KL) block_sums(kl, kl, a.partial, false, 64 * wave + lane_here());
+}
+
+// Work counts of a TOF line: samples, and sample-bin pairs within the bins'
+// supports (intervals between the support edges), one plane per thread.
+__global__ void __launch_bounds__(NT_BLOCK) k_count_tof(ProjArgs a) {
+    const LineP L = a.lines[a.order[blockIdx.x]];
+    const int nrow = L.i_hi - L.i_lo + 1;
+    double samples = 0.0, pairs = 0.0;
+    for (int p = threadIdx.x; nrow > 0 && p < a.n_planes; p += blockDim.x) {
+        const PlaneP P = a.planes[p];
+        const float len = sqrtf(L.lt2 + P.dz2);
+        int is, ie;
+        z_clip<true>(L, P, a.nz, is, ie);
+        if (ie < is) continue;
+        // this plane's samples in t order
+        const int qlo = L.dlam > 0.f ? is - L.i_lo : L.i_hi - ie;
+        const int qhi = L.dlam > 0.f ? ie - L.i_lo : L.i_hi - is;
+        samples += (double)(ie - is + 1);
+        for (int s = 0; s < a.tof.n_int; ++s) {
+            const int na = a.tof.na[s];
+            if (na <= 0) continue;
+            const int c0 = max(cut_count(a.tof.edge[s], len, L.lam0, L.dlam, L.i_lo, L.i_hi), qlo);
+            const int c1 = min(cut_count(a.tof.edge[s + 1], len, L.lam0, L.dlam, L.i_lo, L.i_hi), qhi + 1);
+            if (c1 > c0) pairs += (double)na * (c1 - c0);
+        }
+    }
+    block_sums(samples, pairs, a.partial, true);
+}
+
+// The form of the TOF kernels that serves a geometry: one or two blocks of 16 bins
+// (a second, empty one would cost as many weights and products as the first); 48 or
+// 80 voxels along z per pass of the adjoint (the cells past a shorter axis are
+// gathered for nothing: with 33 slices and 25 bins a subset gradient takes 690 us
+// in the longer form and 601 in the shorter one, with 32 slices and 13 bins 118
+// and 109); two planes of a segment per voxel at most, or any number.
+template <typename F>
+void tof_form(int n_tof, int nz, bool gather_two, F &&f) {
+    const bool one = n_tof <= 16;
+    if (!gather_two)
+        one ? f(Int<1>(), Int<STAGE_ZB>(), Int<1>()) : f(Int<2>(), Int<STAGE_ZB>(), Int<1>());
+    else if (nz <= 48)
+        one ? f(Int<1>(), Int<3>(), Int<0>()) : f(Int<2>(), Int<3>(), Int<0>());
+    else
+        one ? f(Int<1>(), Int<STAGE_ZB>(), Int<0>()) : f(Int<2>(), Int<STAGE_ZB>(), Int<0>());
 }
 
 // Persistent subset-gradient kernel over a batch: the work items of one step
@@ -761,8 +1094,11 @@ __global__ void __launch_bounds__(64 * TOF_MAX_WAVES) k_line_tof(ProjArgs a) {
 // each into the gradient-sheet slot of its view's subset; else the lines of
 // the step's subset into slot 0), concatenated in `order`.  Workgroups take
 // items from a global counter (zeroed by the step's prep kernel) until none
-// is left.
-__global__ void __launch_bounds__(64 * TOF_MAX_WAVES) k_line_batched(const BMember *__restrict__ mem,
+// is left.  MB, NZB, MANY: the TOF form that serves every member (see tof_form;
+// each form of the line body also serves fewer bins, shorter axes, fewer planes).
+// (MANY with 80 voxels a pass would not fit the registers beside the loop.)
+template <int MB, int NZB, bool MANY>
+__global__ void __launch_bounds__(64 * MAX_WAVES) k_line_batched(const BMember *__restrict__ mem,
                                                                      const int *__restrict__ order, int n_mem,
                                                                      int step, int *__restrict__ counter) {
     extern __shared__ float4 smem4[];
@@ -780,29 +1116,32 @@ __global__ void __launch_bounds__(64 * TOF_MAX_WAVES) k_line_batched(const BMemb
         s_cum[n_mem] = c;
     }
     __syncthreads();
-    const int total = s_cum[n_mem];
-    const int nw = blockDim.x >> 6;
+    const int total = __builtin_amdgcn_readfirstlane(s_cum[n_mem]);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
+        if (wave == 0 && lane_here() == 0) s_item = atomicAdd(counter, 1);
         __syncthreads();
-        const int item = s_item;
+        // (scalar, and so the member's arguments)
+        const int item = __builtin_amdgcn_readfirstlane(s_item);
         if (item >= total) break;
         int q = 0;
-        while (s_cum[q + 1] <= item) ++q;
+        while (__builtin_amdgcn_readfirstlane(s_cum[q + 1]) <= item) ++q;
         const BMember &m = mem[order[q]];
+        const ProjArgs &pa = scalar_ref(m.pa);
         const BStep st = m.steps[step];
-        const int local = item - s_cum[q];
-        const int n_rad = m.pa.n_rad;
+        const int local = item - __builtin_amdgcn_readfirstlane(s_cum[q]);
+        const int n_rad = pa.n_rad;
         const int jv = local / n_rad;
         const int k = local - jv * n_rad;
         const bool snap = (st.flags & B_SNAP) != 0;
-        const int view = snap ? jv : m.views[st.subset * m.views_stride + jv];
+        const int view = __builtin_amdgcn_readfirstlane(snap ? jv : m.views[st.subset * m.views_stride + jv]);
         const int64_t g_off = snap ? (int64_t)(jv % m.n_sub) * m.g_slot : 0;
         if (m.is_tof) {
-            double kl = 0.0, pairs = 0.0;
-            line_tof_body<M_GRAD>(m.pa, view * n_rad + k, smem, min(m.tof_waves, nw), kl, pairs, g_off);
+            double no_kl = 0.0;
+            const int line = view * n_rad + k;
+            line_tof_body<M_GRAD, MB, NZB, MANY, false, MB == 1 ? 4 : 2>(pa, line, smem, wave, no_kl, g_off);
         } else {
-            line_nt_body<M_GRAD>(m.pa, view * n_rad + k, smem, g_off);
+            line_nt_body<M_GRAD>(pa, view * n_rad + k, smem, 64 * wave + lane_here(), g_off);
         }
         __syncthreads();
     }
@@ -818,27 +1157,59 @@ size_t nt_lds(const pet_geom_s *g) {
     return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0));
 }
 
-template <int MODE>
-hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
-    if (g->d.n_tof > 1)
-        hipLaunchKernelGGL((k_line_tof<MODE>), grid, dim3(64 * g->tof_waves), MODE == M_COUNT ? 0 : g->lds_bytes, s, a);
-    else
-        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(g->nt_threads), nt_lds<MODE>(g), s, a);
+template <int MODE, int MB, int NZB, bool MANY, bool KL>
+hipError_t launch_tof(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
+    const bool x = MODE != M_BACK, z = MODE != M_FWD && MODE != M_OBJ;
+    const size_t lds = tof_lds_bytes(g, x, z ? g->q_units : MODE == M_OBJ ? TOF_BLOCK / 64 : 0, z ? TOF_BLOCK / 64 : 0);
+    static size_t granted = 64 * 1024;
+    if (lds > granted) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY, KL>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e == hipSuccess) granted = lds;
+        (void)hipGetLastError();
+    }
+    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY, KL>), grid, dim3(TOF_BLOCK), lds, s, a);
     return hipGetLastError();
 }
 
-// Raise the dynamic-LDS limit of the line kernels to what this geometry needs
-// (checked against the device limit at creation).  Only needed above the
+template <int MODE>
+hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
+    if (g->d.n_tof == 1) {
+        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(g->nt_threads), nt_lds<MODE>(g), s, a);
+        return hipGetLastError();
+    }
+    if constexpr (MODE == M_COUNT) {
+        hipLaunchKernelGGL(k_count_tof, grid, dim3(g->nt_threads), 0, s, a);
+        return hipGetLastError();
+    } else {
+        hipError_t e = hipSuccess;
+        tof_form(a.tof.n_tof, a.nz, a.gather_two, [&](auto mb, auto nzb, auto many) {
+            // (without an adjoint the last two make no difference)
+            if constexpr (MODE == M_FWD || MODE == M_OBJ) {
+                e = launch_tof<MODE, mb.value, STAGE_ZB, false, MODE == M_OBJ>(g, grid, a, s);
+            } else {
+                if constexpr (MODE == M_GRAD || MODE == M_EM) {
+                    if (a.partial) {
+                        e = launch_tof<MODE, mb.value, nzb.value, many.value != 0, true>(g, grid, a, s);
+                        return;
+                    }
+                }
+                e = launch_tof<MODE, mb.value, nzb.value, many.value != 0, false>(g, grid, a, s);
+            }
+        });
+        return e;
+    }
+}
+
+// Raise the dynamic-LDS limit of the non-TOF line kernels to what this geometry
+// needs (checked against the device limit at creation).  Only needed above the
 // default; a failure here is reported by the launch itself.
 void set_lds_attr(size_t need) {
     static size_t granted = 64 * 1024;
     if (need <= granted) return;
-    const void *fns[] = {(const void *)k_line_nt<M_FWD>,   (const void *)k_line_nt<M_BACK>,
-                         (const void *)k_line_nt<M_GRAD>,  (const void *)k_line_nt<M_EM>,
-                         (const void *)k_line_nt<M_OBJ>,   (const void *)k_line_nt<M_HVP>,
-                         (const void *)k_line_tof<M_FWD>,  (const void *)k_line_tof<M_BACK>,
-                         (const void *)k_line_tof<M_GRAD>, (const void *)k_line_tof<M_EM>,
-                         (const void *)k_line_tof<M_OBJ>,  (const void *)k_line_tof<M_HVP>};
+    const void *fns[] = {(const void *)k_line_nt<M_FWD>,  (const void *)k_line_nt<M_BACK>,
+                         (const void *)k_line_nt<M_GRAD>, (const void *)k_line_nt<M_EM>,
+                         (const void *)k_line_nt<M_OBJ>,  (const void *)k_line_nt<M_HVP>};
     hipError_t e = hipSuccess;
     for (const void *f : fns)
         if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
@@ -857,7 +1228,7 @@ hipError_t launch_back_fold(const pet_geom_s *g, dim3 grid, const ProjArgs &a0, 
 }
 
 hipError_t launch_line_kernel_impl(const pet_geom_s *g, int mode, dim3 grid, const ProjArgs &a, hipStream_t s) {
-    set_lds_attr(std::max(g->lds_bytes, nt_lds<M_GRAD>(g)));
+    set_lds_attr(nt_lds<M_GRAD>(g));
     switch (mode) {
         case M_FWD: return launch_mode<M_FWD>(g, grid, a, s);
         case M_BACK:
@@ -874,17 +1245,24 @@ hipError_t launch_line_kernel_impl(const pet_geom_s *g, int mode, dim3 grid, con
 
 }  // namespace
 
-hipError_t prime_line_batched(size_t lds) {
-    static size_t granted = 64 * 1024;
-    if (lds <= granted) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void *)k_line_batched, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) granted = lds;
+hipError_t prime_line_batched(const BatchForm &f, size_t lds) {
+    hipError_t e = hipSuccess;
+    tof_form(f.n_tof, f.nz, f.gather_two, [&](auto mb, auto nzb, auto many) {
+        static size_t granted = 64 * 1024;
+        if (lds <= granted) return;
+        e = hipFuncSetAttribute((const void *)k_line_batched<mb.value, many.value ? 3 : nzb.value, many.value != 0>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e == hipSuccess) granted = lds;
+    });
     return e;
 }
 
-hipError_t launch_line_batched(const BMember *mem, const int *order, int n_mem, int step, int *counter, int blocks,
-                               int waves, size_t lds, hipStream_t s) {
-    hipLaunchKernelGGL(k_line_batched, dim3(blocks), dim3(64 * waves), lds, s, mem, order, n_mem, step, counter);
+hipError_t launch_line_batched(const BatchForm &f, const BMember *mem, const int *order, int n_mem, int step,
+                               int *counter, int blocks, int waves, size_t lds, hipStream_t s) {
+    tof_form(f.n_tof, f.nz, f.gather_two, [&](auto mb, auto nzb, auto many) {
+        hipLaunchKernelGGL((k_line_batched<mb.value, many.value ? 3 : nzb.value, many.value != 0>), dim3(blocks), dim3(64 * waves), lds, s,
+                           mem, order, n_mem, step, counter);
+    });
     return hipGetLastError();
 }
 
