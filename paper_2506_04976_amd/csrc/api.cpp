@@ -614,33 +614,44 @@ static pet_status sgm_epoch(pet_geom g, pet_svrg_state *st, int estimator, float
             if (e == hipSuccess) e = launch_from_sheets(g, st->ghat_i + (size_t)q * nv, 0, s);
         }
     }
+    // as in svrg_epoch_impl: the iterate alternates between x and xtmp, and fused
+    // steps leave the image sheets of the new iterate and zero gradient sheets
+    float *cur = x, *nxt = g->xtmp;
+    const bool fuse = step_tile_ok(g) && !st->kappa;
+    bool sheets = false, zeroed = false;
     for (int j = 0; j < n && e == hipSuccess; ++j) {
         const int64_t k = st->k + j;
         const int i = subset_seq[j];
         const bool first = estimator == SGM_SAGA && k == 0;
-        e = launch_to_sheets(g, x, s);
+        if (!sheets) e = launch_to_sheets(g, cur, s);
         if (first) {
             // table of data gradients at x, then the prior shares and the sum
             for (int q = 0; q < n && e == hipSuccess; ++q) {
-                e = cnt ? counts_grad_sheets(g, cnt, q, nullptr, s)
-                        : subset_grad_sheets(g, q, st->y, st->y_dtype, st->add, st->mult, nullptr, 0, s);
-                if (e == hipSuccess) e = launch_snapshot_accum(g, st->ghat_i + (size_t)q * nv, st->ghat, nullptr, q == 0, s);
+                e = cnt ? counts_grad_sheets(g, cnt, q, nullptr, s, 0, zeroed)
+                        : subset_grad_sheets(g, q, st->y, st->y_dtype, st->add, st->mult, nullptr, 0, s, zeroed);
+                if (e == hipSuccess)
+                    e = launch_snapshot_accum(g, st->ghat_i + (size_t)q * nv, st->ghat, nullptr, q == 0, s, nullptr, fuse);
+                zeroed = fuse;
             }
             if (e == hipSuccess)
-                e = launch_rdp(g, x, st->kappa, st->w, st->beta, st->gamma, st->eps, g->num, nullptr, nullptr, s);
+                e = launch_rdp(g, cur, st->kappa, st->w, st->beta, st->gamma, st->eps, g->num, nullptr, nullptr, s);
             if (e == hipSuccess) e = launch_saga_table_prior(g, st->ghat_i, st->ghat, g->num, s, cnt ? st->sens : nullptr);
         } else {
-            e = cnt ? counts_grad_sheets(g, cnt, i, nullptr, s)
-                    : subset_grad_sheets(g, i, st->y, st->y_dtype, st->add, st->mult, nullptr, 0, s);
-            if (e == hipSuccess) e = launch_from_sheets(g, g->g, 0, s);
+            if (e == hipSuccess)
+                e = cnt ? counts_grad_sheets(g, cnt, i, nullptr, s, 0, zeroed)
+                        : subset_grad_sheets(g, i, st->y, st->y_dtype, st->add, st->mult, nullptr, 0, s, zeroed);
+            if (e == hipSuccess && !fuse) e = launch_from_sheets(g, g->g, 0, s);
         }
         float *table_i = estimator == SGM_SAGA || cnt ? st->ghat_i + (size_t)i * nv : nullptr;
         if (e == hipSuccess)
-            e = launch_sgm_step(g, estimator, x, st->kappa, st->w, st->beta, st->gamma, st->eps, update_pc[j],
+            e = launch_sgm_step(g, estimator, cur, st->kappa, st->w, st->beta, st->gamma, st->eps, update_pc[j],
                                 st->sens, st->alpha, st->delta, st->D, first, g->g, table_i, st->ghat, (float)n,
-                                tau[j], g->xtmp, s);
-        if (e == hipSuccess) e = launch_copy(x, g->xtmp, nv, s);
+                                tau[j], nxt, fuse, s);
+        sheets = fuse;
+        zeroed = fuse;
+        std::swap(cur, nxt);
     }
+    if (e == hipSuccess && cur != x) e = launch_copy(x, cur, nv, s);
     if (e != hipSuccess) return hip_check(e, name);
     st->k += n;
     if (objective_out)

@@ -450,7 +450,7 @@ hipError_t launch_saga_table_prior(const pet_geom_s *g, float *table, double *ta
 hipError_t launch_sgm_step(const pet_geom_s *g, int estimator, const float *x, const float *kappa, const float *w27,
                            float beta, float gamma, float eps, int update_pc, const float *sens, float alpha,
                            float delta, float *D, int first, const float *gi, float *table_i, double *table_sum,
-                           float n_sub, float tau, float *x_out, hipStream_t s);
+                           float n_sub, float tau, float *x_out, bool tile, hipStream_t s);
 // ghat_i <- the gradient sheets' image; ghat (+)= it in FP64 (first: ghat = base + it, base nullable)
 // clear (only without a resolution model): zero the gradient sheets' cells
 // after reading them
