@@ -201,8 +201,7 @@ hipError_t hvp_impl(pet_geom g, int subset, const float *x, const float *v, cons
     a.mult = mult;
     a.out = ybar_work;
     if (e == hipSuccess) e = launch_line_kernel(g, M_FWD, subset, a, s);
-    if (e == hipSuccess) e = launch_to_sheets(g, v, s);
-    if (e == hipSuccess) e = launch_zero_sheets(g, s);
+    if (e == hipSuccess) e = launch_to_sheets(g, v, s, true);
     ProjArgs b = base_args(g, subset);
     b.y = y;
     b.y_dtype = dt;
@@ -317,8 +316,8 @@ extern "C" pet_status pet_subset_grad(pet_geom g, int subset, const float *x, co
         const pet_status st = check_data(g, g->check_counts, s, "pet_subset_grad", x, y, y_dtype, add, mult);
         if (st != PET_OK) return st;
     }
-    hipError_t e = launch_to_sheets(g, x, s);
-    if (e == hipSuccess) e = subset_grad_sheets(g, subset, y, y_dtype, add, mult, kl_out, 0, s);
+    hipError_t e = launch_to_sheets(g, x, s, true);
+    if (e == hipSuccess) e = subset_grad_sheets(g, subset, y, y_dtype, add, mult, kl_out, 0, s, true);
     if (e == hipSuccess) e = launch_from_sheets(g, grad_out, 0, s);
     return hip_check(e, "pet_subset_grad");
 }
@@ -375,8 +374,7 @@ extern "C" pet_status pet_osem_epoch(pet_geom g, float *x, const void *y, int y_
         if (e == hipSuccess) e = launch_line_kernel(g, M_BACK, i, a, s);
         if (e == hipSuccess) e = launch_from_sheets(g, g->sensi, 0, s);
         // P_i^T (mult y / ybar)
-        if (e == hipSuccess) e = launch_to_sheets(g, x, s);
-        if (e == hipSuccess) e = launch_zero_sheets(g, s);
+        if (e == hipSuccess) e = launch_to_sheets(g, x, s, true);
         ProjArgs b = base_args(g, i);
         b.y = y;
         b.y_dtype = y_dtype;
@@ -873,8 +871,8 @@ extern "C" pet_status pet_subset_grad_counts(pet_geom g, pet_counts c, int subse
         if (cs != PET_OK) return cs;
     }
     const int row = subset < 0 ? c->n_subsets : subset;
-    hipError_t e = launch_to_sheets(g, x, s);
-    if (e == hipSuccess) e = counts_grad_sheets(g, c, subset, kl_out, s);
+    hipError_t e = launch_to_sheets(g, x, s, true);
+    if (e == hipSuccess) e = counts_grad_sheets(g, c, subset, kl_out, s, 0, true);
     if (e == hipSuccess) e = launch_from_sheets(g, grad_out, 0, s);
     if (e == hipSuccess && sens_subset) e = launch_lincomb(grad_out, 1.f, grad_out, 1.f, sens_subset, g->n_vox, s);
     if (e == hipSuccess && kl_out) e = launch_dot(sens_subset, x, g->n_vox, g->partial, kl_out, 1, s);
@@ -910,8 +908,8 @@ extern "C" pet_status pet_osem_epoch_counts(pet_geom g, pet_counts c, float *x, 
             e = j == 0 ? launch_copy(sens_out, g->sensi, g->n_vox, s)
                        : launch_lincomb(sens_out, 1.f, sens_out, 1.f, g->sensi, g->n_vox, s);
         // -P_i^T (mult y / ybar) from the bins with counts; the update negates
-        if (e == hipSuccess) e = launch_to_sheets(g, x, s);
-        if (e == hipSuccess) e = counts_grad_sheets(g, c, i, nullptr, s);
+        if (e == hipSuccess) e = launch_to_sheets(g, x, s, true);
+        if (e == hipSuccess) e = counts_grad_sheets(g, c, i, nullptr, s, 0, true);
         if (e == hipSuccess) e = launch_from_sheets(g, g->num, 0, s);
         if (e == hipSuccess) e = launch_osem_update(g, x, g->num, g->sensi, s, -1.f);
     }

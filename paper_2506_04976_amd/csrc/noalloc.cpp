@@ -111,8 +111,7 @@ extern "C" pet_status pet_subset_grad_noalloc(pet_geom g, int subset, const floa
     // the array keeps the previous call's contents (possibly another layout):
     // the image sheets' zero borders and the gradient sheets are cleared here
     hipError_t e = launch_clear_image_sheets(g, w, s);
-    if (e == hipSuccess) e = launch_to_sheets_b(g, w, x, s);
-    if (e == hipSuccess) e = launch_zero_sheets_b(g, w, s);
+    if (e == hipSuccess) e = launch_to_sheets_b(g, w, x, s, true);
     ProjArgs a = subset_proj_args(g, subset);
     a.T0 = w.T0;
     a.T1 = w.T1;

@@ -389,13 +389,14 @@ struct SheetBufs {
     float *T0, *T1, *G0, *G1, *psf_a, *psf_b;
 };
 SheetBufs geom_bufs(const pet_geom_s *g);
-hipError_t launch_to_sheets_b(const pet_geom_s *g, const SheetBufs &w, const float *x, hipStream_t s);
+// (zero: the gradient sheets are cleared as well)
+hipError_t launch_to_sheets_b(const pet_geom_s *g, const SheetBufs &w, const float *x, hipStream_t s, bool zero = false);
 hipError_t launch_zero_sheets_b(const pet_geom_s *g, const SheetBufs &w, hipStream_t s);
 hipError_t launch_from_sheets_b(const pet_geom_s *g, const SheetBufs &w, float *out, int accumulate, hipStream_t s);
 hipError_t launch_clear_image_sheets(const pet_geom_s *g, const SheetBufs &w, hipStream_t s);
 hipError_t launch_psf_b(const pet_geom_s *g, const SheetBufs &w, const float *in, float *out, int accumulate,
                         hipStream_t s);
-hipError_t launch_to_sheets(const pet_geom_s *g, const float *x, hipStream_t s);
+hipError_t launch_to_sheets(const pet_geom_s *g, const float *x, hipStream_t s, bool zero = false);
 hipError_t launch_zero_sheets(const pet_geom_s *g, hipStream_t s);
 hipError_t launch_from_sheets(const pet_geom_s *g, float *out, int accumulate, hipStream_t s);
 hipError_t launch_rdp(const pet_geom_s *g, const float *x, const float *kappa, const float *w27,
