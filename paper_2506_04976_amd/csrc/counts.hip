@@ -20,9 +20,9 @@
 // forward and back.  The TOF weight of a sample at signed distance t from
 // the LOR centre in bin b depends only on d = t - t_b (the kernel is shift
 // invariant): W(d) = 1/2 [E(w/2 - d) - E(-w/2 - d)], E the clamped erf.  It
-// is tabulated once per geometry at NW_TAB + 1 nodes over its support
-// |d| <= w/2 + nsig sigma (FP64 on the host) and interpolated linearly from
-// LDS.
+// is even and tabulated once per geometry over half its support, |d| <= w/2 +
+// nsig sigma, in CNT_TAB intervals (FP64 on the host; each interval's line splits
+// the error evenly above and below), and interpolated linearly from LDS.
 #include "line_sheets.h"
 
 #include <algorithm>
@@ -116,7 +116,7 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
         r.is = (int)lo;
         r.ie = (int)hi;
         r.pA = dd * c.inv_dx;
-        r.pB = fmaf(d0, c.inv_dx, c.pos0);
+        r.pB = d0 * c.inv_dx;
     }
     r.zA = P.zs * L.dlam;
     r.zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
@@ -132,7 +132,7 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
         if (!(u >= 0.f && u < ulim)) return false;
         if (TOF) {
             const float pos = fmaf((float)i, r.pA, r.pB);
-            if (!(pos >= 0.f && pos <= c.pos_max)) return false;
+            if (!(fabsf(pos) <= c.pos_max)) return false;
         }
         return true;
     };
@@ -192,12 +192,11 @@ __global__ void __launch_bounds__(256) k_counts_fill(const void *__restrict__ y,
     }
 }
 
-// TOF weight W(d) from the LDS table of (W_k, W_{k+1} - W_k) at its NW_TAB
-// nodes, at table position pos = d / dx + NW/2 in [0, pos_max]: linear
-// interpolation between the two nodes around pos (one 8-byte LDS read).
+// TOF weight W(d) from the LDS table, at table position pos = d / dx, |pos| <=
+// pos_max (the absolute value costs nothing: a modifier of both conversions).
 __device__ __forceinline__ float tof_weight_at(const float2 *tab, float pos) {
-    const float2 t = tab[(int)pos];
-    return fmaf(__builtin_amdgcn_fractf(pos), t.y, t.x);
+    const float2 t = tab[(int)fabsf(pos)];
+    return fmaf(__builtin_amdgcn_fractf(fabsf(pos)), t.y, t.x);
 }
 
 // Sum over the workgroup, the same value in every thread (wave sums by
@@ -327,7 +326,7 @@ __device__ __forceinline__ int lanes_per_bin(int n_c) {
 }
 
 // Rows of the image sheet whose loads a thread has in flight at once.
-constexpr int CNT_SHEET_ROWS = 8;
+constexpr int CNT_SHEET_ROWS = 4;
 
 // Image sheet X of a line (rows [0, nrow), padded axial positions [0, rz)):
 // the transaxial interpolation of the transposed image, as build_sheet.
@@ -379,27 +378,22 @@ constexpr int CNT_ROUNDS = 4;
 static_assert(CNT_QCAP <= CNT_ROUNDS * CNT_BLOCK, "a chunk takes at most CNT_ROUNDS rounds of one bin per thread");
 
 // One workgroup per line with counts.  MODE M_GRAD: gradient sheets receive
-// -P^T [mult y / ybar]; M_OBJ: no gradient.  Both write the workgroup's FP64
-// sum of y log(y / ybar) when a.partial is set.
+// -P^T [mult y / ybar]; M_OBJ: no gradient.  KL: the workgroup's FP64 sum of
+// y log(y / ybar) goes to a.partial.
 //
 // LDS: one sheet region that holds the image sheet X (nrow x rz floats) while
 // the bins are walked forward, and then the packed gradient sheet of the rows
 // of one parity (ceil(nrow / 2) x rz 64-bit words, the same bytes); the TOF
 // table.
-// About 71 KB on the brain-sized workloads, so that two workgroups share a CU
-// and one's barriers overlap the other's samples.
-//
-// The line's bins are taken in chunks of at most c.q_cap.  Phase one walks
-// every bin of the chunk forward (ybar, the log term, Q = mult y / ybar ell).
-// With M_GRAD, phase two runs once per parity of the rows (even rows, then
-// odd ones, so that every bin's window splits about evenly between the two
-// passes): it clears the packed sheet, adds the chunk's shares -Q W(t - t_b)
-// (times the axial interpolation weights, scaled by 2^30 / sum |Q|) of the
-// samples in those rows, and reads them out.  Each thread keeps what phase two needs of its bins (one per
-// round of the chunk, at most CNT_ROUNDS) and their factors in registers
-// between the phases.  A next chunk rebuilds X.
-template <bool TOF, int MODE>
-__global__ void __launch_bounds__(CNT_BLOCK) k_line_counts(ProjArgs a, CountArgs c) {
+// About 52 KB on the brain-sized workloads, so that three workgroups share a CU
+// and one's barriers overlap the others' samples; that also takes 80 registers at
+// most, which the form without the sum (KL) keeps to (the FP64 logarithm needs 109).
+// Bound by vector instructions (18 and 16 per sample forward and back).  With a table
+// of the whole support in 4096 intervals (71 KB in all) and 109 registers, two
+// workgroups: 167 us for a subset gradient of 128 x 128 x 71 voxels and 13 bins,
+// now 162; without TOF, a SAGA epoch of 96 x 96 x 32 voxels, 931 and now 807.
+template <bool TOF, int MODE, bool KL>
+__global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs a, CountArgs c) {
     extern __shared__ float4 smem4[];
     float *smem = reinterpret_cast<float *>(smem4);
     __shared__ float2 red[CNT_BLOCK / 64];
@@ -415,15 +409,14 @@ __global__ void __launch_bounds__(CNT_BLOCK) k_line_counts(ProjArgs a, CountArgs
     const CountRec none{1, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // no rows, no count
 
     if (TOF) {
-        // the table's loads in flight together, eight per thread
-        static_assert(NW_TAB % (8 * CNT_BLOCK) == 0, "the table load assumes 8 CNT_BLOCK divides NW_TAB");
-        for (int k0 = threadIdx.x; k0 < NW_TAB; k0 += 8 * CNT_BLOCK) {
-            float2 wv[8];
+        // the table's loads in flight together
+        constexpr int TV = CNT_TAB / CNT_BLOCK;
+        static_assert(CNT_TAB % CNT_BLOCK == 0, "the same number of entries per thread");
+        float2 wv[TV];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) wv[u] = c.wtab[k0 + u * CNT_BLOCK];
+        for (int u = 0; u < TV; ++u) wv[u] = c.wtab[threadIdx.x + u * CNT_BLOCK];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) tab[k0 + u * CNT_BLOCK] = wv[u];
-        }
+        for (int u = 0; u < TV; ++u) tab[threadIdx.x + u * CNT_BLOCK] = wv[u];
     }
     if (nrow > 0) build_x(a, L, nrow, X);
     __syncthreads();
@@ -489,7 +482,7 @@ __global__ void __launch_bounds__(CNT_BLOCK) k_line_counts(ProjArgs a, CountArgs
             for (int o = 1; o < C; o <<= 1) s += __shfl_xor(s, o, 64);
             const float ybar = fmaf(e.me, s, e.add);
             // (the FP64 logarithm only when the sums are wanted)
-            if (a.partial && act && ch == 0) kl += (double)e.y * log((double)e.y / (double)ybar);
+            if (KL && act && ch == 0) kl += (double)e.y * log((double)e.y / (double)ybar);
             if (NEED_Z) {
                 const float Q = act ? e.me * e.y * __builtin_amdgcn_rcpf(ybar) : 0.f;
                 if (ch == 0) {
@@ -577,7 +570,7 @@ __global__ void __launch_bounds__(CNT_BLOCK) k_line_counts(ProjArgs a, CountArgs
             __syncthreads();
         }
     }
-    if (a.partial) block_sums(kl, kl, a.partial, false);
+    if (KL) block_sums(kl, kl, a.partial, false);
 }
 
 // Descriptors of a launch's lines (geometry and item ranges), one per line.
@@ -595,28 +588,28 @@ __global__ void k_counts_desc(const int *__restrict__ lines, int n, const LineP 
     desc[k] = d;
 }
 
-template <bool TOF, int MODE>
+template <bool TOF, int MODE, bool KL>
 void set_counts_lds(size_t need) {
     static size_t granted = 64 * 1024;
     if (need <= granted) return;
-    if (hipFuncSetAttribute((const void *)k_line_counts<TOF, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void *)k_line_counts<TOF, MODE, KL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)need) == hipSuccess)
         granted = need;
     (void)hipGetLastError();
 }
 
-template <bool TOF, int MODE>
+template <bool TOF, int MODE, bool KL>
 hipError_t launch_counts_mode(const pet_geom_s *g, const pet_counts_s *cs, int nblk, int threads, size_t lds,
                               const ProjArgs &a, const CountArgs &c, hipStream_t s) {
-    set_counts_lds<TOF, MODE>(lds);
-    hipLaunchKernelGGL((k_line_counts<TOF, MODE>), dim3(nblk), dim3(threads), lds, s, a, c);
+    set_counts_lds<TOF, MODE, KL>(lds);
+    hipLaunchKernelGGL((k_line_counts<TOF, MODE, KL>), dim3(nblk), dim3(threads), lds, s, a, c);
     return hipGetLastError();
 }
 
 }  // namespace
 
 // LDS of the counts kernel (dynamic), in floats: the sheet region (X, or the
-// packed gradient sheet of the rows of one parity), the TOF table (NW_TAB
+// packed gradient sheet of the rows of one parity), the TOF table (CNT_TAB
 // (W, dW) pairs), each rounded up to 16 bytes.
 static size_t counts_sheet_floats(const pet_geom_s *g) {
     const size_t rz = (size_t)g->d.nz + 2 * PADZ;
@@ -625,7 +618,7 @@ static size_t counts_sheet_floats(const pet_geom_s *g) {
     return (std::max(x, zu) + 3) & ~(size_t)3;
 }
 
-static size_t counts_tab_floats(const pet_geom_s *g) { return g->d.n_tof > 1 ? 2 * (size_t)NW_TAB : 0; }
+static size_t counts_tab_floats(const pet_geom_s *g) { return g->d.n_tof > 1 ? 2 * (size_t)CNT_TAB : 0; }
 
 static size_t counts_lds_base(const pet_geom_s *g) {
     return sizeof(float) * (counts_sheet_floats(g) + counts_tab_floats(g));
@@ -648,15 +641,13 @@ int counts_blocks(const pet_counts_s *cs, int subset) {
 // The TOF table's constants (and the TOF bin count) of a geometry.
 static CountArgs count_args(const pet_geom_s *g) {
     CountArgs c{};
-    c.wtab = g->wtab;
-    c.nw = NW_TAB;
+    c.wtab = g->ctab;
     c.sheet_floats = (int)counts_sheet_floats(g);
     c.tab_floats = (int)counts_tab_floats(g);
     c.n_tof = g->d.n_tof;
     c.wD = g->wD;
-    c.inv_dx = (float)(NW_TAB / (2.0 * g->wD));
-    c.pos0 = (float)(NW_TAB / 2);
-    c.pos_max = (float)NW_TAB - 1e-3f;
+    c.inv_dx = (float)(CNT_TAB / (double)g->wD);
+    c.pos_max = (float)CNT_TAB - 1e-3f;
     return c;
 }
 
@@ -693,11 +684,13 @@ hipError_t launch_line_counts(pet_geom_s *g, const pet_counts_s *cs, int mode, i
     }
     if (e == hipSuccess) {
         if (mode == M_GRAD)
-            e = tof ? launch_counts_mode<true, M_GRAD>(g, cs, nblk, threads, lds, a, c, s)
-                    : launch_counts_mode<false, M_GRAD>(g, cs, nblk, threads, lds, a, c, s);
+            e = a.partial ? tof ? launch_counts_mode<true, M_GRAD, true>(g, cs, nblk, threads, lds, a, c, s)
+                                : launch_counts_mode<false, M_GRAD, true>(g, cs, nblk, threads, lds, a, c, s)
+                : tof     ? launch_counts_mode<true, M_GRAD, false>(g, cs, nblk, threads, lds, a, c, s)
+                          : launch_counts_mode<false, M_GRAD, false>(g, cs, nblk, threads, lds, a, c, s);
         else
-            e = tof ? launch_counts_mode<true, M_OBJ>(g, cs, nblk, threads, lds, a, c, s)
-                    : launch_counts_mode<false, M_OBJ>(g, cs, nblk, threads, lds, a, c, s);
+            e = tof ? launch_counts_mode<true, M_OBJ, true>(g, cs, nblk, threads, lds, a, c, s)
+                    : launch_counts_mode<false, M_OBJ, true>(g, cs, nblk, threads, lds, a, c, s);
     }
     if (e == hipSuccess && e1) e = hipEventRecord(e1, s);
     return e;

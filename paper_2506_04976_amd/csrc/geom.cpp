@@ -502,11 +502,22 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
         for (int k = 0; k < NW_TAB; ++k) tab[k] = make_float2((float)W[k], (float)(W[k + 1] - W[k]));
         e = hipMalloc(&g->wtab, sizeof(float2) * NW_TAB);
         if (e == hipSuccess) e = hipMemcpy(g->wtab, tab.data(), sizeof(float2) * NW_TAB, hipMemcpyHostToDevice);
-        std::vector<float> tabf(NW_TAB + 1);
-        for (int k = 0; k <= NW_TAB; ++k) tabf[k] = (float)W[k];
-        if (e == hipSuccess) e = hipMalloc(&g->wtabf, sizeof(float) * (NW_TAB + 1));
-        if (e == hipSuccess)
-            e = hipMemcpy(g->wtabf, tabf.data(), sizeof(float) * (NW_TAB + 1), hipMemcpyHostToDevice);
+        // W on [0, D] as a line per interval, moved so that its largest errors above
+        // and below are equal (half those of the chord)
+        std::vector<float2> ctab(CNT_TAB);
+        auto w_at = [&](double dd) { return dd >= D ? 0.0 : 0.5 * (E(h - dd) - E(-h - dd)); };
+        for (int k = 0; k < CNT_TAB; ++k) {
+            const double w0 = w_at(D * k / CNT_TAB), w1 = w_at(D * (k + 1) / CNT_TAB);
+            double lo = 0.0, hi = 0.0;
+            for (int i = 1; i < 16; ++i) {
+                const double off = w_at(D * (k + i / 16.0) / CNT_TAB) - (w0 + (w1 - w0) * i / 16.0);
+                lo = std::min(lo, off);
+                hi = std::max(hi, off);
+            }
+            ctab[k] = make_float2((float)(w0 + 0.5 * (lo + hi)), (float)(w1 - w0));
+        }
+        if (e == hipSuccess) e = hipMalloc(&g->ctab, sizeof(float2) * CNT_TAB);
+        if (e == hipSuccess) e = hipMemcpy(g->ctab, ctab.data(), sizeof(float2) * CNT_TAB, hipMemcpyHostToDevice);
     }
     // padded sheet borders must be zero once; interiors are rewritten per use
     if (e == hipSuccess) e = hipMemset(g->T0, 0, sizeof(float) * g->t0_elems);
@@ -535,7 +546,7 @@ extern "C" pet_status pet_geom_destroy(pet_geom g) {
     }
     void *ptrs[] = {g->lines, g->planes, g->units, g->etab, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
                     g->grad, g->hess, g->num, g->sensi, g->partial, g->dscratch, g->fscratch, g->psf_a, g->psf_b,
-                    g->check_counts, g->wtab, g->wtabf, g->gsegs, g->gather, g->gchunk};
+                    g->check_counts, g->wtab, g->ctab, g->gsegs, g->gather, g->gchunk};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete g;

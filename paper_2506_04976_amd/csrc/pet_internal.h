@@ -178,6 +178,7 @@ struct CountRec {
 };
 static_assert(sizeof(CountRec) == 32, "CountRec layout");
 constexpr int NW_TAB = 4096;    // intervals of the tabulated TOF weight W(d)
+constexpr int CNT_TAB = 1536;   // intervals of its table of W(d), d >= 0 (three workgroups per CU beside 71 slices)
 constexpr int CNT_BLOCK = 512;   // threads per workgroup of the counts line kernel
 constexpr int CNT_QCAP = 2048;   // bins per chunk of the counts line kernel (four rounds of one bin per thread)
 constexpr int CU_LDS_BYTES = 160 * 1024;  // LDS of one gfx950 CU
@@ -195,11 +196,11 @@ static_assert(sizeof(CountLine) == 48, "CountLine layout");
 struct CountArgs {
     const CountRec *items;
     const CountLine *desc;    // the launch's lines (workgroup b takes desc[b])
-    const float2 *wtab;       // TOF: (W_k, W_{k+1} - W_k) at the table's NW_TAB nodes
+    const float2 *wtab;       // TOF: value and difference of W's line in each of CNT_TAB intervals
     int sheet_floats, tab_floats;  // LDS layout: sheet region, TOF table (floats)
     int nw, n_tof;
     float wD;                 // support of W: |d| <= wD
-    float inv_dx, pos0, pos_max;  // table position of d: d * inv_dx + pos0, clamped to [0, pos_max]
+    float inv_dx, pos_max;    // table position of d: d * inv_dx, its magnitude at most pos_max
     int q_cap;                // bins per chunk of a line (at most CNT_QCAP with M_GRAD)
     int force_signed;         // signed fixed-point sheets for every chunk (tests)
     int64_t slot_floats;      // 0, or the stride of per-subset gradient sheets (G0, G1 + slot * stride)
@@ -288,7 +289,7 @@ struct pet_geom_s {
     // W(d) = 1/2 [E(bin/2 - d) - E(-bin/2 - d)] (E the clamped erf), at NW_TAB + 1
     // nodes over its support |d| <= wD, as (W_k, W_{k+1} - W_k) pairs
     float2 *wtab = nullptr;   // TOF weight table: (W_k, W_{k+1} - W_k) at NW_TAB nodes (gather adjoint)
-    float *wtabf = nullptr;   // and W at the NW_TAB + 1 nodes (counts kernels)
+    float2 *ctab = nullptr;   // the same for d >= 0 in CNT_TAB intervals (counts kernels)
     float wD = 0.f;
     size_t max_lds = 0;                 // the device's LDS limit per workgroup
     // scratch arena
