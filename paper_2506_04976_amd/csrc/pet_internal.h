@@ -275,7 +275,7 @@ struct pet_geom_s {
     int rows_max = 0;
     pet::TofUnit *units = nullptr;      // TOF line kernels
     float4 *etab = nullptr;
-    int n_units = 0, bins_blk = 0, q_units = 0, unit_floats = 0, n_etab = 0, x_stride = 0;
+    int n_units = 0, bins_blk = 0, q_units = 0, q_units_back = 0, unit_floats = 0, n_etab = 0, x_stride = 0;
     double e_scale = 0.0;
     int nt_threads = pet::NT_BLOCK;     // non-TOF line kernel: threads per workgroup
     int *views_dev = nullptr;           // [n_subsets + 1][max(max_views, n_views)]; last row: all views

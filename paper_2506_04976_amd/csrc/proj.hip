@@ -1158,9 +1158,10 @@ size_t nt_lds(const pet_geom_s *g) {
 }
 
 template <int MODE, int MB, int NZB, bool MANY, bool KL>
-hipError_t launch_tof(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
+hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s) {
     const bool x = MODE != M_BACK, z = MODE != M_FWD && MODE != M_OBJ;
-    const size_t lds = tof_lds_bytes(g, x, z ? g->q_units : MODE == M_OBJ ? TOF_BLOCK / 64 : 0, z ? TOF_BLOCK / 64 : 0);
+    if (MODE == M_BACK) a.q_units = g->q_units_back;
+    const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : MODE == M_OBJ ? TOF_BLOCK / 64 : 0, z ? TOF_BLOCK / 64 : 0);
     static size_t granted = 64 * 1024;
     if (lds > granted) {
         hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY, KL>,
