@@ -183,6 +183,22 @@ struct RdpArgs {
     const double *tau_bb;
 };
 
+// One neighbour's terms: with d = x_i - x_j, phi = x_i + x_j + eps + gamma |d|,
+// c = 2 x_j + eps and a = d / phi, b = c / phi, those of the
+// sums below are w a (1 + b) (for phi + c over phi), w b^2 / phi (doubled at the
+// end) and w a d: three products fewer than with 1 / phi^2 and 1 / phi^3.
+template <int F>
+__device__ __forceinline__ void rdp_pair(float w, float xi, float xj, float xe, float gamma, float eps, bool in,
+                                         float &g, float &h, float &sv) {
+    const float d = xi - xj;
+    const float phi = fmaf(gamma, fabsf(d), xe + xj);
+    const float r = in ? __builtin_amdgcn_rcpf(phi) : 0.f;
+    const float a = d * r, b = fmaf(2.f, xj, eps) * r;  // (c without the cancellation of s + eps - d)
+    g = fmaf(w, fmaf(a, b, a), g);
+    if (F & (R_HESS_OUT | R_PRECOND)) h = fmaf(w, b * b * r, h);
+    if (F & R_VALUE) sv = fmaf(w, a * d, sv);
+}
+
 // RDP sums of one voxel over its 26 neighbours (eq. (rdp); derivatives as in
 // Appendix A): with d = x_i - x_j, phi = x_i + x_j + gamma |d| + eps and
 // c = 2 x_j + eps (= s - d + eps, s = x_i + x_j),
@@ -223,17 +239,11 @@ __device__ __forceinline__ void rdp_sums(const RdpArgs &a, int v, int ix, int iy
                 const float xj = a.x[u];
                 float wk = a.w.w[dz * 9 + dy * 3 + dx];
                 if (KAPPA) wk *= ki * a.kappa[u];
-                const float d = xi - xj;
-                const float phi = fmaf(a.gamma, fabsf(d), xe + xj);
-                const float r = ozy && ox[dx] ? __builtin_amdgcn_rcpf(phi) : 0.f;
-                const float c = fmaf(2.f, xj, a.eps);
-                const float r2 = r * r;
-                g = fmaf(wk * d * (phi + c), r2, g);
-                if (F & (R_HESS_OUT | R_PRECOND)) h = fmaf(2.f * wk * c * c, r2 * r, h);
-                if (F & R_VALUE) sv = fmaf(wk * d * d, r, sv);
+                rdp_pair<F>(wk, xi, xj, xe, a.gamma, a.eps, ozy && ox[dx], g, h, sv);
             }
         }
     }
+    h *= 2.f;
 }
 
 // What the flags ask for at one voxel once its RDP sums are known (gradient,
@@ -472,16 +482,11 @@ __global__ void __launch_bounds__(STEP_BLOCK) k_step_tile(RdpArgs a, float *__re
                     const bool in = ozy && ix + dx - 1 >= 0 && ix + dx - 1 < nx;
                     const float xj = halo[(dy * hz + z + dz) * hx + xx + dx];
                     const float wk = a.w.w[dz * 9 + dy * 3 + dx];
-                    const float d = xi - xj;
-                    const float phi = fmaf(a.gamma, fabsf(d), xe + xj);
-                    const float r = in ? __builtin_amdgcn_rcpf(phi) : 0.f;
-                    const float c = fmaf(2.f, xj, a.eps);
-                    const float r2 = r * r;
-                    g = fmaf(wk * d * (phi + c), r2, g);
-                    if (F & (R_HESS_OUT | R_PRECOND)) h = fmaf(2.f * wk * c * c, r2 * r, h);
+                    rdp_pair<F>(wk, xi, xj, xe, a.gamma, a.eps, in, g, h, sv);
                 }
             }
         }
+        h *= 2.f;
         (void)nxy;
         double val = 0.0, pq = 0.0, qdq = 0.0;
         const float gi = reads_gi<F>() ? tile[z * (TT + 1) + xx] : 0.f;
