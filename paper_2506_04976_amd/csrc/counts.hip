@@ -275,7 +275,7 @@ __device__ __forceinline__ float packed_cell_value(const unsigned long long *Zu,
         // nonnegative shares: B <= A in every cell (each sample's rounded
         // f q <= its rounded q), so A - B + B' < 2^32 in 32-bit arithmetic
         const unsigned long long w = Zu[e];
-        const uint32_t Bp = zp > 0 ? (uint32_t)(Zu[e - 1] >> 32) : 0u;
+        const uint32_t Bq = (uint32_t)(Zu[e - (zp > 0 ? 1 : 0)] >> 32), Bp = zp > 0 ? Bq : 0u;
         const uint32_t V = (uint32_t)w - (uint32_t)(w >> 32) + Bp;
         return finite ? -(float)V * inv_scale : __builtin_nanf("");
     }
@@ -290,28 +290,34 @@ __device__ __forceinline__ float packed_cell_value(const unsigned long long *Zu,
 // of the line in Zu row k, k < nh), spread over the two transaxial neighbours
 // like the FP64 sheet of the dense kernels.  A line whose bound is not finite
 // (a bin with ybar = 0) adds NaN to every cell it covers.
+// rows: the transposed rows' offsets and fractions (sheet_row), once per line.
 template <bool SIGNED>
 __device__ __forceinline__ void scatter_rows_parity(const ProjArgs &a, const LineP &L, int par, int nh,
-                                                    const unsigned long long *Zu, float inv_scale, bool finite,
-                                                    int64_t g_off) {
+                                                    const unsigned long long *Zu, const SheetRow *rows,
+                                                    float inv_scale, bool finite, int64_t g_off) {
     const int rz = a.rz;
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
-    const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
+    auto spread = [&](const SheetRow &row, int zp, float val) {
+        if (val != 0.f) spread_cell(Gout, row, zp, rz, val);
+    };
     if (rz <= (int)blockDim.x) {
         const SheetWalk w = sheet_walk(rz, threadIdx.x);
         if (!w.on) return;
-        for (int k = w.r0; k < nh; k += w.R) {
-            const float val = packed_cell_value<SIGNED>(Zu, k * rz + w.zp, w.zp, inv_scale, finite);
-            if (val == 0.f) continue;
-            spread_cell(Gout, sheet_row(L, L.i_lo + par + 2 * k, other_stride, rz), w.zp, rz, val);
+        // (two cells' LDS reads in flight together)
+        int k = w.r0;
+        for (; k + w.R < nh; k += 2 * w.R) {
+            const SheetRow s0 = rows[par + 2 * k], s1 = rows[par + 2 * (k + w.R)];
+            const float v0 = packed_cell_value<SIGNED>(Zu, k * rz + w.zp, w.zp, inv_scale, finite);
+            const float v1 = packed_cell_value<SIGNED>(Zu, (k + w.R) * rz + w.zp, w.zp, inv_scale, finite);
+            spread(s0, w.zp, v0);
+            spread(s1, w.zp, v1);
         }
+        if (k < nh) spread(rows[par + 2 * k], w.zp, packed_cell_value<SIGNED>(Zu, k * rz + w.zp, w.zp, inv_scale, finite));
     } else {
         for (int e = threadIdx.x; e < nh * rz; e += blockDim.x) {
             const int k = e / rz;
             const int zp = e - k * rz;
-            const float val = packed_cell_value<SIGNED>(Zu, e, zp, inv_scale, finite);
-            if (val == 0.f) continue;
-            spread_cell(Gout, sheet_row(L, L.i_lo + par + 2 * k, other_stride, rz), zp, rz, val);
+            spread(rows[par + 2 * k], zp, packed_cell_value<SIGNED>(Zu, e, zp, inv_scale, finite));
         }
     }
 }
@@ -332,13 +338,15 @@ constexpr int CNT_SHEET_ROWS = 4;
 // the transaxial interpolation of the transposed image, as build_sheet.
 __device__ __forceinline__ void build_x(const ProjArgs &a, const LineP &L, int nrow, float *X) {
     const int rz = a.rz;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (nothing of it is kept for the next chunk's rebuild)
     if (rz > (int)blockDim.x) {
-        build_sheet(a, L, nrow, X, rz, threadIdx.x);
+        build_sheet(a, L, nrow, X, rz, tid);
         return;
     }
     const float *T = L.axis ? a.T1 : a.T0;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
-    const SheetWalk sw = sheet_walk(rz, threadIdx.x);
+    const SheetWalk sw = sheet_walk(rz, tid);
     if (!sw.on) return;
     for (int rb = sw.r0; rb < nrow; rb += CNT_SHEET_ROWS * sw.R) {
         float t0[CNT_SHEET_ROWS], t1[CNT_SHEET_ROWS], tf[CNT_SHEET_ROWS];
@@ -388,10 +396,11 @@ static_assert(CNT_QCAP <= CNT_ROUNDS * CNT_BLOCK, "a chunk takes at most CNT_ROU
 // About 52 KB on the brain-sized workloads, so that three workgroups share a CU
 // and one's barriers overlap the others' samples; that also takes 80 registers at
 // most, which the form without the sum (KL) keeps to (the FP64 logarithm needs 109).
-// Bound by vector instructions (18 and 16 per sample forward and back).  With a table
-// of the whole support in 4096 intervals (71 KB in all) and 109 registers, two
-// workgroups: 167 us for a subset gradient of 128 x 128 x 71 voxels and 13 bins,
-// now 162; without TOF, a SAGA epoch of 96 x 96 x 32 voxels, 931 and now 807.
+// Bound by vector instructions (18 and 16 per sample forward and back, the rest in
+// the sheets).  With a table of the whole support in 4096 intervals (71 KB in all) and
+// 109 registers, two workgroups: 167 us for a subset gradient of 128 x 128 x 71 voxels
+// and 13 bins, with three 162, with the readout's rows from a table 154; without TOF,
+// a SAGA epoch of 96 x 96 x 32 voxels, 931 and now 805.
 template <bool TOF, int MODE, bool KL>
 __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs a, CountArgs c) {
     extern __shared__ float4 smem4[];
@@ -405,6 +414,7 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
     float *X = smem;
     unsigned long long *Zu = reinterpret_cast<unsigned long long *>(smem);  // (X's bytes, after phase one)
     float2 *tab = reinterpret_cast<float2 *>(smem + c.sheet_floats);
+    SheetRow *rows = reinterpret_cast<SheetRow *>(smem + c.sheet_floats + c.tab_floats);
     const int64_t i0 = desc.i0, i1 = desc.i0 + desc.n;
     const CountRec none{1, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // no rows, no count
 
@@ -418,6 +428,9 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
 #pragma unroll
         for (int u = 0; u < TV; ++u) tab[threadIdx.x + u * CNT_BLOCK] = wv[u];
     }
+    if (NEED_Z)
+        for (int r = threadIdx.x; r < nrow; r += blockDim.x)
+            rows[r] = sheet_row(L, L.i_lo + r, ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz, rz);
     if (nrow > 0) build_x(a, L, nrow, X);
     __syncthreads();
 
@@ -563,9 +576,9 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
             __syncthreads();
             const int64_t g_off = (int64_t)desc.slot * c.slot_floats;
             if (sgn)
-                scatter_rows_parity<true>(a, L, par, nh, Zu, finite ? 1.f / scale : 0.f, finite, g_off);
+                scatter_rows_parity<true>(a, L, par, nh, Zu, rows, finite ? 1.f / scale : 0.f, finite, g_off);
             else
-                scatter_rows_parity<false>(a, L, par, nh, Zu, finite ? 1.f / scale : 0.f, finite, g_off);
+                scatter_rows_parity<false>(a, L, par, nh, Zu, rows, finite ? 1.f / scale : 0.f, finite, g_off);
             // (before the next pass clears the sheet, or the next chunk's X)
             __syncthreads();
         }
@@ -621,7 +634,7 @@ static size_t counts_sheet_floats(const pet_geom_s *g) {
 static size_t counts_tab_floats(const pet_geom_s *g) { return g->d.n_tof > 1 ? 2 * (size_t)CNT_TAB : 0; }
 
 static size_t counts_lds_base(const pet_geom_s *g) {
-    return sizeof(float) * (counts_sheet_floats(g) + counts_tab_floats(g));
+    return sizeof(float) * (counts_sheet_floats(g) + counts_tab_floats(g)) + sizeof(SheetRow) * (size_t)g->rows_max;
 }
 
 // Bins per chunk with M_GRAD: CNT_QCAP (their factors live in registers), or
