@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
 // 6 to 8 per sample), then the matrix cores (151 us of the 784) and the data's
 // loads.  A wave per segment with FP64 LDS adds per sample took 1026 us for it;
 // 945 -> 612 us with 161 x 161 x 33 voxels and 25 bins, and a forward projection
-// of 96 x 96 x 32 voxels 694 -> 255 us.
+// of 96 x 96 x 32 voxels 694 -> 225 us.
 //
 // Lane layouts of the 16x16x4 instruction: A[m][k] in lane 16 k + m, B[k][n] in
 // lane 16 k + n, D[m][n] in register m mod 4 of lane 16 (m / 4) + n.
@@ -1037,7 +1037,7 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
 
 // One line per workgroup, in the order a.order (longest first).
 template <int MODE, int MB, int NZB, bool MANY, bool KL>
-__global__ void __launch_bounds__(TOF_BLOCK, 4) k_line_tof(ProjArgs a) {
+__global__ void __launch_bounds__(TOF_BLOCK, MODE == M_FWD && MB == 1 ? 8 : 4) k_line_tof(ProjArgs a) {
     extern __shared__ float4 smem4[];
     double kl = 0.0;  // (not live through the body)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1161,7 +1161,13 @@ template <int MODE, int MB, int NZB, bool MANY, bool KL>
 hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s) {
     const bool x = MODE != M_BACK, z = MODE != M_FWD && MODE != M_OBJ;
     if (MODE == M_BACK) a.q_units = g->q_units_back;
-    const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : MODE == M_OBJ ? TOF_BLOCK / 64 : 0, z ? TOF_BLOCK / 64 : 0);
+    // Without an adjoint a wave has nothing but units to do: no more waves than units
+    // (four at least, for the image sheet), and more workgroups on a CU instead: five
+    // units, all views, 96 x 96 x 32, 255 -> 225 us with 64 registers.  Fewer waves for
+    // even rounds of many units are slower (41 on 7 waves 367 us against 347 on 8; 17
+    // on 6: 173 against 162): less is in flight.
+    const int waves = z ? TOF_BLOCK / 64 : std::min(TOF_BLOCK / 64, std::max(4, g->n_units));
+    const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : MODE == M_OBJ ? waves : 0, z ? waves : 0);
     static size_t granted = 64 * 1024;
     if (lds > granted) {
         hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY, KL>,
@@ -1169,7 +1175,7 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
         if (e == hipSuccess) granted = lds;
         (void)hipGetLastError();
     }
-    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY, KL>), grid, dim3(TOF_BLOCK), lds, s, a);
+    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY, KL>), grid, dim3(64 * waves), lds, s, a);
     return hipGetLastError();
 }
 
