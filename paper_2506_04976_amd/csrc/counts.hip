@@ -132,7 +132,7 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
         if (!(u >= 0.f && u < ulim)) return false;
         if (TOF) {
             const float pos = fmaf((float)i, r.pA, r.pB);
-            if (!(fabsf(pos) <= c.pos_max)) return false;
+            if (!(pos >= -c.pos_max && pos <= c.pos_max)) return false;
         }
         return true;
     };
