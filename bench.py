@@ -36,8 +36,8 @@ PEAK_HBM_GBPS = 8000.0
 # calibrated FETCH_SIZE / WRITE_SIZE counter runs, and its VALU issue fraction
 # (SQ counters), valid for the kernel source with this hash only (reported as
 # null otherwise).
-MEASURED_TRAFFIC = {"c2_tof": (203.3e6, "517351a8e0f8bb05")}
-MEASURED_VALU = {"c2_tof": (0.80, "517351a8e0f8bb05")}
+MEASURED_TRAFFIC = {"c2_tof": (203.3e6, "bafd195b0bc06ac0")}
+MEASURED_VALU = {"c2_tof": (0.83, "bafd195b0bc06ac0")}
 
 
 def log(msg):
