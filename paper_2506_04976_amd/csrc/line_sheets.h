@@ -148,8 +148,10 @@ __device__ __forceinline__ float gather_two(const float *Qs, const GatherSeg &G,
 // planes of weight 0 left out.
 __device__ __forceinline__ float gather_many(const float *Qs, const GatherSeg &G, float t, float kappa) {
     const float h = 1.f / kappa;
-    // (clamped to the planes before the conversion; one plane of margin)
-    const float lo = fminf(fmaxf(floorf(t - h), G.lo + 1.f), G.hi), hi = fmaxf(fminf(ceilf(t + h), G.hi - 1.f), G.lo);
+    // (clamped to the planes before the conversion; the margin covers the rounding of
+    // t, a whole plane on both sides would double the planes of kappa just below 1)
+    const float lo = fminf(fmaxf(ceilf(t - h - 1e-3f), G.lo + 1.f), G.hi);
+    const float hi = fmaxf(fminf(floorf(t + h + 1e-3f), G.hi - 1.f), G.lo);
     float s = 0.f;
     for (int p = (int)lo; p <= (int)hi; ++p) {
         const float w = fmaf(-kappa, fabsf(t - (float)p), 1.f);
