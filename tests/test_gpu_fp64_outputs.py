@@ -1,0 +1,93 @@
+"""FP64 outputs (the prior's value, Kullback-Leibler sums, objectives) against
+recorded values.
+
+Each is an FP64 sum of terms computed in 32 bits in a fixed order, so that the
+same inputs give the same value: to 1e-12 of it, which leaves room for the order
+of the FP64 sum (about 1e-15) and for nothing else.  The recorded values come
+from this library's sequential form of each sum (samples of a LOR one after the
+other; w d d / phi of a pair of voxels), on inputs drawn with numpy's default
+generator.  An evaluation of the terms in another order or with other roundings
+moves the values by 1e-11 to 1e-8 on images of this size.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from synth import configs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+GEOMETRIES = {
+    "mini_nontof": configs.get("mini_nontof"),
+    "mini_2d": configs.get("mini_2d"),
+    "slab": configs.get("mini_nontof", nx=33, ny=30, radius=140.0, nz=26, vz=4.1, n_rings=27, ring_pitch=3.9, max_ring_diff=3),
+}
+
+
+class Inputs:
+    def __init__(self, name):
+        import paper_2506_04976_amd as pm
+        self.pm, self.cfg = pm, GEOMETRIES[name]
+        self.geom = pm.Geometry(self.cfg)
+        g = self.geom
+        rng = np.random.default_rng(17)
+
+        def t(a, dtype=np.float32):
+            return torch.from_numpy(a.astype(dtype)).to("cuda:0")
+
+        self.x = t(0.2 + rng.random(g.n_vox))
+        self.mult = t(0.02 * (0.5 + rng.random(g.n_lors)))
+        self.add = t(0.05 + 0.3 * rng.random(g.n_bins))
+        self.y = t(rng.integers(0, 6, g.n_bins), np.uint8)
+        self.kappa = t(0.5 + rng.random(g.n_vox))
+        self.sens = t(0.1 + rng.random(g.n_vox))
+        self.grad = torch.zeros_like(self.x)
+        self.out = torch.full((1,), -1.0, dtype=torch.float64, device="cuda:0")
+        self.prior = (pm.rdp_weights27(self.cfg["vx"], self.cfg["vy"], self.cfg["vz"]), 0.1, 2.0, 1e-3)
+
+
+def prior_value(d, kappa=False, alone=False):
+    grad, hess = (None, None) if alone else (d.grad, torch.zeros_like(d.x))
+    d.pm.pet_rdp_grad_hessdiag(d.geom, d.x, d.kappa if kappa else None, *d.prior, grad, hess, d.out)
+    return float(d.out)
+
+
+def prior_value_kappa(d):
+    return prior_value(d, kappa=True)
+
+
+def prior_value_alone(d):
+    return prior_value(d, alone=True)
+
+
+RECORDED = {
+    ("prior_value", "mini_nontof"): "0x1.8fd248fe27c56p+7",
+    ("prior_value_kappa", "mini_nontof"): "0x1.8a6e5f9411fe3p+7",
+    ("prior_value_alone", "mini_nontof"): "0x1.8fd248fe27c56p+7",
+    ("prior_value", "mini_2d"): "0x1.e7f00581c8ce0p+2",
+    ("prior_value_alone", "mini_2d"): "0x1.e7f00581c8ce0p+2",
+    ("prior_value", "slab"): "0x1.77bf798c7377ep+10",
+    ("prior_value_kappa", "slab"): "0x1.77c4d16101344p+10",
+}
+
+
+@pytest.fixture(scope="module")
+def inputs():
+    made = {}
+
+    def of(name):
+        if name not in made:
+            made[name] = Inputs(name)
+        return made[name]
+    return of
+
+
+@pytest.mark.parametrize("what,name", RECORDED)
+def test_value_as_recorded(inputs, what, name):
+    want = float.fromhex(RECORDED[what, name])
+    got = globals()[what](inputs(name))
+    print(f"\n[fp64 outputs] {what} {name}: {got:.15g}, off by {abs(got - want) / abs(want):.2e}", flush=True)
+    assert got == pytest.approx(want, rel=TOL, abs=0.0)
