@@ -509,7 +509,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
         e = hipMalloc(&g->wtab, sizeof(float2) * NW_TAB);
         if (e == hipSuccess) e = hipMemcpy(g->wtab, tab.data(), sizeof(float2) * NW_TAB, hipMemcpyHostToDevice);
         // W on [0, D] as a line per interval, moved so that its largest errors above
-        // and below are equal (half those of the chord)
+        // and below are equal (half those of the chord), but nowhere below zero: the
+        // kernels add its products to sheets that hold nonnegative numbers
         std::vector<float2> ctab(CNT_TAB);
         auto w_at = [&](double dd) { return dd >= D ? 0.0 : 0.5 * (E(h - dd) - E(-h - dd)); };
         for (int k = 0; k < CNT_TAB; ++k) {
@@ -520,7 +521,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
                 lo = std::min(lo, off);
                 hi = std::max(hi, off);
             }
-            ctab[k] = make_float2((float)(w0 + 0.5 * (lo + hi)), (float)(w1 - w0));
+            const double move = std::max(0.5 * (lo + hi), -std::min(w0, w1));
+            ctab[k] = make_float2((float)(w0 + move), (float)(w1 - w0));
         }
         if (e == hipSuccess) e = hipMalloc(&g->ctab, sizeof(float2) * CNT_TAB);
         if (e == hipSuccess) e = hipMemcpy(g->ctab, ctab.data(), sizeof(float2) * CNT_TAB, hipMemcpyHostToDevice);
