@@ -301,7 +301,10 @@ __global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
 //    registers over all units.  No LDS atomics, no sheet of doubles.
 //
 // The weight of bin b at t is 1/2 [E(hi_b - t) - E(lo_b - t)], E the clamped erf,
-// from a table of cubics in LDS (error below 1e-8, see pet_geom_create).
+// from a table of cubics in LDS: off by less than 1e-8 in exact arithmetic (see
+// pet_geom_create) and by about 6e-8 a weight in 32 bits, plus the rounding of the
+// table position times the slope there.  The forward adds the position up in parts
+// (TofPos); the adjoint forms it in one multiply-add.
 //
 // What bounds it: vector instructions (57% of the cycles of a subset gradient of
 // 128 x 128 x 71 voxels, 2204 planes and 13 bins; 12 per gathered cell and unit,
@@ -378,7 +381,7 @@ __device__ __forceinline__ void tof_fwd_rows(const ProjArgs &a, const float4 *ta
             float hi = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, lo),
                                                                               0x101 /* row_shl:1 */, 0xf, 0xf, true));
             if (full) hi = half_erf_at(tab, p + a.dpos, last);
-            w[mb] = hi - lo;
+            w[mb] = fmaxf(hi - lo, 0.f);  // (the table's rounding: -3e-8 where E is flat)
         }
     };
     const float *xr = X + (j_lo + jr) * xs;
@@ -411,7 +414,7 @@ __device__ __forceinline__ void tof_fwd_rows(const ProjArgs &a, const float4 *ta
 // Weight of bin b at row j.
 __device__ __forceinline__ float tof_weight(const ProjArgs &a, const float4 *tab, const TofPos &tp, float fj, int b) {
     const float p = fmaf((float)b, a.dpos, fmaf(fj, tp.pA, tp.pB)), last = (float)a.n_etab;
-    return half_erf_at(tab, p + a.dpos, last) - half_erf_at(tab, p, last);
+    return fmaxf(half_erf_at(tab, p + a.dpos, last) - half_erf_at(tab, p, last), 0.f);
 }
 
 // The forward sum of one bin of one LOR without the products of zero weights
@@ -585,7 +588,7 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
 #pragma unroll
             for (int q = 0; q < K; ++q) {
                 const float lo = cubic_at(c[2 * q], f[2 * q]), hi = cubic_at(c[2 * q + 1], f[2 * q + 1]);
-                w[q] = b + 4 * q < nt ? hi - lo : 0.f;
+                w[q] = b + 4 * q < nt ? fmaxf(hi - lo, 0.f) : 0.f;
             }
         }
 #pragma unroll

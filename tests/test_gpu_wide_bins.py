@@ -57,3 +57,26 @@ def test_counts_gradient_at_the_ends_of_the_support(ratio):
     err = np.linalg.norm(got.cpu().double().numpy() - want.ravel()) / np.linalg.norm(want)
     print(f"\n[wide bins] {ratio} sigma: error {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("nsigma", [2.5, 4.0, 5.0])
+@pytest.mark.parametrize("ratio", [2.0, 12.0])
+def test_dense_weights_at_the_ends_of_the_support(ratio, nsigma):
+    # an image (a sinogram) that only such samples meet: no bin's mean (no voxel) below zero
+    import paper_2506_04976_amd as pm
+    lowest = 0.0
+    for inside in (*np.linspace(5e-4, 5e-3, 40), 0.02, 0.1, 0.3, 1.0, 3.0):
+        cfg = _config(ratio, nsigma, inside)
+        geom = pm.Geometry(cfg)
+        x = torch.zeros((1, cfg["ny"], cfg["nx"]), device="cuda:0")
+        x[0, 0] = x[0, -1] = 1.0
+        out = torch.full((geom.n_bins,), float("nan"), device="cuda:0")
+        pm.pet_fwd(geom, -1, x.flatten(), None, None, out)
+        sino = torch.zeros((geom.n_bins // 3, 3), device="cuda:0")
+        sino[:, 1] = 1.0
+        img = torch.full((geom.n_vox,), float("nan"), device="cuda:0")
+        pm.pet_back(geom, -1, sino.flatten(), None, img)
+        assert bool(torch.isfinite(out).all() and torch.isfinite(img).all())
+        lowest = min(lowest, float(out.min()), float(img.min()))
+    print(f"\n[wide bins] {ratio} sigma, truncated at {nsigma}: lowest {lowest:.2e}", flush=True)
+    assert lowest == 0.0
