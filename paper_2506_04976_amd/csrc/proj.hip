@@ -163,22 +163,21 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         }
         if (NEED_Z || (NEED_X && ic == 0)) __syncthreads();
 
-        // planes in rounds of blockDim threads; the planes of a last, partial
-        // round take c threads each (c a power of two: the threads of a plane are
-        // lanes of one wave), which split its rows and add their forward sums by
-        // shuffles
-        const int np = ch.p1 - ch.p0;
-        const int full = NEED_X ? np / nb * nb : np;
-        const int rem = np - full;
-        int c = 1;
-        while (rem > 0 && c < 64 && rem * (2 * c) <= nb) c *= 2;
-        for (int base = 0; base < np; base += nb) {
-            const bool tail = base >= full;
-            const int cc = tail ? c : 1;
-            const int rank = base + (tail ? tid / c : tid);
-            const int cs = tail ? tid % c : 0;
-            const bool act = rank < np;
-            const int p = ch.p0 + (act ? rank : 0);
+        // planes in rounds of blockDim threads; the planes of the line's last,
+        // partial round take c threads each (c a power of two: the threads of a
+        // plane are lanes of one wave), which split its rows and add their forward
+        // sums by shuffles (chunks of planes do not change which planes those are,
+        // nor so their sums)
+        const int full = NEED_X ? a.n_planes / nb * nb : a.n_planes;
+        const int rem = a.n_planes - full;
+        int lg_c = 0;
+        while (rem > 0 && lg_c < 6 && (rem << (lg_c + 1)) <= nb) ++lg_c;
+        for (int base = ch.p0, end; base < ch.p1; base = end) {
+            const int lg = base >= full ? lg_c : 0, cc = 1 << lg;
+            end = min(base >= full ? ch.p1 : min(ch.p1, full), base + (nb >> lg));
+            const int cs = tid & (cc - 1);
+            const bool act = base + (tid >> lg) < end;
+            const int p = act ? base + (tid >> lg) : base;
             const PlaneP P = a.planes[p];
             const int64_t lor = (int64_t)line * a.n_planes + p;
             const float len = sqrtf(L.lt2 + P.dz2);
@@ -194,20 +193,21 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
                 // padded axial cell of sample i: u = zA i + zB = z + PADZ, clamped
                 // to [0, nz + 2] (the clamp only guards the LDS bounds; z-clipped
                 // samples lie inside), where truncation is the floor; two samples
-                // per iteration, their LDS reads in flight together
+                // per iteration, their LDS reads in flight together, added one after
+                // the other (the likelihood's FP64 sum shows the order)
                 const float zA = P.zs * L.dlam, zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
                 const float umax = (float)(a.nz + PADZ);
                 const float fc = (float)cc, fie = (float)ie;
                 const int step = cc * rz;
                 const float *xr = X + (is + cs - L.i_lo) * rz;
-                float fi = (float)(is + cs), s1 = 0.f;
+                float fi = (float)(is + cs);
                 for (; fi + fc <= fie; fi += 2.f * fc, xr += 2 * step) {
                     const float u0 = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
                     const float u1 = __builtin_amdgcn_fmed3f(fmaf(fi + fc, zA, zB), 0.f, umax);
                     const int j0 = (int)u0, j1 = (int)u1;
                     const float a0 = xr[j0], b0 = xr[j0 + 1], a1 = xr[step + j1], b1 = xr[step + j1 + 1];
                     s += fmaf(__builtin_amdgcn_fractf(u0), b0 - a0, a0);
-                    s1 += fmaf(__builtin_amdgcn_fractf(u1), b1 - a1, a1);
+                    s += fmaf(__builtin_amdgcn_fractf(u1), b1 - a1, a1);
                 }
                 if (fi <= fie) {
                     const float u = __builtin_amdgcn_fmed3f(fmaf(fi, zA, zB), 0.f, umax);
@@ -215,7 +215,6 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
                     const float x0 = xr[j], x1 = xr[j + 1];
                     s += fmaf(__builtin_amdgcn_fractf(u), x1 - x0, x0);
                 }
-                s += s1;
                 for (int o = 1; o < cc; o <<= 1) s += __shfl_xor(s, o, 64);
             }
             if (!act || cs != 0) continue;

@@ -19,7 +19,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import projector, recon
+from oracle import poisson, projector, recon
 from synth import configs, data
 
 pytestmark = pytest.mark.gpu
@@ -120,3 +120,22 @@ def test_factors_not_finite(name):
         out = torch.empty(geom.n_vox, device=dev)
         pm.pet_back(geom, -1, torch.from_numpy(sino.ravel()).to(dev), None, out)
         np.testing.assert_array_equal(~np.isfinite(out.cpu().numpy()), reach)
+
+
+def test_likelihood_and_gradient_without_it(setup):
+    # the likelihood is added up over chunks and partial rounds of planes, each
+    # LOR once; the gradient does not depend on whether it is asked for
+    pm = setup.pm
+    prob = recon.Problem(setup.cfg, setup.y, setup.add, setup.mult, beta=1.0, gamma=2.0, eps=1.0)
+    x = setup.t(setup.x)
+    args = (setup.geom, 1, x, setup.t(setup.y), setup.t(setup.add), setup.t(setup.mult))
+    with_kl, without = (torch.full_like(x, float("nan")) for _ in range(2))
+    kl = torch.full((1,), float("nan"), dtype=torch.float64, device=setup.dev)
+    pm.pet_subset_grad(*args, with_kl, kl)
+    pm.pet_subset_grad(*args, without)
+    yb = prob.ybar(setup.x.astype(np.float64), 1)
+    assert float(kl) == pytest.approx(float(np.sum(poisson.kl(yb, prob.y[1]))), rel=1e-5)
+    ref = prob.data_grad(setup.x.astype(np.float64), 1).ravel()
+    scale = np.linalg.norm(prob.back(prob.a[1] * (1 + prob.y[1] / yb), 1))
+    for g in (with_kl, without):
+        assert np.linalg.norm(g.cpu().double().numpy() - ref) / scale <= 1e-5

@@ -23,6 +23,9 @@ TOL = 1e-12
 GEOMETRIES = {
     "mini_nontof": configs.get("mini_nontof"),
     "mini_2d": configs.get("mini_2d"),
+    "planes_1100": configs.get("mini_nontof", n_rings=44, ring_pitch=0.8, max_ring_diff=14),
+    "chunks": configs.get("mini_nontof", n_views=6, n_crystals=12, n_rad=5, n_subsets=2, nx=6, ny=7, nz=400, vz=1.0,
+                          n_rings=390, ring_pitch=1.01, max_ring_diff=20),
     "slab": configs.get("mini_nontof", nx=33, ny=30, radius=140.0, nz=26, vz=4.1, n_rings=27, ring_pitch=3.9, max_ring_diff=3),
 }
 
@@ -63,6 +66,26 @@ def prior_value_alone(d):
     return prior_value(d, alone=True)
 
 
+def likelihood(d, subset=0):
+    """Of the fused subset gradient."""
+    d.pm.pet_subset_grad(d.geom, subset, d.x, d.y, d.add, d.mult, d.grad, d.out)
+    return float(d.out)
+
+
+def likelihood_all(d):
+    return likelihood(d, -1)
+
+
+def likelihood_noalloc(d):
+    d.pm.pet_subset_grad_noalloc(d.geom, 1, d.x, d.y, d.add, d.mult, d.grad, d.out)
+    return float(d.out)
+
+
+def objective(d):
+    d.pm.pet_objective(d.geom, d.x, d.y, d.add, d.mult, None, *d.prior, d.out)
+    return float(d.out)
+
+
 RECORDED = {
     ("prior_value", "mini_nontof"): "0x1.8fd248fe27c56p+7",
     ("prior_value_kappa", "mini_nontof"): "0x1.8a6e5f9411fe3p+7",
@@ -71,6 +94,17 @@ RECORDED = {
     ("prior_value_alone", "mini_2d"): "0x1.e7f00581c8ce0p+2",
     ("prior_value", "slab"): "0x1.77bf798c7377ep+10",
     ("prior_value_kappa", "slab"): "0x1.77c4d16101344p+10",
+    ("likelihood", "mini_nontof"): "0x1.1530798ab2358p+13",
+    ("likelihood_all", "mini_nontof"): "0x1.d7660906c5d64p+14",
+    ("likelihood_noalloc", "mini_nontof"): "0x1.b74ef49f9d25fp+12",
+    ("objective", "mini_nontof"): "0x1.da85ad98c225dp+14",
+    ("likelihood", "mini_2d"): "0x1.acd6979a34864p+7",
+    ("objective", "mini_2d"): "0x1.67ee54b9d35fep+9",
+    ("likelihood", "planes_1100"): "0x1.a1915e16d5356p+17",
+    ("likelihood_all", "planes_1100"): "0x1.677e10394e6cep+19",
+    ("likelihood", "slab"): "0x1.bd6534c00fa36p+14",
+    ("likelihood", "chunks"): "0x1.0411cdc49284fp+20",
+    ("objective", "chunks"): "0x1.0396d17279f67p+21",
 }
 
 
