@@ -75,6 +75,8 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.dpos = (float)(g->d.tof_bin_mm * g->e_scale);
     a.dpos_hi = high_part(a.dpos);
     a.dpos_lo = (float)((double)g->d.tof_bin_mm * g->e_scale - a.dpos_hi);
+    a.walk_order = g->walk_order;
+    a.ws = g->tof_ws;
     a.order = g->line_order + g->order_off[subset < 0 ? g->d.n_subsets : subset];
     return a;
 }

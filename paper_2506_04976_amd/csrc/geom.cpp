@@ -347,19 +347,18 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     // non-TOF: one thread per plane, in as many waves as the planes need (up to
     // 16; more resident waves hide the LDS latency of the sample loop)
     g->nt_threads = std::min(NT_BLOCK, std::max(64, (g->n_planes + 63) / 64 * 64));
-    int ws = 1;
     if (d.n_tof > 1) {
         for (const SegP &sg : gsegs)
             if (sg.np > 64) {
                 delete g;
                 return fail(PET_E_ARG, "pet_geom_create: TOF needs at most 64 planes per segment (one wave)");
             }
-        for (int s = 0; s < T.n_int; ++s) ws = std::max(ws, T.na[s]);
+        g->tof_ws = 1;
+        for (int s = 0; s < T.n_int; ++s) g->tof_ws = std::max(g->tof_ws, T.na[s]);
     }
 
-    // Largest image served: three sheets of floats in LDS and, with TOF, four
-    // to eight floats per row and the bins' support edges (the line kernels
-    // themselves need less).
+    // Largest image served: three sheets of floats in LDS and, with TOF, one wave's
+    // tables (the TOF walk; the other line kernels need less).
     int rz = d.nz + 2 * PADZ;
     size_t sheet = ((size_t)rows_max * rz + 3) & ~(size_t)3;
     int max_lds = 0;
@@ -367,8 +366,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     if (max_lds <= 0) max_lds = 64 * 1024;
     g->max_lds = (size_t)max_lds;
     size_t need = 3 * sheet * sizeof(float);
-    if (d.n_tof > 1)
-        need += (((size_t)rows_max * std::max(4, ws) + ((T.n_int + 1 + 3) & ~3) + 3) & ~(size_t)3) * sizeof(float);
+    const size_t walk_wave = d.n_tof > 1 ? walk_wave_floats(rows_max, g->tof_ws, T.n_int) * sizeof(float) : 0;
+    need += walk_wave;
     if (need > (size_t)max_lds) {
         delete g;
         return fail(PET_E_ARG, "pet_geom_create: image too large for the LDS sheets of the line kernels (" +
@@ -378,6 +377,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     // TOF line kernels: units, LDS split, table of the halved clamped erf
     std::vector<TofUnit> hunits;
     std::vector<float4> hetab;
+    std::vector<int> hwalk;
     if (d.n_tof > 1) {
         auto ring_d = [&](const SegP &sg) { return planes[sg.p0].r2 - planes[sg.p0].r1; };
         int max_np = 0;
@@ -398,6 +398,40 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
             max_np = std::max(max_np, sg.np);
         }
         g->n_units = (int)hunits.size();
+        // TOF walk: as many waves as its LDS holds (up to 16: they wait on LDS
+        // latency); wave w takes entries w, w + W, w + 2W, ... of the order.  The two
+        // halves -k and +k of a pair of single segments have the same oblique length
+        // and so the same weight table, and go to consecutive rounds of one wave, which
+        // then fills the table once (both carry the same squared axial extent).  The
+        // other units keep their relative order.
+        const int ns = g->n_units;
+        const int W = std::max(1, std::min({ns, MAX_WAVES, (int)(((size_t)max_lds - 3 * sheet * sizeof(float)) / walk_wave)}));
+        g->walk_waves = W;
+        std::vector<std::vector<int>> lists(W);
+        std::vector<int> cap(W), rest;
+        for (int w = 0; w < W; ++w) cap[w] = ns / W + (w < ns % W ? 1 : 0);
+        for (int i = 0, w = 0; i < ns; ++i) {
+            const TofUnit &u = hunits[i];
+            if (!(W > 1 && i + 1 < ns && u.k > 0.f && u.n1 == u.np && hunits[i + 1].n1 == hunits[i + 1].np && hunits[i + 1].k == u.k)) {
+                rest.push_back(i);
+                continue;
+            }
+            hunits[i + 1].dz2 = u.dz2;
+            int tries = 0;
+            while (tries < W && (int)lists[w].size() + 2 > cap[w]) {
+                w = (w + 1) % W;
+                ++tries;
+            }
+            std::vector<int> &to = tries < W ? lists[w] : rest;
+            to.push_back(i);
+            to.push_back(i + 1);
+            if (tries < W) w = (w + 1) % W;
+            ++i;
+        }
+        hwalk.resize(ns);
+        for (int r = 0, next = 0; r <= ns / W; ++r)  // (the rest fills the free places in order)
+            for (int w = 0; w < W; ++w)
+                if (r < cap[w]) hwalk[r * W + w] = r < (int)lists[w].size() ? lists[w][r] : rest[next++];
         g->bins_blk = d.n_tof <= 16 ? d.n_tof : (d.n_tof + 1) / 2;
         g->unit_floats = (max_np + 15) / 16 * 16 * d.n_tof;
         // E(x) = erf(x) on [-c, c], c the kernel's truncation (erf is constant in
@@ -462,6 +496,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     bool ok = alloc((void **)&g->lines, sizeof(LineP) * nl) && alloc((void **)&g->planes, sizeof(PlaneP) * planes.size()) &&
               alloc((void **)&g->units, sizeof(TofUnit) * hunits.size()) &&
               alloc((void **)&g->etab, sizeof(float4) * hetab.size()) &&
+              alloc((void **)&g->walk_order, sizeof(int) * hwalk.size()) &&
               alloc((void **)&g->gsegs, sizeof(SegP) * gsegs.size()) &&
               alloc((void **)&g->gather, sizeof(GatherSeg) * hgather.size()) &&
               alloc((void **)&g->gchunk, sizeof(GatherChunk) * hchunks.size()) &&
@@ -485,6 +520,8 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     if (e == hipSuccess) e = hipMemcpy(g->planes, hplanes.data(), sizeof(PlaneP) * planes.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !hunits.empty())
         e = hipMemcpy(g->units, hunits.data(), sizeof(TofUnit) * hunits.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !hwalk.empty())
+        e = hipMemcpy(g->walk_order, hwalk.data(), sizeof(int) * hwalk.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !hetab.empty())
         e = hipMemcpy(g->etab, hetab.data(), sizeof(float4) * hetab.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->gsegs, gsegs.data(), sizeof(SegP) * gsegs.size(), hipMemcpyHostToDevice);
@@ -552,7 +589,7 @@ extern "C" pet_status pet_geom_destroy(pet_geom g) {
         (void)hipEventDestroy(e.first);
         (void)hipEventDestroy(e.second);
     }
-    void *ptrs[] = {g->lines, g->planes, g->units, g->etab, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
+    void *ptrs[] = {g->lines, g->planes, g->units, g->etab, g->walk_order, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
                     g->grad, g->hess, g->num, g->sensi, g->partial, g->dscratch, g->fscratch, g->psf_a, g->psf_b,
                     g->check_counts, g->wtab, g->ctab, g->gsegs, g->gather, g->gchunk};
     for (void *p : ptrs)

@@ -37,6 +37,35 @@ __device__ __forceinline__ void z_clip(const LineP &L, const PlaneP &P, int nz, 
     }
 }
 
+__device__ __forceinline__ float load_y(const void *y, int dt, int64_t idx) {
+    if (dt == PET_Y_U8) return (float)((const uint8_t *)y)[idx];
+    if (dt == PET_Y_U16) return (float)((const uint16_t *)y)[idx];
+    return ((const float *)y)[idx];
+}
+
+// Poisson deviance term d(ybar, y) of the KL data fidelity, FP64.
+__device__ __forceinline__ double kl_term(float ybar, float yv) {
+    double s = ybar, t = yv;
+    if (t > 0.0) return s - t + t * log(t / s);
+    return s;
+}
+
+// Number of samples of [is, ie] (in increasing-t order) with t < e.
+__device__ __forceinline__ int cut_count(float e, float len, float lam0, float dlam, int is, int ie) {
+    float lam_e = e / len + 0.5f;
+    float r = (lam_e - lam0) / dlam;
+    int nq = ie - is + 1;
+    int c;
+    if (dlam > 0.f) {
+        float cr = ceilf(r);
+        c = cr < (float)is ? 0 : (cr > (float)(ie + 1) ? nq : (int)cr - is);
+    } else {
+        float fr = floorf(r);
+        c = fr >= (float)ie ? 0 : (fr < (float)(is - 1) ? nq : ie - (int)fr);
+    }
+    return c;
+}
+
 // Sheet cells (row r, padded axial position zp) are dealt to the threads of
 // a workgroup by column: thread t keeps zp = t mod rz and takes rows
 // t / rz, t / rz + R, ... with R = blockDim / rz (the threads past R rz idle).

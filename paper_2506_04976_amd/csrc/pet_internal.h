@@ -161,7 +161,16 @@ struct ProjArgs {
     int n_etab;
     double e_scale;
     float e_mid, dpos, dpos_hi, dpos_lo;
+    // TOF walk (walk.hip): order of the units, most bins that overlap one point
+    const int *walk_order;
+    int ws;
 };
+
+// LDS floats of one wave of the TOF walk: weights [rows][4] and [rows][ws - 4],
+// interval cuts
+__host__ __device__ inline int walk_wave_floats(int rows_max, int ws, int n_int) {
+    return (rows_max * (ws > 4 ? ws : 4) + ((n_int + 1 + 3) & ~3) + 3) & ~3;
+}
 
 // ---- zero-count-aware data term (counts.hip) --------------------------------
 // One bin with y > 0 of a transaxial line, with what the counts kernel needs
@@ -277,6 +286,8 @@ struct pet_geom_s {
     float4 *etab = nullptr;
     int n_units = 0, bins_blk = 0, q_units = 0, q_units_back = 0, unit_floats = 0, n_etab = 0, x_stride = 0;
     double e_scale = 0.0;
+    int *walk_order = nullptr;          // TOF walk: order of the units
+    int walk_waves = 0, tof_ws = 0;     // its waves; most bins that overlap one point
     int nt_threads = pet::NT_BLOCK;     // non-TOF line kernel: threads per workgroup
     int *views_dev = nullptr;           // [n_subsets + 1][max(max_views, n_views)]; last row: all views
     int views_stride = 0;
@@ -348,6 +359,14 @@ inline size_t tof_lds_bytes(const pet_geom_s *g, bool x, int slots, int waves) {
                             (size_t)slots * g->unit_floats + (size_t)waves * TOF_STAGE_FLOATS) +
            sizeof(float4) * ((size_t)g->n_etab + 1 + 2 * g->n_units);
 }
+// LDS of the TOF walk: image sheet, FP64 gradient sheet (z), the waves' tables
+inline size_t walk_lds_bytes(const pet_geom_s *g, bool z) {
+    const size_t sheet = ((size_t)g->rows_max * (g->d.nz + 2 * PADZ) + 3) & ~(size_t)3;
+    return sizeof(float) * ((z ? 3 : 1) * sheet +
+                            (size_t)g->walk_waves * walk_wave_floats(g->rows_max, g->tof_ws, g->tof.n_int));
+}
+// TOF objective (M_OBJ) and subset gradient with its likelihood (M_GRAD) (walk.hip)
+hipError_t launch_tof_walk(const pet_geom_s *g, int mode, dim3 grid, const ProjArgs &a, hipStream_t s);
 // persistent batched subset-gradient line kernel over the work items of one step
 // (f: what its TOF members need at most)
 struct BatchForm {

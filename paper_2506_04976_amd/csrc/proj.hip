@@ -1,5 +1,5 @@
 // Joseph projector kernels for gfx950 (forward, adjoint, fused subset gradient,
-// EM ratio, KL objective, work counts), line-driven with LDS sheets.
+// EM ratio, non-TOF likelihood, work counts), line-driven with LDS sheets.
 //
 // Separability used here: every LOR of a transaxial line (view, radial) has the
 // same principal axis m, the same sample positions lambda(i) along m and the
@@ -26,70 +26,12 @@
 namespace pet {
 namespace {
 
-__device__ __forceinline__ float load_y(const void *y, int dt, int64_t idx) {
-    if (dt == PET_Y_U8) return (float)((const uint8_t *)y)[idx];
-    if (dt == PET_Y_U16) return (float)((const uint16_t *)y)[idx];
-    return ((const float *)y)[idx];
-}
-
 // The lane index, opaque: what follows from it is formed where it is used and not
 // kept in registers across the other phases (which need all 128 of them).
 __device__ __forceinline__ int lane_here() {
     int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     asm volatile("" : "+v"(lane));
     return lane;
-}
-
-// Poisson deviance term d(ybar, y) of the KL data fidelity, FP64.
-__device__ __forceinline__ double kl_term(float ybar, float yv) {
-    double s = ybar, t = yv;
-    if (t > 0.0) return s - t + t * log(t / s);
-    return s;
-}
-
-// The same term where registers are short: the logarithm from
-// log(m 2^e) = e log 2 + 2 artanh((m - 1) / (m + 1)), m in [sqrt(1/2), sqrt 2], the
-// artanh series to s^21 (remainder below 1e-18), its coefficients read from
-// constant memory at each use (as literals they would be kept in registers for
-// the whole kernel).
-__constant__ double LOG_SERIES[11] = {2.0,        2.0 / 3.0,  2.0 / 5.0,  2.0 / 7.0,  2.0 / 9.0, 2.0 / 11.0,
-                                      2.0 / 13.0, 2.0 / 15.0, 2.0 / 17.0, 2.0 / 19.0, 2.0 / 21.0};
-
-__device__ __forceinline__ double kl_term_lean(float ybar, float yv) {
-    const double s = ybar, t = yv;
-    if (!(t > 0.0)) return s;
-    const double x = t / s;
-    if (!(x > 0.0 && x < (double)INFINITY)) return s - t + t * (x == (double)INFINITY ? x : (double)__builtin_nanf(""));
-    typedef const double __attribute__((address_space(4))) *Coefs;
-    Coefs c = (Coefs)(uintptr_t)LOG_SERIES;
-    asm volatile("" : "+s"(c));
-    double m = __builtin_amdgcn_frexp_mant(x);
-    int e = __builtin_amdgcn_frexp_exp(x);
-    if (m < 0.70710678118654752) {
-        m *= 2.0;
-        e -= 1;
-    }
-    const double r = (m - 1.0) / (m + 1.0), z = r * r;
-    double p = c[10];
-#pragma unroll
-    for (int k = 9; k >= 0; --k) p = fma(p, z, c[k]);
-    return s - t + t * fma((double)e, 0.69314718055994531, r * p);
-}
-
-// Number of samples of [is, ie] (in increasing-t order) with t < e.
-__device__ __forceinline__ int cut_count(float e, float len, float lam0, float dlam, int is, int ie) {
-    float lam_e = e / len + 0.5f;
-    float r = (lam_e - lam0) / dlam;
-    int nq = ie - is + 1;
-    int c;
-    if (dlam > 0.f) {
-        float cr = ceilf(r);
-        c = cr < (float)is ? 0 : (cr > (float)(ie + 1) ? nq : (int)cr - is);
-    } else {
-        float fr = floorf(r);
-        c = fr >= (float)ie ? 0 : (fr < (float)(is - 1) ? nq : ie - (int)fr);
-    }
-    return c;
 }
 
 // ---------------------------------------------------------------------------
@@ -667,32 +609,25 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
     }
 }
 
-// A line that misses the image: forward values and likelihood terms from the
-// additive terms alone, in memory order; it has no adjoint.
-template <int MODE>
-__device__ __forceinline__ void tof_line_outside(const ProjArgs &a, int line, int tid, double &kl) {
+// A line that misses the image: forward values from the additive terms alone, in
+// memory order; it has no adjoint.
+__device__ __forceinline__ void tof_line_outside(const ProjArgs &a, int line, int tid) {
     const int nt = a.tof.n_tof, n = a.n_planes * nt, nb = blockDim.x;
     const int64_t lor0 = (int64_t)line * a.n_planes, base = lor0 * nt;
     for (int e0 = tid; e0 < n; e0 += 4 * nb) {
-        float m[4], v[4], y[4];
+        float m[4], v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = e0 + q * nb;
-            m[q] = v[q] = y[q] = 0.f;
+            m[q] = v[q] = 0.f;
             if (e >= n) continue;
             m[q] = a.mult ? a.mult[lor0 + e / nt] : 1.f;
             if (a.add) v[q] = a.add[base + e];
-            if (MODE != M_FWD) y[q] = load_y(a.y, a.y_dtype, base + e);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = e0 + q * nb;
-            if (e >= n) continue;
-            const float ybar = fmaf(m[q], 0.f, v[q]);
-            if (MODE == M_FWD)
-                a.out[base + e] = ybar;
-            else
-                kl += kl_term_lean(ybar, y[q]);
+            if (e < n) a.out[base + e] = fmaf(m[q], 0.f, v[q]);
         }
     }
 }
@@ -715,14 +650,13 @@ __device__ __forceinline__ float uniform(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
-// One transaxial line of a TOF geometry by the whole workgroup; adds this
-// thread's FP64 partial (KL) to kl.  The adjoint takes 16 NZB voxels along z at a
-// time; MANY: more than two planes of a segment may reach a voxel; KL: the Poisson
-// deviance is wanted as well (M_OBJ: alone); TILES: the forward takes that many tiles
-// of 16 planes at a time (16 registers of sums with four tiles or two blocks of bins).
-template <int MODE, int MB, int NZB, bool MANY, bool KL, int TILES>
-__device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float *smem, int wave, double &kl,
-                                              int64_t g_off = 0) {
+// One transaxial line of a TOF geometry by the whole workgroup (the likelihood has
+// kernels of its own, walk.hip).  The adjoint takes 16 NZB voxels along z at a
+// time; MANY: more than two planes of a segment may reach a voxel; TILES: the
+// forward takes that many tiles of 16 planes at a time (16 registers of sums with
+// four tiles or two blocks of bins).
+template <int MODE, int MB, int NZB, bool MANY, int TILES>
+__device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float *smem, int wave, int64_t g_off = 0) {
     constexpr bool NEED_X = MODE != M_BACK;
     constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
     const int nw = blockDim.x >> 6;
@@ -730,15 +664,15 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
     const int nrow = L.i_hi - L.i_lo + 1;
     const int rz = a.rz, nt = a.tof.n_tof;
     if (nrow <= 0) {  // (uniform)
-        if (MODE == M_FWD || KL) tof_line_outside<MODE>(a, line, 64 * wave + lane_here(), kl);
+        if (MODE == M_FWD) tof_line_outside(a, line, 64 * wave + lane_here());
         return;
     }
     const int tid = 64 * wave + lane_here();
-    // LDS: X | factors of q_units units (the objective: sums of one unit per wave)
-    // | per wave: rows of Q | units' table positions | table of E
+    // LDS: X | factors of q_units units | per wave: rows of Q | units' table
+    // positions | table of E
     float *X = smem;
     float *Fs = smem + (NEED_X ? tof_x_floats(a.rows_max, a.x_stride) : 0);
-    const int n_slots = NEED_Z ? a.q_units : MODE == M_OBJ ? nw : 0;
+    const int n_slots = NEED_Z ? a.q_units : 0;
     float *stage = Fs + n_slots * a.unit_floats + wave * TOF_STAGE_FLOATS;
     TofPos *utab = reinterpret_cast<TofPos *>(Fs + n_slots * a.unit_floats + (NEED_Z ? nw * TOF_STAGE_FLOATS : 0));
     float4 *tab = reinterpret_cast<float4 *>(utab + a.n_units);
@@ -783,21 +717,14 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
     const int nzc = (a.nz + 16 * NZB - 1) / (16 * NZB);
     // a wave's cells stay in its registers over the groups of units if it has
     // one block of rows and one pass along z; else they are spread per group
-    const bool keep = !KL && nblk <= nw && nzc == 1;
+    const bool keep = nblk <= nw && nzc == 1;
     double acc[4][NZB];
 #pragma unroll
     for (int h = 0; h < 4; ++h)
 #pragma unroll
         for (int zb = 0; zb < NZB; ++zb) acc[h][zb] = 0.0;
 
-    double *kl_w = nullptr;  // this wave's sum (in LDS: no register through the adjoint)
-    if constexpr (KL) {
-        __shared__ double s_kl[MAX_WAVES];
-        kl_w = s_kl + wave;
-        if (lane_here() == 0) *kl_w = 0.0;
-    }
     for (int u0 = 0; u0 < a.n_units; u0 += a.q_units) {
-        double kl_u = 0.0;
         const int u1 = NEED_Z ? min(u0 + a.q_units, a.n_units) : a.n_units;
         // ---- forward projection and factors, one unit per wave ----
         for (int u = u0 + wave; u < u1; u += nw) {
@@ -807,7 +734,7 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
             const TofPos tp = utab[u];
             // Bin b of plane idx in LDS: F[(idx / 16 nt + b) 16 + idx mod 16] (the
             // tiles are filled up with zero planes), in memory base + idx nt + b.
-            float *F = Fs + (NEED_Z ? u - u0 : wave) * a.unit_floats;
+            float *F = Fs + (u - u0) * a.unit_floats;
             const int64_t lor0 = (int64_t)line * a.n_planes + p0, base = lor0 * nt;
             auto slow = [&](int i0, int i1, auto each) {  // the bins of planes [i0, i1), one per lane and round
 #pragma unroll 1
@@ -859,29 +786,6 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                         for (int r = 0; r < 4; ++r) top += fabsf(D[mb][pb][r]);
                 special = __any(!(top < INFINITY));
             }
-            if (KL) {
-                // D to F: the terms one per lane and round
-                const int ln = lane_here();
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int pb = 0; pb < TILES; ++pb)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int b = mb * a.bins_blk + 4 * (ln >> 4) + r;
-                            if (pb < nt0 && 4 * (ln >> 4) + r < a.bins_blk && b < nt)
-                                F[((t0 + pb) * nt + b) * 16 + (ln & 15)] = D[mb][pb][r];
-                        }
-                wave_lds_order();
-                slow(i0, i1, [&](int e, int idx, int b, float *f) {
-                    float sum = *f;
-                    if (!(fabsf(sum) < INFINITY)) sum = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b);
-                    const float m = a.mult ? a.mult[lor0 + idx] : 1.f;
-                    kl_u += kl_term_lean(fmaf(m, sum * tp.ell, a.add ? a.add[base + e] : 0.f),
-                                       load_y(a.y, a.y_dtype, base + e));
-                });
-                wave_lds_order();
-            }
             if (MODE == M_FWD && special) {
                 // (without the products of zero weights)
                 slow(i0, i1, [&](int e, int idx, int b, float *) {
@@ -890,7 +794,6 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                 });
                 continue;
             }
-            if (MODE == M_OBJ) continue;
             float top = 0.f;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
@@ -969,15 +872,6 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                 });
             }
         }
-        if (KL) {
-#pragma unroll
-            for (int k = 32; k; k >>= 1) {
-                const int from = (lane_here() ^ k) << 2;
-                kl_u += __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(kl_u)),
-                                         __builtin_amdgcn_ds_bpermute(from, __double2loint(kl_u)));
-            }
-            if (lane_here() == 0) *kl_w += kl_u;
-        }
         if (!NEED_Z) break;
         __syncthreads();
 
@@ -1034,17 +928,14 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
         }
         if (u1 < a.n_units) __syncthreads();
     }
-    if (KL && lane_here() == 0) kl += *kl_w;
 }
 
 // One line per workgroup, in the order a.order (longest first).
-template <int MODE, int MB, int NZB, bool MANY, bool KL>
+template <int MODE, int MB, int NZB, bool MANY>
 __global__ void __launch_bounds__(TOF_BLOCK, MODE == M_FWD && MB == 1 ? 8 : 4) k_line_tof(ProjArgs a) {
     extern __shared__ float4 smem4[];
-    double kl = 0.0;  // (not live through the body)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    line_tof_body<MODE, MB, NZB, MANY, KL, MB == 1 ? 4 : 2>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), wave, kl);
-    if (KL) block_sums(kl, kl, a.partial, false, 64 * wave + lane_here());
+    line_tof_body<MODE, MB, NZB, MANY, MB == 1 ? 4 : 2>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), wave);
 }
 
 // Work counts of a TOF line: samples, and sample-bin pairs within the bins'
@@ -1139,9 +1030,7 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) k_line_batched(const BMember *
         const int view = __builtin_amdgcn_readfirstlane(snap ? jv : m.views[st.subset * m.views_stride + jv]);
         const int64_t g_off = snap ? (int64_t)(jv % m.n_sub) * m.g_slot : 0;
         if (m.is_tof) {
-            double no_kl = 0.0;
-            const int line = view * n_rad + k;
-            line_tof_body<M_GRAD, MB, NZB, MANY, false, MB == 1 ? 4 : 2>(pa, line, smem, wave, no_kl, g_off);
+            line_tof_body<M_GRAD, MB, NZB, MANY, MB == 1 ? 4 : 2>(pa, view * n_rad + k, smem, wave, g_off);
         } else {
             line_nt_body<M_GRAD>(pa, view * n_rad + k, smem, 64 * wave + lane_here(), g_off);
         }
@@ -1159,9 +1048,9 @@ size_t nt_lds(const pet_geom_s *g) {
     return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0));
 }
 
-template <int MODE, int MB, int NZB, bool MANY, bool KL>
+template <int MODE, int MB, int NZB, bool MANY>
 hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s) {
-    const bool x = MODE != M_BACK, z = MODE != M_FWD && MODE != M_OBJ;
+    const bool x = MODE != M_BACK, z = MODE != M_FWD;
     if (MODE == M_BACK) a.q_units = g->q_units_back;
     // Without an adjoint a wave has nothing but units to do: no more waves than units
     // (four at least, for the image sheet), and more workgroups on a CU instead: five
@@ -1169,15 +1058,15 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
     // even rounds of many units are slower (41 on 7 waves 367 us against 347 on 8; 17
     // on 6: 173 against 162): less is in flight.
     const int waves = z ? TOF_BLOCK / 64 : std::min(TOF_BLOCK / 64, std::max(4, g->n_units));
-    const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : MODE == M_OBJ ? waves : 0, z ? waves : 0);
+    const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : 0, z ? waves : 0);
     static size_t granted = 64 * 1024;
     if (lds > granted) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY, KL>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e == hipSuccess) granted = lds;
         (void)hipGetLastError();
     }
-    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY, KL>), grid, dim3(64 * waves), lds, s, a);
+    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY>), grid, dim3(64 * waves), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1190,21 +1079,17 @@ hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStr
     if constexpr (MODE == M_COUNT) {
         hipLaunchKernelGGL(k_count_tof, grid, dim3(g->nt_threads), 0, s, a);
         return hipGetLastError();
+    } else if constexpr (MODE == M_OBJ) {
+        return launch_tof_walk(g, M_OBJ, grid, a, s);
     } else {
+        if (MODE == M_GRAD && a.partial) return launch_tof_walk(g, M_GRAD, grid, a, s);
         hipError_t e = hipSuccess;
         tof_form(a.tof.n_tof, a.nz, a.gather_two, [&](auto mb, auto nzb, auto many) {
             // (without an adjoint the last two make no difference)
-            if constexpr (MODE == M_FWD || MODE == M_OBJ) {
-                e = launch_tof<MODE, mb.value, STAGE_ZB, false, MODE == M_OBJ>(g, grid, a, s);
-            } else {
-                if constexpr (MODE == M_GRAD || MODE == M_EM) {
-                    if (a.partial) {
-                        e = launch_tof<MODE, mb.value, nzb.value, many.value != 0, true>(g, grid, a, s);
-                        return;
-                    }
-                }
-                e = launch_tof<MODE, mb.value, nzb.value, many.value != 0, false>(g, grid, a, s);
-            }
+            if constexpr (MODE == M_FWD)
+                e = launch_tof<MODE, mb.value, STAGE_ZB, false>(g, grid, a, s);
+            else
+                e = launch_tof<MODE, mb.value, nzb.value, many.value != 0>(g, grid, a, s);
         });
         return e;
     }

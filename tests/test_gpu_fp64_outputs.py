@@ -23,6 +23,13 @@ TOL = 1e-12
 GEOMETRIES = {
     "mini_nontof": configs.get("mini_nontof"),
     "mini_2d": configs.get("mini_2d"),
+    "mini_tof": configs.get("mini_tof"),
+    "mini_tof_many": configs.get("mini_tof_many"),
+    "mini_tof_seg40": configs.get("mini_tof_seg40"),
+    "mini_tof_psf": configs.get("mini_tof_psf"),
+    "tof_2d": configs.get("mini_2d", n_tof=5, tof_bin=30.0, tof_sigma=18.0, tof_nsigma=3.0),
+    "tof_wide": configs.get("mini_tof", nx=40, ny=37, n_views=30, n_crystals=60, n_rad=21, radius=130.0, n_rings=14,
+                            max_ring_diff=9, n_tof=26, tof_bin=9.0, tof_sigma=7.5, tof_nsigma=2.5),
     "planes_1100": configs.get("mini_nontof", n_rings=44, ring_pitch=0.8, max_ring_diff=14),
     "chunks": configs.get("mini_nontof", n_views=6, n_crystals=12, n_rad=5, n_subsets=2, nx=6, ny=7, nz=400, vz=1.0,
                           n_rings=390, ring_pitch=1.01, max_ring_diff=20),
@@ -105,6 +112,21 @@ RECORDED = {
     ("likelihood", "slab"): "0x1.bd6534c00fa36p+14",
     ("likelihood", "chunks"): "0x1.0411cdc49284fp+20",
     ("objective", "chunks"): "0x1.0396d17279f67p+21",
+    ("likelihood", "mini_nontof"): "0x1.1530798ab2358p+13",
+    ("likelihood_all", "mini_nontof"): "0x1.d7660906c5d64p+14",
+    ("likelihood_noalloc", "mini_nontof"): "0x1.b74ef49f9d25fp+12",
+    ("objective", "mini_nontof"): "0x1.da85ad98c225dp+14",
+    ("likelihood", "mini_tof"): "0x1.46e6e8e5b1a86p+16",
+    ("likelihood_all", "mini_tof"): "0x1.1ce9af971478ap+18",
+    ("likelihood_noalloc", "mini_tof"): "0x1.104ff4b4ffebbp+16",
+    ("objective", "mini_tof"): "0x1.1d1ba9e0343dap+18",
+    ("likelihood", "mini_tof_many"): "0x1.92c53123fcbfep+18",
+    ("objective", "mini_tof_many"): "0x1.6060710052d33p+20",
+    ("likelihood", "mini_tof_seg40"): "0x1.ef85372c9c6fcp+18",
+    ("objective", "mini_tof_seg40"): "0x1.b055d7c2cb819p+20",
+    ("likelihood", "mini_tof_psf"): "0x1.4b6248e306dcap+16",
+    ("likelihood", "tof_2d"): "0x1.31294ea7915dcp+11",
+    ("likelihood", "tof_wide"): "0x1.9c3851c1712bcp+21",
 }
 
 
