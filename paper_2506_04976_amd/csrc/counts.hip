@@ -22,7 +22,9 @@
 // invariant): W(d) = 1/2 [E(w/2 - d) - E(-w/2 - d)], E the clamped erf.  It
 // is even and tabulated once per geometry over half its support, |d| <= w/2 +
 // nsig sigma, in CNT_TAB intervals (FP64 on the host; each interval's line splits
-// the error evenly above and below), and interpolated linearly from LDS.
+// the error evenly above and below), and interpolated linearly from LDS.  With the
+// FP64 likelihood, which shows a table's errors (1e-9 to 1e-8 of it on small data),
+// the kernels read the one of NW_TAB chords over the whole support.
 #include "line_sheets.h"
 
 #include <algorithm>
@@ -85,13 +87,21 @@ __global__ void __launch_bounds__(256) k_counts_per_line(const void *__restrict_
 }
 
 // Geometry of one bin with counts within its line (plane p, TOF bin b): the
-// sample rows [is, ie] (z range, then TOF window), the table position
-// pos(i) = pA i + pB of row i, the padded axial position u(i) = zA i + zB
+// sample rows [is, ie] (z range, then TOF window), the distance d(i) = dA i + dB
+// (mm) of row i from the bin's centre, the padded axial position u(i) = zA i + zB
 // and the step length ell.
 struct RecGeo {
     int is, ie;
-    float pA, pB, zA, zB, ell;
+    float dA, dB, zA, zB, ell;
 };
+
+// Table position pos(i) = x i + y of row i of a bin: d / dx, or with the likelihood
+// d / dx + NW_TAB / 2 (dx that of its table).
+template <bool KL>
+__device__ __forceinline__ float2 table_pos(const CountArgs &c, float dA, float dB) {
+    if (KL) return make_float2(dA * c.inv_dw, fmaf(dB, c.inv_dw, (float)(NW_TAB / 2)));
+    return make_float2(dA * c.inv_dx, dB * c.inv_dx);
+}
 
 template <bool TOF>
 __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c, const LineP &L, const PlaneP &P,
@@ -100,7 +110,7 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
     const float len = sqrtf(L.lt2 + P.dz2);
     r.ell = L.vm_um * len;
     z_clip<true>(L, P, a.nz, r.is, r.ie);  // (u is clamped by the loops)
-    r.pA = r.pB = 0.f;
+    r.dA = r.dB = 0.f;
     if (TOF) {
         // d(i) = t(i) - t_b, t(i) = (lambda(i) - 1/2) |u| the signed distance
         // from the LOR centre; rows outside |d| <= D (one row of margin, where
@@ -115,13 +125,14 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
         const float hi = fmaxf(fminf(ceilf(fmaxf(ia, ib)) + 1.f, (float)r.ie), (float)(r.is - 1));
         r.is = (int)lo;
         r.ie = (int)hi;
-        r.pA = dd * c.inv_dx;
-        r.pB = d0 * c.inv_dx;
+        r.dA = dd;
+        r.dB = d0;
     }
+    const float2 pc = table_pos<false>(c, r.dA, r.dB), pw = table_pos<true>(c, r.dA, r.dB);
     r.zA = P.zs * L.dlam;
     r.zB = fmaf(L.lam0, P.zs, P.zb) + (float)PADZ;
     // Rows whose axial position u would leave the sheet row (cells j, j + 1
-    // for u in [0, rz - 1)) or whose table position would leave the TOF table
+    // for u in [0, rz - 1)) or whose table position would leave one of the TOF tables
     // carry no weight (zero padding, outside the TOF support): drop them at the
     // ends, so that the line kernels need no clamps.  Both positions are affine
     // in the row and evaluated as the kernels do (one correctly rounded FMA,
@@ -131,8 +142,9 @@ __device__ __forceinline__ RecGeo rec_geo(const ProjArgs &a, const CountArgs &c,
         const float u = fmaf((float)i, r.zA, r.zB);
         if (!(u >= 0.f && u < ulim)) return false;
         if (TOF) {
-            const float pos = fmaf((float)i, r.pA, r.pB);
+            const float pos = fmaf((float)i, pc.x, pc.y), pos_w = fmaf((float)i, pw.x, pw.y);
             if (!(pos >= -c.pos_max && pos <= c.pos_max)) return false;
+            if (!(pos_w >= 0.f && pos_w <= (float)NW_TAB - 1e-3f)) return false;
         }
         return true;
     };
@@ -178,8 +190,8 @@ __global__ void __launch_bounds__(256) k_counts_fill(const void *__restrict__ y,
             CountRec it;
             it.is = (int16_t)g.is;
             it.ie = (int16_t)g.ie;
-            it.pA = g.pA;
-            it.pB = g.pB;
+            it.dA = g.dA;
+            it.dB = g.dB;
             it.zA = g.zA;
             it.zB = g.zB;
             it.me = (mult ? mult[(int64_t)blockIdx.x * n_planes + plane] : 1.f) * g.ell;
@@ -192,8 +204,9 @@ __global__ void __launch_bounds__(256) k_counts_fill(const void *__restrict__ y,
     }
 }
 
-// TOF weight W(d) from the LDS table, at table position pos = d / dx, |pos| <=
-// pos_max (the absolute value costs nothing: a modifier of both conversions).
+// TOF weight W(d) from the LDS table, at table position pos: d / dx, |pos| <= pos_max,
+// or with the likelihood in [0, NW_TAB) (the absolute value costs nothing: a
+// modifier of both conversions).
 __device__ __forceinline__ float tof_weight_at(const float2 *tab, float pos) {
     const float2 t = tab[(int)fabsf(pos)];
     return fmaf(__builtin_amdgcn_fractf(fabsf(pos)), t.y, t.x);
@@ -377,8 +390,8 @@ struct BinB {
     float pA, pB, zA, zB, Q;
 };
 
-__device__ __forceinline__ BinB bin_b(const CountRec &e, float Q) {
-    return {(uint32_t)(uint16_t)e.is | ((uint32_t)(uint16_t)e.ie << 16), e.pA, e.pB, e.zA, e.zB, Q};
+__device__ __forceinline__ BinB bin_b(const CountRec &e, float2 pos, float Q) {
+    return {(uint32_t)(uint16_t)e.is | ((uint32_t)(uint16_t)e.ie << 16), pos.x, pos.y, e.zA, e.zB, Q};
 }
 
 // Rounds of a chunk (bins per thread) that phase two keeps in registers.
@@ -420,11 +433,12 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
 
     if (TOF) {
         // the table's loads in flight together
-        constexpr int TV = CNT_TAB / CNT_BLOCK;
-        static_assert(CNT_TAB % CNT_BLOCK == 0, "the same number of entries per thread");
+        constexpr int TV = (KL ? NW_TAB : CNT_TAB) / CNT_BLOCK;
+        static_assert(CNT_TAB % CNT_BLOCK == 0 && NW_TAB % CNT_BLOCK == 0, "the same number of entries per thread");
+        const float2 *wtab = KL ? c.wtab : c.ctab;
         float2 wv[TV];
 #pragma unroll
-        for (int u = 0; u < TV; ++u) wv[u] = c.wtab[threadIdx.x + u * CNT_BLOCK];
+        for (int u = 0; u < TV; ++u) wv[u] = wtab[threadIdx.x + u * CNT_BLOCK];
 #pragma unroll
         for (int u = 0; u < TV; ++u) tab[threadIdx.x + u * CNT_BLOCK] = wv[u];
     }
@@ -453,7 +467,7 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
         float qabs = 0.f, qneg = 0.f;
         // the thread's bins of the chunk's rounds (at most CNT_ROUNDS) and
         // their factors, for phase two
-        BinB b0 = bin_b(none, 0.f), b1 = b0, b2 = b0, b3 = b0;
+        BinB b0 = bin_b(none, make_float2(0.f, 0.f), 0.f), b1 = b0, b2 = b0, b3 = b0;
         for (int rr = 0; rr < nr; ++rr) {
             const int m = min(CNT_BLOCK, n_c - rr * CNT_BLOCK);
             const int C = lanes_per_bin(m);
@@ -464,6 +478,7 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
             const int k = (int)threadIdx.x / C;
             const bool act = k < m;
             const CountRec e = act ? c.items[c0 + (int64_t)rr * CNT_BLOCK + k] : none;
+            const float2 pos = TOF ? table_pos<KL>(c, e.dA, e.dB) : make_float2(0.f, 0.f);
             // rows as floats (exact integers): no conversion per sample
             const float fis = (float)(e.is + ch), fie = (float)e.ie;
             // two samples per iteration (their LDS reads in flight together,
@@ -480,15 +495,15 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
                 const float a0 = xr[j0], b0 = xr[j0 + 1], a1 = xr[step + j1], b1 = xr[step + j1 + 1];
                 const float v0 = fmaf(__builtin_amdgcn_fractf(u0), b0 - a0, a0);
                 const float v1 = fmaf(__builtin_amdgcn_fractf(u1), b1 - a1, a1);
-                s = TOF ? fmaf(tof_weight_at(tab, fmaf(fi, e.pA, e.pB)), v0, s) : s + v0;
-                s1 = TOF ? fmaf(tof_weight_at(tab, fmaf(fj, e.pA, e.pB)), v1, s1) : s1 + v1;
+                s = TOF ? fmaf(tof_weight_at(tab, fmaf(fi, pos.x, pos.y)), v0, s) : s + v0;
+                s1 = TOF ? fmaf(tof_weight_at(tab, fmaf(fj, pos.x, pos.y)), v1, s1) : s1 + v1;
             }
             if (fi <= fie) {
                 const float u = fmaf(fi, e.zA, e.zB);
                 const int j = (int)u;
                 const float x0 = xr[j], x1 = xr[j + 1];
                 const float v = fmaf(__builtin_amdgcn_fractf(u), x1 - x0, x0);
-                s = TOF ? fmaf(tof_weight_at(tab, fmaf(fi, e.pA, e.pB)), v, s) : s + v;
+                s = TOF ? fmaf(tof_weight_at(tab, fmaf(fi, pos.x, pos.y)), v, s) : s + v;
             }
             s += s1;
             // (every lane of the bin ends with the bin's sum)
@@ -503,7 +518,7 @@ __global__ void __launch_bounds__(CNT_BLOCK, KL ? 4 : 6) k_line_counts(ProjArgs 
                     qneg += Q < 0.f ? 1.f : 0.f;
                 }
                 // (a uniform switch keeps every register index static)
-                const BinB b = bin_b(e, Q);
+                const BinB b = bin_b(e, pos, Q);
                 switch (rr) {
                     case 0: b0 = b; break;
                     case 1: b1 = b; break;
@@ -622,8 +637,8 @@ hipError_t launch_counts_mode(const pet_geom_s *g, const pet_counts_s *cs, int n
 }  // namespace
 
 // LDS of the counts kernel (dynamic), in floats: the sheet region (X, or the
-// packed gradient sheet of the rows of one parity), the TOF table (CNT_TAB
-// (W, dW) pairs), each rounded up to 16 bytes.
+// packed gradient sheet of the rows of one parity), the TOF table (CNT_TAB, with
+// the likelihood NW_TAB, (W, dW) pairs), each rounded up to 16 bytes.
 static size_t counts_sheet_floats(const pet_geom_s *g) {
     const size_t rz = (size_t)g->d.nz + 2 * PADZ;
     const size_t x = (size_t)g->rows_max * rz;
@@ -631,20 +646,20 @@ static size_t counts_sheet_floats(const pet_geom_s *g) {
     return (std::max(x, zu) + 3) & ~(size_t)3;
 }
 
-static size_t counts_tab_floats(const pet_geom_s *g) { return g->d.n_tof > 1 ? 2 * (size_t)CNT_TAB : 0; }
+static size_t counts_tab_floats(const pet_geom_s *g, bool kl) {
+    return g->d.n_tof > 1 ? 2 * (size_t)(kl ? NW_TAB : CNT_TAB) : 0;
+}
 
-static size_t counts_lds_base(const pet_geom_s *g) {
-    return sizeof(float) * (counts_sheet_floats(g) + counts_tab_floats(g)) + sizeof(SheetRow) * (size_t)g->rows_max;
+static size_t counts_lds_base(const pet_geom_s *g, bool kl) {
+    return sizeof(float) * (counts_sheet_floats(g) + counts_tab_floats(g, kl)) + sizeof(SheetRow) * (size_t)g->rows_max;
 }
 
 // Bins per chunk with M_GRAD: CNT_QCAP (their factors live in registers), or
-// 0 if the sheet and the table (with 1 KB of static shared memory) exceed the
+// 0 if the sheet and the larger table (with 1 KB of static shared memory) exceed the
 // LDS.
 static int counts_q_cap(const pet_geom_s *g) {
-    return counts_lds_base(g) + 1024 <= g->max_lds ? CNT_QCAP : 0;
+    return counts_lds_base(g, true) + 1024 <= g->max_lds ? CNT_QCAP : 0;
 }
-
-size_t counts_lds_bytes(const pet_geom_s *g, int) { return counts_lds_base(g); }
 
 int counts_blocks(const pet_counts_s *cs, int subset) {
     const int row = subset < 0 ? cs->n_subsets : subset;
@@ -652,15 +667,17 @@ int counts_blocks(const pet_counts_s *cs, int subset) {
 }
 
 // The TOF table's constants (and the TOF bin count) of a geometry.
-static CountArgs count_args(const pet_geom_s *g) {
+static CountArgs count_args(const pet_geom_s *g, bool kl) {
     CountArgs c{};
-    c.wtab = g->ctab;
+    c.ctab = g->ctab;
+    c.wtab = g->wtab;
     c.sheet_floats = (int)counts_sheet_floats(g);
-    c.tab_floats = (int)counts_tab_floats(g);
+    c.tab_floats = (int)counts_tab_floats(g, kl);
     c.n_tof = g->d.n_tof;
     c.wD = g->wD;
     c.inv_dx = (float)(CNT_TAB / (double)g->wD);
     c.pos_max = (float)CNT_TAB - 1e-3f;
+    c.inv_dw = (float)(NW_TAB / (2.0 * g->wD));
     return c;
 }
 
@@ -669,13 +686,14 @@ hipError_t launch_line_counts(pet_geom_s *g, const pet_counts_s *cs, int mode, i
     const int nblk = counts_blocks(cs, subset);
     if (nblk == 0) return hipSuccess;
     if (slot_floats && (subset >= 0 || mode != M_GRAD)) return hipErrorInvalidValue;
-    CountArgs c = count_args(g);
+    const bool kl = a.partial || mode != M_GRAD;
+    CountArgs c = count_args(g, kl);
     c.slot_floats = slot_floats;
     c.items = cs->items;
     c.desc = cs->desc + cs->lines_off[subset < 0 ? cs->n_subsets : subset];
     c.q_cap = mode != M_GRAD ? (1 << 30) : (g->flags & PET_SMALL_CHUNKS) ? std::min(16, counts_q_cap(g)) : counts_q_cap(g);
     c.force_signed = (g->flags & PET_SIGNED_SHEETS) != 0;
-    const size_t lds = counts_lds_bytes(g, mode);
+    const size_t lds = counts_lds_base(g, kl);
     const bool tof = g->d.n_tof > 1;
     const int threads = CNT_BLOCK;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -748,7 +766,7 @@ extern "C" pet_status pet_counts_create(pet_geom g, const void *y, int y_dtype, 
     if (e == hipSuccess) e = hipMemcpy(c->line_off, off.data(), sizeof(int64_t) * (n_lines + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess && c->n_items > 0) {
         const ProjArgs pa = geom_proj_args(g);
-        const CountArgs ca = count_args(g);
+        const CountArgs ca = count_args(g, false);
         if (g->d.n_tof > 1)
             hipLaunchKernelGGL(k_counts_fill<true>, dim3(n_lines), dim3(256), 0, 0, y, y_dtype, add, mult, bpl,
                                c->line_off, pa, ca, c->items);

@@ -175,19 +175,22 @@ __host__ __device__ inline int walk_wave_floats(int rows_max, int ws, int n_int)
 // ---- zero-count-aware data term (counts.hip) --------------------------------
 // One bin with y > 0 of a transaxial line, with what the counts kernel needs
 // of its LOR (computed once, at compaction): the sample rows that reach the
-// grid and the bin's TOF window, the TOF table position and the padded axial
-// position as affine functions of the row, mult times the step length, the
+// grid and the bin's TOF window, the distance from the bin's centre and the padded
+// axial position as affine functions of the row, mult times the step length, the
 // count and the background.
 struct CountRec {
     int16_t is, ie;  // sample rows [is, ie] (empty: is > ie)
-    float pA, pB;    // TOF table position of row i: pA i + pB (0 without TOF)
+    float dA, dB;    // distance (mm) of row i from the TOF bin's centre: dA i + dB (0 without TOF)
     float zA, zB;    // padded axial position of row i: zA i + zB
     float me;        // mult * ell, ell the LOR's step length (mm)
     float y, add;
 };
 static_assert(sizeof(CountRec) == 32, "CountRec layout");
 constexpr int NW_TAB = 4096;    // intervals of the tabulated TOF weight W(d)
-constexpr int CNT_TAB = 1536;   // intervals of its table of W(d), d >= 0 (three workgroups per CU beside 71 slices)
+// Intervals of the count kernels' table of W(d), d >= 0.  12 KB leave room for three
+// workgroups per CU beside sheets of up to 10200 cells (128 rows of 75 slices), and
+// its lines are no further off than 4096 chords over both signs.
+constexpr int CNT_TAB = 1536;
 constexpr int CNT_BLOCK = 512;   // threads per workgroup of the counts line kernel
 constexpr int CNT_QCAP = 2048;   // bins per chunk of the counts line kernel (four rounds of one bin per thread)
 constexpr int CU_LDS_BYTES = 160 * 1024;  // LDS of one gfx950 CU
@@ -205,11 +208,13 @@ static_assert(sizeof(CountLine) == 48, "CountLine layout");
 struct CountArgs {
     const CountRec *items;
     const CountLine *desc;    // the launch's lines (workgroup b takes desc[b])
-    const float2 *wtab;       // TOF: value and difference of W's line in each of CNT_TAB intervals
+    const float2 *ctab;       // TOF: value and difference of W's line in each of CNT_TAB intervals of [0, wD]
+    const float2 *wtab;       // and of its chord in each of NW_TAB intervals of [-wD, wD] (with the likelihood)
     int sheet_floats, tab_floats;  // LDS layout: sheet region, TOF table (floats)
-    int nw, n_tof;
+    int n_tof;
     float wD;                 // support of W: |d| <= wD
-    float inv_dx, pos_max;    // table position of d: d * inv_dx, its magnitude at most pos_max
+    float inv_dx, pos_max;    // position of d in ctab: d * inv_dx, its magnitude at most pos_max
+    float inv_dw;             // in wtab: d * inv_dw + NW_TAB / 2
     int q_cap;                // bins per chunk of a line (at most CNT_QCAP with M_GRAD)
     int force_signed;         // signed fixed-point sheets for every chunk (tests)
     int64_t slot_floats;      // 0, or the stride of per-subset gradient sheets (G0, G1 + slot * stride)
@@ -395,7 +400,6 @@ int n_line_blocks(const pet_geom_s *g, int subset);
 hipError_t launch_line_counts(pet_geom_s *g, const pet_counts_s *c, int mode, int subset, const ProjArgs &a,
                               hipStream_t s, int64_t slot_floats = 0);
 int counts_blocks(const pet_counts_s *c, int subset);
-size_t counts_lds_bytes(const pet_geom_s *g, int mode);
 
 // cell-driven (gather) adjoint into the gradient sheets (gather.hip)
 hipError_t launch_line_gather(pet_geom_s *g, int subset, const ProjArgs &a, hipStream_t s);

@@ -56,6 +56,7 @@ class Inputs:
         self.sens = t(0.1 + rng.random(g.n_vox))
         self.grad = torch.zeros_like(self.x)
         self.out = torch.full((1,), -1.0, dtype=torch.float64, device="cuda:0")
+        self.counts = pm.Counts(g, self.y, self.add, self.mult)
         self.prior = (pm.rdp_weights27(self.cfg["vx"], self.cfg["vy"], self.cfg["vz"]), 0.1, 2.0, 1e-3)
 
 
@@ -93,6 +94,17 @@ def objective(d):
     return float(d.out)
 
 
+def counts_likelihood(d):
+    """Of the zero-count-aware subset gradient."""
+    d.pm.pet_subset_grad_counts(d.geom, d.counts, 0, d.x, d.sens, d.grad, d.out)
+    return float(d.out)
+
+
+def counts_objective(d):
+    d.pm.pet_objective_counts(d.geom, d.counts, d.x, d.sens, None, *d.prior, d.out)
+    return float(d.out)
+
+
 RECORDED = {
     ("prior_value", "mini_nontof"): "0x1.8fd248fe27c56p+7",
     ("prior_value_kappa", "mini_nontof"): "0x1.8a6e5f9411fe3p+7",
@@ -127,6 +139,19 @@ RECORDED = {
     ("likelihood", "mini_tof_psf"): "0x1.4b6248e306dcap+16",
     ("likelihood", "tof_2d"): "0x1.31294ea7915dcp+11",
     ("likelihood", "tof_wide"): "0x1.9c3851c1712bcp+21",
+    ("counts_likelihood", "mini_nontof"): "0x1.9a0dbcf33a84cp+12",
+    ("counts_objective", "mini_nontof"): "0x1.2312b7794a873p+14",
+    ("counts_likelihood", "mini_2d"): "0x1.0f9f0107f87fep+8",
+    ("counts_likelihood", "mini_tof"): "0x1.3e6c3838c5f04p+16",
+    ("counts_objective", "mini_tof"): "0x1.121b43c2ac869p+18",
+    ("counts_likelihood", "mini_tof_many"): "0x1.908782bb8977cp+18",
+    ("counts_objective", "mini_tof_many"): "0x1.5d852556ef30ap+20",
+    ("counts_likelihood", "mini_tof_seg40"): "0x1.dba2aaf9e0d86p+18",
+    ("counts_likelihood", "mini_tof_psf"): "0x1.43a3c41eeb914p+16",
+    ("counts_likelihood", "tof_2d"): "0x1.393686f309018p+11",
+    ("counts_likelihood", "tof_wide"): "0x1.96e7715d41ddcp+21",
+    ("counts_likelihood", "planes_1100"): "0x1.e6a3e25993cacp+16",
+    ("counts_likelihood", "slab"): "0x1.d1bd6181cb8c0p+13",
 }
 
 
