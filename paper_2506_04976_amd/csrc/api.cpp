@@ -55,7 +55,7 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.gather = g->gather;
     a.gchunk = g->gchunk;
     a.n_gchunk = g->n_gchunk;
-    a.gather_two = g->gather_two;
+    a.gather_planes = g->gather_planes;
     a.kappa = (float)g->kappa;
     a.inv_kappa = 1.0 / g->kappa;
     a.rho0 = g->ring0 + 1.0;

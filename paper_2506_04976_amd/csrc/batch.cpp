@@ -180,7 +180,7 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         if (m.is_tof) {
             b->form.n_tof = std::max(b->form.n_tof, (int)g->d.n_tof);
             b->form.nz = std::max(b->form.nz, (int)g->d.nz);
-            b->form.gather_two &= m.pa.gather_two != 0;
+            b->form.gather_two &= m.pa.gather_planes == 2;
         }
         m.nx = g->d.nx;
         m.ny = g->d.ny;

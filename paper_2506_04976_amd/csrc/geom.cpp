@@ -305,12 +305,12 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
             c.s0 = (int)hgather.size();
             c.p0 = part.front().p0;
             c.p1 = part.back().p0 + part.back().np;
-            int at = 1;  // (a zero before the first part; two after each)
+            int at = GATHER_ZEROS;  // (before the first part and after each)
             std::vector<int> qb(part.size());
             for (size_t i = 0; i < part.size(); ++i) {
                 for (int j = 0; j < part[i].np; ++j) hplanes[part[i].p0 + j].q = at + j;
                 qb[i] = at - 1 - part[i].off;
-                at += part[i].np + 2;
+                at += part[i].np + GATHER_ZEROS;
             }
             c.n_q = at;
             for (int neg = 0; neg < 2; ++neg) {
@@ -326,23 +326,23 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
             g->q_floats = std::max(g->q_floats, (at + 3) & ~3);
             part.clear();
         };
-        int used = 1;
+        int used = GATHER_ZEROS;
         for (const SegP &sg : gsegs)
             for (int off = 0; off < sg.np; off += GATHER_PLANES) {
                 const int np = std::min(GATHER_PLANES, sg.np - off);
-                if (used + np + 2 > cap) {
+                if (used + np + GATHER_ZEROS > cap) {
                     flush();
-                    used = 1;
+                    used = GATHER_ZEROS;
                 }
                 part.push_back({sg.p0 + off, np, planes[sg.p0].r2 - planes[sg.p0].r1, off});
-                used += np + 2;
+                used += np + GATHER_ZEROS;
             }
         flush();
     }
     g->n_gchunk = (int)hchunks.size();
-    g->gather_two = (float)g->kappa >= 1.f;
+    g->gather_planes = gather_form((float)g->kappa);
     for (const SegP &sg : gsegs)
-        if (sg.np > GATHER_PLANES) g->gather_two = 0;
+        if (sg.np > GATHER_PLANES) g->gather_planes = GATHER_MANY;
     g->rows_max = rows_max;
     // non-TOF: one thread per plane, in as many waves as the planes need (up to
     // 16; more resident waves hide the LDS latency of the sample loop)

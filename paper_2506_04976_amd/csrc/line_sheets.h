@@ -163,30 +163,61 @@ typedef const GatherSeg __attribute__((address_space(4))) *GatherSegList;
 // planes at most while the rings are no closer than the voxels (kappa >= 1):
 // their weights need no comparison, a plane that is too far gets the clamped
 // weight 0.
-__device__ __forceinline__ float gather_two(const float *Qs, const GatherSeg &G, float t, float kappa,
-                                            float one_minus_kappa) {
+__device__ __forceinline__ float gather_two(const float *Qs, const GatherSeg &G, float t, float kappa) {
     const float tc = __builtin_amdgcn_fmed3f(t, 0.f, G.hi);
     const float f = __builtin_amdgcn_fractf(tc);
     const float *q = Qs + G.qb + (int)tc;
     const float w0 = __builtin_amdgcn_fmed3f(fmaf(-kappa, f, 1.f), 0.f, 1.f);
-    const float w1 = __builtin_amdgcn_fmed3f(fmaf(kappa, f, one_minus_kappa), 0.f, 1.f);
+    const float w1 = __builtin_amdgcn_fmed3f(fmaf(kappa, f, 1.f - kappa), 0.f, 1.f);
     return fmaf(w1, q[1], w0 * q[0]);
+}
+
+// Three planes, the nearest and its neighbours, while a share reaches no further
+// than 3/2 rings (2/3 <= kappa; the nearest plane's weight is positive up to
+// kappa = 2).  t is shifted by GATHER_THREE more than in the other forms, so that
+// its truncation is the nearest plane.
+constexpr float GATHER_THREE = 1.5f;
+__device__ __forceinline__ float gather_three(const float *Qs, const GatherSeg &G, float t, float kappa) {
+    const float tc = __builtin_amdgcn_fmed3f(t, 0.5f, G.hi + 2.5f);
+    const float f = __builtin_amdgcn_fractf(tc);
+    const float *q = Qs + (G.qb - 2) + (int)tc;
+    const float w0 = __builtin_amdgcn_fmed3f(fmaf(-kappa, f, fmaf(-0.5f, kappa, 1.f)), 0.f, 1.f);
+    const float w1 = fmaf(-kappa, fabsf(f - 0.5f), 1.f);
+    const float w2 = __builtin_amdgcn_fmed3f(fmaf(kappa, f, fmaf(-1.5f, kappa, 1.f)), 0.f, 1.f);
+    return fmaf(w2, q[2], fmaf(w1, q[1], w0 * q[0]));
 }
 
 // Any kappa, and factors that are not finite: every plane within 1 / kappa,
 // planes of weight 0 left out.
-__device__ __forceinline__ float gather_many(const float *Qs, const GatherSeg &G, float t, float kappa) {
+__device__ __forceinline__ double gather_many(const float *Qs, const GatherSeg &G, float t, float kappa) {
     const float h = 1.f / kappa;
     // (clamped to the planes before the conversion; the margin covers the rounding of
     // t, a whole plane on both sides would double the planes of kappa just below 1)
     const float lo = fminf(fmaxf(ceilf(t - h - 1e-3f), G.lo + 1.f), G.hi);
     const float hi = fmaxf(fminf(floorf(t + h + 1e-3f), G.hi - 1.f), G.lo);
-    float s = 0.f;
+    double s = 0.0;
     for (int p = (int)lo; p <= (int)hi; ++p) {
         const float w = fmaf(-kappa, fabsf(t - (float)p), 1.f);
-        if (w > 0.f) s = fmaf(w, Qs[G.qb + p], s);
+        if (w > 0.f) s += (double)(w * Qs[G.qb + p]);
     }
     return s;
+}
+
+// PLANES: 2, 3 or GATHER_MANY (see the three forms).
+template <int PLANES>
+__device__ __forceinline__ auto gather_planes(const float *Qs, const GatherSeg &G, float t, float kappa) {
+    if constexpr (PLANES == 2)
+        return gather_two(Qs, G, t, kappa);
+    else if constexpr (PLANES == 3)
+        return gather_three(Qs, G, t, kappa);
+    else
+        return gather_many(Qs, G, t, kappa);
+}
+
+// Shifted position of voxel z before the segment's part, in the form's shift.
+template <int PLANES>
+__device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
+    return (float)fma((double)z, a.inv_kappa, a.rho0 + (PLANES == 3 ? (double)GATHER_THREE : 0.0));
 }
 
 // Backprojection of one chunk of planes of a non-TOF line from their factors
@@ -195,39 +226,41 @@ __device__ __forceinline__ float gather_many(const float *Qs, const GatherSeg &G
 // FP64 and spreads the sum over the two transaxial neighbours.  No sheet, no LDS
 // atomics.
 //
-// Bound by VALU issue: 12 instructions per cell and segment (position, clamp,
-// fraction and cell, two weights, two products, FP64 add) against one two-word
-// LDS read.  A scatter instead adds two shares per sample with FP64 LDS atomics
-// into a sheet of doubles, which took 77 KB and left one workgroup per CU:
-// backprojection of a 10-view subset of the 128x128x71, 2204-plane geometry
-// 397 us against 157 us, its fused gradient 603 against 387 us, the TOF
-// sensitivity over all 252 views 7.6 against 3.8 ms.
+// Bound by VALU issue: 13 instructions per cell and segment (position, clamp,
+// fraction and cell, two weights, two products, FP64 conversion and add) against one
+// two-word LDS read; 17 with three planes.  A scatter instead adds two shares per
+// sample with FP64 LDS atomics into a sheet of doubles, which took 77 KB and left
+// one workgroup per CU: backprojection of a 10-view subset of the 128x128x71,
+// 2204-plane geometry 397 us (now 146), its fused gradient 603 (303), the TOF
+// sensitivity over all 252 views 7.6 ms (3.4).  The forms' lines: with kappa just
+// below 1, the loop of gather_many takes 65.7 us for a gradient of 96 x 96 x 32
+// voxels at kappa 0.9, three fixed planes 51.6, the scatter 76; at kappa 0.6 and 0.2
+// the loop takes 71 and 121, the scatter 87 and 191.
 //
 // fold (a TOF geometry's mult alone): every sample carries the sum of its TOF
 // bins' weights, a function of the row and the segment's length.  Where every
 // row of a wave lies far enough inside the bins for all segments, that sum is
 // one constant; elsewhere it is evaluated per share.
-template <bool MANY, bool FOLD, typename Fold>
+template <int PLANES, bool FOLD, typename Fold>
 __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, int nrow, const float *Qs,
                                              const GatherChunk &ch, int64_t g_off, const Fold &fold, int tid) {
     const int nz = a.nz, rz = a.rz;
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
     const GatherSegList segs = (GatherSegList)(uintptr_t)a.gather;
-    const float kappa = a.kappa, omk = 1.f - a.kappa;
+    const float kappa = a.kappa;
     const int dr = (int)blockDim.x / nz, dz = (int)blockDim.x - dr * nz;
     int r = tid / nz, z = tid - r * nz;
     while (r < nrow) {
         const float lam = fmaf((float)(L.i_lo + r), L.dlam, L.lam0);
-        const float rho = (float)fma((double)z, a.inv_kappa, a.rho0);
+        const float rho = gather_rho<PLANES>(a, z);
         double acc = 0.0;
         auto run = [&](int s0, int s1, float slope, auto each) {
 #pragma unroll 4
             for (int s = s0; s < s1; ++s) {
                 const GatherSeg G = {segs[s].k, segs[s].lo, segs[s].hi, segs[s].qb};
                 const float t = fmaf(-slope, G.k, rho);
-                const float v = MANY ? gather_many(Qs, G, t, kappa) : gather_two(Qs, G, t, kappa, omk);
-                acc += (double)each(v, G.k);
+                acc += (double)each(gather_planes<PLANES>(Qs, G, t, kappa), G.k);
             }
         };
         auto both = [&](auto each) {
@@ -235,9 +268,9 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
             run(ch.s_neg, ch.s1, 1.f - lam, each);
         };
         if (FOLD && !__all(fold.constant(lam))) {
-            both([&](float v, float k) { return v * fold.weight(lam, k); });
+            both([&](auto v, float k) { return v * fold.weight(lam, k); });
         } else {
-            both([](float v, float) { return v; });
+            both([](auto v, float) { return v; });
             if (FOLD) acc *= (double)fold.inside();
         }
         const float val = (float)acc;

@@ -62,7 +62,7 @@ struct SegP {
 // 1 - lambda.
 //
 // One segment, or at most GATHER_PLANES planes of one: its factors lie in LDS at
-// Qs[qb + lo + 1 ..], zeros around them (one before, two after); positions are
+// Qs[qb + lo + 1 ..], GATHER_ZEROS zeros before and after them; positions are
 // shifted by one, so that a truncation is the floor.
 struct GatherSeg {
     float k;       // |d|
@@ -78,12 +78,19 @@ struct GatherChunk {
     int32_t n_q;     // floats of their LDS region
 };
 constexpr int GATHER_PLANES = 1024;
+constexpr int GATHER_ZEROS = 3;
+// Planes of a segment that may reach a voxel, the forms of the gather: two, three or
+// any number (see line_sheets.h)
+constexpr int GATHER_MANY = 0;
+__host__ __device__ inline int gather_form(float kappa) {
+    return kappa >= 1.f ? 2 : kappa >= 0.6667f ? 3 : GATHER_MANY;
+}
 
 // ---- TOF line kernels --------------------------------------------------------
 // One unit of a TOF line: a segment, or a pair -k, +k whose planes fit in 64
 // lanes (same |u|, so the same TOF weights).  Its first n1 planes are the first
-// segment (all of them if it has one); in a staged row of the adjoint they are
-// columns 1 .. n1, the second segment's n1 + 3 .., zeros between.
+// segment (all of them if it has one); in a staged row of the adjoint they follow
+// GATHER_ZEROS zeros, and the second segment's as many more.
 struct TofUnit {
     int32_t p0;
     uint8_t np, n1, neg, pad;  // planes; of the first segment; its ring difference is negative
@@ -146,7 +153,7 @@ struct ProjArgs {
     const GatherSeg *gather;
     const GatherChunk *gchunk;
     int n_gchunk;
-    int gather_two;             // two planes per voxel and segment at most, segments whole (see gather_two)
+    int gather_planes;          // form of the gather: 2 or 3 planes (segments whole) or GATHER_MANY
     float kappa;                // ring pitch / vz
     double inv_kappa, rho0;     // shifted position of voxel z before the segment's part: z inv_kappa + rho0
     float pitch2, k_max;        // squared ring pitch, largest ring difference
@@ -284,7 +291,7 @@ struct pet_geom_s {
     int n_gseg = 0;
     pet::GatherSeg *gather = nullptr;   // axial gather of the adjoint: segments by chunk, and the chunks
     pet::GatherChunk *gchunk = nullptr;
-    int n_gchunk = 0, gather_two = 0, q_floats = 0;     // chunks; LDS floats of the largest one's factors
+    int n_gchunk = 0, gather_planes = 0, q_floats = 0;  // chunks; form; LDS floats of the largest one's factors
     double kappa = 1.0, ring0 = 0.0;    // ring pitch / vz; position of voxel 0 in rings, negated
     int rows_max = 0;
     pet::TofUnit *units = nullptr;      // TOF line kernels

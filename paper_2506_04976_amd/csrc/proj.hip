@@ -26,6 +26,11 @@
 namespace pet {
 namespace {
 
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+
 // The lane index, opaque: what follows from it is formed where it is used and not
 // kept in registers across the other phases (which need all 128 of them).
 __device__ __forceinline__ int lane_here() {
@@ -190,19 +195,21 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         if (!NEED_Z) continue;
         __syncthreads();
         if (nrow <= 0) continue;
-        const bool many = s_special || !a.gather_two;  // (uniform)
+        const int form = s_special ? GATHER_MANY : a.gather_planes;  // (uniform)
         const LineFold F(a, L);
-        if (MODE == M_BACK && a.tof_fold) {
-            if (many)
-                gather_cells<true, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F, tid);
+        auto cells = [&](auto fold) {
+            constexpr bool FOLD = fold.value != 0;
+            if (form == 2)
+                gather_cells<2, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+            else if (form == 3)
+                gather_cells<3, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
             else
-                gather_cells<false, MODE == M_BACK>(a, L, nrow, Qs, ch, g_off, F, tid);
-        } else {
-            if (many)
-                gather_cells<true, false>(a, L, nrow, Qs, ch, g_off, F, tid);
-            else
-                gather_cells<false, false>(a, L, nrow, Qs, ch, g_off, F, tid);
-        }
+                gather_cells<GATHER_MANY, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+        };
+        if (MODE == M_BACK && a.tof_fold)
+            cells(Int<MODE == M_BACK>());
+        else
+            cells(Int<0>());
     }
     return kl;
 }
@@ -256,10 +263,6 @@ __global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
 //
 // Lane layouts of the 16x16x4 instruction: A[m][k] in lane 16 k + m, B[k][n] in
 // lane 16 k + n, D[m][n] in register m mod 4 of lane 16 (m / 4) + n.
-template <int V>
-struct Int {
-    static constexpr int value = V;
-};
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef const TofUnit __attribute__((address_space(4))) *TofUnitList;
 
@@ -491,7 +494,7 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
         rho[zb] = (float)fma((double)(z0 + 16 * zb + (lane_here() & 15)), a.inv_kappa, a.rho0);
         __builtin_amdgcn_sched_barrier(0);  // (one by one: registers)
     }
-    const float last = (float)a.n_etab, kappa = a.kappa, omk = 1.f - a.kappa;
+    const float last = (float)a.n_etab, kappa = a.kappa;
     float w[KEEP_KK], w_dz2 = -1.f;
 #pragma unroll
     for (int q = 0; q < KEEP_KK; ++q) w[q] = 0.f;
@@ -598,7 +601,7 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
 #pragma unroll
                 for (int zb = 0; zb < NZB; ++zb) {
                     const float t = fmaf(-slope, G.k, rho[zb]);
-                    v[zb] = MANY ? gather_many(srow, G, t, kappa) : gather_two(srow, G, t, kappa, omk);
+                    v[zb] = MANY ? (float)gather_many(srow, G, t, kappa) : gather_two(srow, G, t, kappa);
                 }
 #pragma unroll
                 for (int zb = 0; zb < NZB; ++zb) acc[h][zb] += (double)v[zb];
@@ -1084,7 +1087,7 @@ hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStr
     } else {
         if (MODE == M_GRAD && a.partial) return launch_tof_walk(g, M_GRAD, grid, a, s);
         hipError_t e = hipSuccess;
-        tof_form(a.tof.n_tof, a.nz, a.gather_two, [&](auto mb, auto nzb, auto many) {
+        tof_form(a.tof.n_tof, a.nz, a.gather_planes == 2, [&](auto mb, auto nzb, auto many) {
             // (without an adjoint the last two make no difference)
             if constexpr (MODE == M_FWD)
                 e = launch_tof<MODE, mb.value, STAGE_ZB, false>(g, grid, a, s);
