@@ -144,6 +144,7 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
     b->device = geoms[0]->device;
     hipError_t e = hipSetDevice(b->device);
     std::vector<BMember> hm(n_members);
+    double kappa_min = 1.0, kappa_max = 1.0;  // of the TOF members
     for (int r = 0; r < n_members && e == hipSuccess; ++r) {
         pet_geom g = geoms[r];
         const pet_svrg_state *st = states[r];
@@ -180,7 +181,9 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         if (m.is_tof) {
             b->form.n_tof = std::max(b->form.n_tof, (int)g->d.n_tof);
             b->form.nz = std::max(b->form.nz, (int)g->d.nz);
-            b->form.gather_two &= m.pa.gather_planes == 2;
+            kappa_min = std::min(kappa_min, g->kappa);
+            kappa_max = std::max(kappa_max, g->kappa);
+            if (m.pa.gather_planes == GATHER_SOME) b->form.planes = GATHER_SOME;
         }
         m.nx = g->d.nx;
         m.ny = g->d.ny;
@@ -217,6 +220,8 @@ extern "C" pet_status pet_batch_create(const pet_geom *geoms, pet_svrg_state *co
         b->lds_per_wave.push_back(m.is_tof ? TOF_STAGE_FLOATS * sizeof(float) : 0);
         b->line_cost.push_back((double)g->n_planes * g->rows_max * (m.is_tof ? 4.0 : 1.0));
     }
+    // (three planes serve the members of the two-plane form as well, up to a pitch of two voxels)
+    if (b->form.planes == 2 && kappa_min < 1.0) b->form.planes = kappa_max <= 2.0 ? 3 : GATHER_SOME;
     if (e == hipSuccess) e = hipMalloc(&b->d_steps, sizeof(BStep) * (size_t)n_members * b->max_steps);
     if (e == hipSuccess) e = hipHostMalloc(&b->h_steps, sizeof(BStep) * (size_t)n_members * b->max_steps);
     for (int r = 0; r < n_members && e == hipSuccess; ++r) hm[r].steps = b->d_steps + (size_t)r * b->max_steps;

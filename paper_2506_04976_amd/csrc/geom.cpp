@@ -342,7 +342,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     g->n_gchunk = (int)hchunks.size();
     g->gather_planes = gather_form((float)g->kappa);
     for (const SegP &sg : gsegs)
-        if (sg.np > GATHER_PLANES) g->gather_planes = GATHER_MANY;
+        if (sg.np > GATHER_PLANES) g->gather_planes = GATHER_SOME;
     g->rows_max = rows_max;
     // non-TOF: one thread per plane, in as many waves as the planes need (up to
     // 16; more resident waves hide the LDS latency of the sample loop)

@@ -187,8 +187,29 @@ __device__ __forceinline__ float gather_three(const float *Qs, const GatherSeg &
     return fmaf(w2, q[2], fmaf(w1, q[1], w0 * q[0]));
 }
 
-// Any kappa, and factors that are not finite: every plane within 1 / kappa,
-// planes of weight 0 left out.
+// Any kappa: a window of as many planes as a share can reach (the whole segment if
+// that is shorter), weights clamped at 0.  The window has the same length in every
+// lane, so that the loop does not diverge and its LDS reads are in flight together;
+// four planes' shares are added in 32 bits, the sums in 64.
+__device__ __forceinline__ double gather_some(const float *Qs, const GatherSeg &G, float t, float kappa) {
+    const float h = 1.f / kappa, n = fminf(ceilf(2.f * h), G.hi - G.lo - 1.f);
+    const float first = __builtin_amdgcn_fmed3f(ceilf(t - h), G.lo + 1.f, G.hi - n);
+    const float *q = Qs + G.qb + (int)first;
+    auto share = [&](float d, float v, float s) {
+        return fmaf(__builtin_amdgcn_fmed3f(fmaf(-kappa, fabsf(d), 1.f), 0.f, 1.f), v, s);
+    };
+    float d = t - first;
+    double s = 0.0;
+    int k = (int)n;
+    for (; k >= 4; k -= 4, d -= 4.f, q += 4) {
+        const float q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+        s += (double)share(d - 3.f, q3, share(d - 2.f, q2, share(d - 1.f, q1, share(d, q0, 0.f))));
+    }
+    for (; k > 0; --k, d -= 1.f, ++q) s += (double)share(d, *q, 0.f);
+    return s;
+}
+
+// Factors that are not finite: planes of weight 0 are left out.
 __device__ __forceinline__ double gather_many(const float *Qs, const GatherSeg &G, float t, float kappa) {
     const float h = 1.f / kappa;
     // (clamped to the planes before the conversion; the margin covers the rounding of
@@ -203,13 +224,15 @@ __device__ __forceinline__ double gather_many(const float *Qs, const GatherSeg &
     return s;
 }
 
-// PLANES: 2, 3 or GATHER_MANY (see the three forms).
+// PLANES: 2, 3, GATHER_SOME or GATHER_MANY (the forms above in their order).
 template <int PLANES>
 __device__ __forceinline__ auto gather_planes(const float *Qs, const GatherSeg &G, float t, float kappa) {
     if constexpr (PLANES == 2)
         return gather_two(Qs, G, t, kappa);
     else if constexpr (PLANES == 3)
         return gather_three(Qs, G, t, kappa);
+    else if constexpr (PLANES == GATHER_SOME)
+        return gather_some(Qs, G, t, kappa);
     else
         return gather_many(Qs, G, t, kappa);
 }
@@ -256,7 +279,8 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
         const float rho = gather_rho<PLANES>(a, z);
         double acc = 0.0;
         auto run = [&](int s0, int s1, float slope, auto each) {
-#pragma unroll 4
+            constexpr int UNROLL = PLANES == 2 || PLANES == 3 ? 4 : 1;
+#pragma unroll UNROLL
             for (int s = s0; s < s1; ++s) {
                 const GatherSeg G = {segs[s].k, segs[s].lo, segs[s].hi, segs[s].qb};
                 const float t = fmaf(-slope, G.k, rho);

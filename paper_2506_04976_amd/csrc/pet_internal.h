@@ -80,11 +80,9 @@ struct GatherChunk {
 constexpr int GATHER_PLANES = 1024;
 constexpr int GATHER_ZEROS = 3;
 // Planes of a segment that may reach a voxel, the forms of the gather: two, three or
-// any number (see line_sheets.h)
-constexpr int GATHER_MANY = 0;
-__host__ __device__ inline int gather_form(float kappa) {
-    return kappa >= 1.f ? 2 : kappa >= 0.6667f ? 3 : GATHER_MANY;
-}
+// any number, and the one for factors that are not finite (see line_sheets.h)
+constexpr int GATHER_SOME = 4, GATHER_MANY = 0;
+inline int gather_form(float kappa) { return kappa >= 1.f ? 2 : kappa >= 0.6667f ? 3 : GATHER_SOME; }
 
 // ---- TOF line kernels --------------------------------------------------------
 // One unit of a TOF line: a segment, or a pair -k, +k whose planes fit in 64
@@ -153,10 +151,11 @@ struct ProjArgs {
     const GatherSeg *gather;
     const GatherChunk *gchunk;
     int n_gchunk;
-    int gather_planes;          // form of the gather: 2 or 3 planes (segments whole) or GATHER_MANY
+    int gather_planes;          // form of the gather: 2 or 3 planes (segments whole) or GATHER_SOME
     float kappa;                // ring pitch / vz
     double inv_kappa, rho0;     // shifted position of voxel z before the segment's part: z inv_kappa + rho0
     float pitch2, k_max;        // squared ring pitch, largest ring difference
+    int em;                     // TOF M_GRAD: the EM ratio's factors instead of the gradient's
     // TOF line kernels: units; bins per block of 16 matrix rows; units whose
     // factors are in LDS together and the floats of each; cubics of the halved
     // clamped erf, [0, n_etab] (position = distance * e_scale + e_mid, one bin
@@ -383,7 +382,7 @@ hipError_t launch_tof_walk(const pet_geom_s *g, int mode, dim3 grid, const ProjA
 // (f: what its TOF members need at most)
 struct BatchForm {
     int n_tof = 1, nz = 1;
-    bool gather_two = true;
+    int planes = 2;  // form of the gather
 };
 hipError_t launch_line_batched(const BatchForm &f, const BMember *mem, const int *order, int n_mem, int step,
                                int *counter, int blocks, int waves, size_t lds, hipStream_t s);

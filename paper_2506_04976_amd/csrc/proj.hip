@@ -203,6 +203,8 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
                 gather_cells<2, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
             else if (form == 3)
                 gather_cells<3, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+            else if (form == GATHER_SOME)
+                gather_cells<GATHER_SOME, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
             else
                 gather_cells<GATHER_MANY, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
         };
@@ -452,10 +454,14 @@ __device__ __forceinline__ void load_counts(const void *y, int dt, int64_t base,
 // LDS of a wave of the adjoint: 4 rows of a unit's planes (at most 64, with the
 // zeros around its two segments), 16 banks apart.
 constexpr int STAGE_COLS = 80, STAGE_ROWS = 4;
+static_assert(64 + 3 * GATHER_ZEROS <= STAGE_COLS, "a unit's planes and the zeros around its segments");
 static_assert(TOF_STAGE_FLOATS == STAGE_COLS * STAGE_ROWS, "LDS layout of the TOF line kernels");
-// Voxels along z of one pass of the adjoint: STAGE_ZB groups of 16.
+// Voxels along z of one pass of the adjoint: at most STAGE_ZB groups of 16.
 constexpr int STAGE_ZB = 5;
 static_assert(16 * STAGE_ZB <= STAGE_COLS, "the finished cells leave through the staged rows");
+// Lines of a launch up to which its workgroups share the chip with no others (two
+// to a CU).
+constexpr unsigned FEW_LINES = 512;
 // Groups of four bins whose weights a wave of the adjoint keeps for a pair of
 // segments of the same length.
 constexpr int KEEP_KK = 3;
@@ -483,7 +489,7 @@ struct TofBack {
 // the 16 rows x 64 planes of Q (one matrix product per 16 planes and group of
 // bins), which pass through the wave's four LDS rows; the products of the next
 // unit are under way while the last rows of this one are gathered.
-template <int NZB, bool MANY>
+template <int NZB, int PLANES>
 __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L, const TofBack &k, int z0,
                                               double (&acc)[4][NZB]) {
     const TofUnitList units = (TofUnitList)(uintptr_t)a.units;
@@ -491,7 +497,7 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
     float rho[NZB];
 #pragma unroll
     for (int zb = 0; zb < NZB; ++zb) {
-        rho[zb] = (float)fma((double)(z0 + 16 * zb + (lane_here() & 15)), a.inv_kappa, a.rho0);
+        rho[zb] = gather_rho<PLANES>(a, z0 + 16 * zb + (lane_here() & 15));
         __builtin_amdgcn_sched_barrier(0);  // (one by one: registers)
     }
     const float last = (float)a.n_etab, kappa = a.kappa;
@@ -543,26 +549,26 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
     };
     auto products = [&](int u) {
         const float dz2 = units[u].dz2;
-        const bool two = units[u].np <= 32;
+        const int np = units[u].np;
         // (segments -k and +k are neighbours: the same length, the same weights)
         const bool fresh = dz2 != w_dz2;
         w_dz2 = dz2;
-        if (k.nkk == 2 && !two) {
+        auto all = [&](auto tiles) {
+            groups(tiles, Int<2>(), Int<1>(), u, 0, true);
+            for (int kc = 2; kc < k.nkk; kc += 2) groups(tiles, Int<2>(), Int<0>(), u, kc, true);
+            w_dz2 = -1.f;
+        };
+        if (np <= 32)
+            all(Int<2>());
+        else if (k.nkk == 2)
             groups(Int<4>(), Int<2>(), Int<1>(), u, 0, fresh);
-        } else if (k.nkk == 3 && !two) {
+        else if (k.nkk == 3)
             groups(Int<4>(), Int<3>(), Int<1>(), u, 0, fresh);
-        } else if (two) {
-            groups(Int<2>(), Int<2>(), Int<1>(), u, 0, true);
-            for (int kc = 2; kc < k.nkk; kc += 2) groups(Int<2>(), Int<2>(), Int<0>(), u, kc, true);
-            w_dz2 = -1.f;
-        } else {
-            groups(Int<4>(), Int<2>(), Int<1>(), u, 0, true);
-            for (int kc = 2; kc < k.nkk; kc += 2) groups(Int<4>(), Int<2>(), Int<0>(), u, kc, true);
-            w_dz2 = -1.f;
-        }
+        else
+            all(Int<4>());
     };
 
-    if ((lane_here() & 15) == 0) k.stage[(lane_here() >> 4) * STAGE_COLS] = 0.f;
+    if ((lane_here() & 15) < GATHER_ZEROS) k.stage[(lane_here() >> 4) * STAGE_COLS + (lane_here() & 15)] = 0.f;
     products(k.u0);
     for (int u = k.u0; u < k.u1; ++u) {
         const int np = units[u].np, n1 = units[u].n1, neg = units[u].neg;
@@ -576,15 +582,16 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
         float *col[4];
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb) {
-            int c = g * STAGE_COLS + 16 * pb + pl + (n1 == np || 16 * pb + pl < n1 ? 1 : 3);
+            int c = g * STAGE_COLS + 16 * pb + pl + (n1 == np || 16 * pb + pl < n1 ? 1 : 2) * GATHER_ZEROS;
             asm volatile("" : "+v"(c));
             col[pb] = k.stage + c;
         }
         wave_lds_order();
-        // The zeros between and after the segments (column 0 keeps its zero; the
-        // planes that fill up the last tile are zeros too, two of them are enough
-        // after a single segment).
-        if ((n1 < np || 16 * npb < np + 2) && pl < 4) srow[pl < 2 ? n1 + 1 + pl : np + 1 + pl] = 0.f;
+        // The zeros between and after the segments (those before stay; the planes that
+        // fill up the last tile are zeros too, three of them are enough after a single
+        // segment).
+        if ((n1 < np || 16 * npb < np + GATHER_ZEROS) && (pl & 3) < GATHER_ZEROS && pl < 8)
+            srow[(pl < 4 ? n1 + GATHER_ZEROS : np + 2 * GATHER_ZEROS) + (pl & 3)] = 0.f;
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
             wave_lds_order();
@@ -597,17 +604,15 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
             __builtin_amdgcn_sched_barrier(0);
             const float lam = fmaf((float)h, L.dlam, lam_g);
             auto segment = [&](const GatherSeg &G, float slope) {
-                float v[NZB];
+                decltype(gather_planes<PLANES>(srow, G, 0.f, kappa)) v[NZB];
 #pragma unroll
-                for (int zb = 0; zb < NZB; ++zb) {
-                    const float t = fmaf(-slope, G.k, rho[zb]);
-                    v[zb] = MANY ? (float)gather_many(srow, G, t, kappa) : gather_two(srow, G, t, kappa);
-                }
+                for (int zb = 0; zb < NZB; ++zb)
+                    v[zb] = gather_planes<PLANES>(srow, G, fmaf(-slope, G.k, rho[zb]), kappa);
 #pragma unroll
                 for (int zb = 0; zb < NZB; ++zb) acc[h][zb] += (double)v[zb];
             };
-            segment({rd, 0.f, (float)(n1 + 1), 0}, neg ? 1.f - lam : lam);
-            if (n1 < np) segment({rd, 0.f, (float)(np - n1 + 1), n1 + 2}, lam);
+            segment({rd, 0.f, (float)(n1 + 1), GATHER_ZEROS - 1}, neg ? 1.f - lam : lam);
+            if (n1 < np) segment({rd, 0.f, (float)(np - n1 + 1), n1 + 2 * GATHER_ZEROS - 1}, lam);
         }
     }
 }
@@ -636,16 +641,16 @@ __device__ __forceinline__ void tof_line_outside(const ProjArgs &a, int line, in
 }
 
 // What the adjoint spreads of a bin: m its factor, s its projection, v the
-// additive term (M_HVP: the mean data, M_BACK: the data), y its counts.
+// additive term (M_HVP: the mean data, M_BACK: the data), y its counts.  em: the EM
+// ratio instead of the gradient's factor.
 template <int MODE>
-__device__ __forceinline__ float tof_factor(float m, float s, float v, float y, float ell) {
+__device__ __forceinline__ float tof_factor(bool em, float m, float s, float v, float y, float ell) {
     if constexpr (MODE == M_BACK) return v * m * ell;
     // data-term Hessian: mult^2 y / ybar^2 (P v), then back
     if constexpr (MODE == M_HVP) return y != 0.f ? m * m * y / (v * v) * s * ell : 0.f;
     // a bin without counts: derivative 1, EM ratio 0
-    const float ri = __builtin_amdgcn_rcpf(fmaf(m, s, v));
-    if constexpr (MODE == M_EM) return y != 0.f ? m * (y * ri) * ell : 0.f;
-    return m * (y != 0.f ? fmaf(-y, ri, 1.f) : 1.f) * ell;
+    const float ri = __builtin_amdgcn_rcpf(fmaf(m, s, v)), one = em ? 0.f : 1.f;
+    return m * (y != 0.f ? fmaf(em ? y : -y, ri, one) : one) * ell;
 }
 
 // A value that is the same in all lanes, in a scalar register.
@@ -654,14 +659,14 @@ __device__ __forceinline__ float uniform(float v) {
 }
 
 // One transaxial line of a TOF geometry by the whole workgroup (the likelihood has
-// kernels of its own, walk.hip).  The adjoint takes 16 NZB voxels along z at a
-// time; MANY: more than two planes of a segment may reach a voxel; TILES: the
-// forward takes that many tiles of 16 planes at a time (16 registers of sums with
-// four tiles or two blocks of bins).
-template <int MODE, int MB, int NZB, bool MANY, int TILES>
+// kernels of its own, walk.hip).  MB blocks of 16 bins; the adjoint takes 16 NZB
+// voxels along z at a time and gathers with the form PLANES; the forward takes
+// TILES tiles of 16 planes at a time (16 registers of sums with four tiles or two
+// blocks of bins).
+template <int MODE, int MB, int NZB, int PLANES, int TILES>
 __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float *smem, int wave, int64_t g_off = 0) {
     constexpr bool NEED_X = MODE != M_BACK;
-    constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
+    constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_HVP;
     const int nw = blockDim.x >> 6;
     const LineP L = scalar_ref(a.lines[line]);
     const int nrow = L.i_hi - L.i_lo + 1;
@@ -716,7 +721,23 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
         }
     }
 
+    // A line of few blocks of rows deals each block to several waves, which take shares
+    // of the units and spread their cells by themselves: gradient of 161 x 161 x 33
+    // voxels, 25 bins, 17 units 589 -> 546 us, of 128 x 128 x 71, 13 bins, 41 units
+    // 874 -> 795.  Shares of one unit cost more in the spreading than they gain
+    // (backprojection of 96 x 96 x 5 voxels, three units, 38.5 -> 42.5 us) unless the
+    // lines leave the chip idle, as do those of a group of units where the cells leave
+    // per group.
     const int nblk = NEED_Z ? (nrow + 15) >> 4 : 0;
+    int lg_parts = 0, part = 0, rb0 = wave;
+    if (NEED_Z && a.nz <= 16 * NZB) {
+        const int least = gridDim.x > FEW_LINES ? 2 : 1;  // units of a share
+        while ((nblk << (lg_parts + 1)) <= nw && min(a.q_units, a.n_units) >> (lg_parts + 1) >= least) ++lg_parts;
+        while (rb0 >= nblk && part + 1 < 1 << lg_parts) {
+            rb0 -= nblk;
+            ++part;
+        }
+    }
     const int nzc = (a.nz + 16 * NZB - 1) / (16 * NZB);
     // a wave's cells stay in its registers over the groups of units if it has
     // one block of rows and one pass along z; else they are spread per group
@@ -839,7 +860,7 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                         const float s = D[mb][pb][r] * tp.ell;
                         float Q = 0.f;
                         if constexpr (MODE == M_FWD) v[pb][r] = fmaf(m[pb], s, v[pb][r]);
-                        if constexpr (NEED_Z) Q = tof_factor<MODE>(m[pb], s, v[pb][r], yv[pb][r], tp.ell);
+                        if constexpr (NEED_Z) Q = tof_factor<MODE>(a.em, m[pb], s, v[pb][r], yv[pb][r], tp.ell);
                         if (NEED_Z) {
                             if (!has) Q = 0.f;
                             top += fabsf(Q);
@@ -864,7 +885,7 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                     if (NEED_X) {
                         const float s = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b) * tp.ell;
                         const float v = MODE == M_HVP ? a.ybar[base + e] : a.add ? a.add[base + e] : 0.f;
-                        Q = tof_factor<MODE>(a.mult ? a.mult[lor0 + idx] : 1.f, s, v, load_y(a.y, a.y_dtype, base + e), tp.ell);
+                        Q = tof_factor<MODE>(a.em, a.mult ? a.mult[lor0 + idx] : 1.f, s, v, load_y(a.y, a.y_dtype, base + e), tp.ell);
                     }
                     if (fabsf(Q) < INFINITY) {
                         *f = Q;
@@ -881,7 +902,8 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
         // ---- adjoint, one block of 16 rows per wave ----
         for (int iz = 0; iz < nzc; ++iz) {
             const int z0 = 16 * NZB * iz;
-            for (int rb = wave; rb < nblk; rb += nw) {
+            for (int rb = rb0; rb < nblk; rb += nw) {
+                const int ua = u0 + ((u1 - u0) * part >> lg_parts), ub = u0 + ((u1 - u0) * (part + 1) >> lg_parts);
                 if (!keep) {
 #pragma unroll
                     for (int h = 0; h < 4; ++h)
@@ -898,9 +920,9 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
                 const int b1 = (int)fmaxf(fminf(ceilf((t1 + sup - a.tof.tb[0]) * rbw + 0.01f), (float)(nt - 1)), -1.f);
                 const int kk0 = __builtin_amdgcn_readfirstlane(b0) >> 2;
                 const int nkk = (__builtin_amdgcn_readfirstlane(b1) >> 2) + 1 - kk0;
-                if (nkk > 0) {
-                    const TofBack k = {Fs, stage, utab, tab, u0, u1, rb, kk0, nkk};
-                    tof_back_rows<NZB, MANY>(a, L, k, z0, acc);
+                if (nkk > 0 && ua < ub) {
+                    const TofBack k = {Fs + (ua - u0) * a.unit_floats, stage, utab, tab, ua, ub, rb, kk0, nkk};
+                    tof_back_rows<NZB, PLANES>(a, L, k, z0, acc);
                 }
                 if (!keep || u1 == a.n_units) {
                     // the cells to the global sheet, through the staged rows so that
@@ -934,11 +956,11 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
 }
 
 // One line per workgroup, in the order a.order (longest first).
-template <int MODE, int MB, int NZB, bool MANY>
+template <int MODE, int MB, int NZB, int PLANES>
 __global__ void __launch_bounds__(TOF_BLOCK, MODE == M_FWD && MB == 1 ? 8 : 4) k_line_tof(ProjArgs a) {
     extern __shared__ float4 smem4[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    line_tof_body<MODE, MB, NZB, MANY, MB == 1 ? 4 : 2>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), wave);
+    line_tof_body<MODE, MB, NZB, PLANES, MB == 1 ? 4 : 2>(a, a.order[blockIdx.x], reinterpret_cast<float *>(smem4), wave);
 }
 
 // Work counts of a TOF line: samples, and sample-bin pairs within the bins'
@@ -968,21 +990,37 @@ __global__ void __launch_bounds__(NT_BLOCK) k_count_tof(ProjArgs a) {
     block_sums(samples, pairs, a.partial, true);
 }
 
-// The form of the TOF kernels that serves a geometry: one or two blocks of 16 bins
-// (a second, empty one would cost as many weights and products as the first); 48 or
-// 80 voxels along z per pass of the adjoint (the cells past a shorter axis are
-// gathered for nothing: with 33 slices and 25 bins a subset gradient takes 690 us
-// in the longer form and 601 in the shorter one, with 32 slices and 13 bins 118
-// and 109); two planes of a segment per voxel at most, or any number.
+// The form of the TOF kernels that serves a geometry:
+//  * one or two blocks of 16 bins (a second, empty one would cost as many weights
+//    and products as the first);
+//  * 16 to 80 voxels along z per pass of the adjoint, so that passes and cells past
+//    the axis, gathered for nothing, cost least (each pass forms the products of all
+//    units, worth 1.3 groups of 16 voxels): gradient of 33 slices and 25 bins, 690 us
+//    in passes of 80, 601 of 48; of 16 slices and 13 bins, 78 of 48, 68 of 16;
+//  * two or three planes of a segment per voxel, or any number (see line_sheets.h).
 template <typename F>
-void tof_form(int n_tof, int nz, bool gather_two, F &&f) {
-    const bool one = n_tof <= 16;
-    if (!gather_two)
-        one ? f(Int<1>(), Int<STAGE_ZB>(), Int<1>()) : f(Int<2>(), Int<STAGE_ZB>(), Int<1>());
-    else if (nz <= 48)
-        one ? f(Int<1>(), Int<3>(), Int<0>()) : f(Int<2>(), Int<3>(), Int<0>());
+void tof_form(int n_tof, int nz, int planes, F &&f) {
+    auto bins = [&](auto nzb, auto pl) { n_tof <= 16 ? f(Int<1>(), nzb, pl) : f(Int<2>(), nzb, pl); };
+    const int groups = (nz + 15) / 16;
+    auto slices = [&](auto pl) {
+        auto cost = [&](int n) { return (groups + n - 1) / n * (10 * n + 13); };
+        int best = 1;
+        for (int n = 2; n <= STAGE_ZB; ++n)
+            if (cost(n) < cost(best)) best = n;
+        switch (best) {
+            case 1: bins(Int<1>(), pl); break;
+            case 2: bins(Int<2>(), pl); break;
+            case 3: bins(Int<3>(), pl); break;
+            case 4: bins(Int<4>(), pl); break;
+            default: bins(Int<STAGE_ZB>(), pl);
+        }
+    };
+    if (planes == 2)
+        slices(Int<2>());
+    else if (planes == 3)
+        slices(Int<3>());
     else
-        one ? f(Int<1>(), Int<STAGE_ZB>(), Int<0>()) : f(Int<2>(), Int<STAGE_ZB>(), Int<0>());
+        groups == 1 ? bins(Int<1>(), Int<GATHER_SOME>()) : bins(Int<3>(), Int<GATHER_SOME>());
 }
 
 // Persistent subset-gradient kernel over a batch: the work items of one step
@@ -990,10 +1028,9 @@ void tof_form(int n_tof, int nz, bool gather_two, F &&f) {
 // each into the gradient-sheet slot of its view's subset; else the lines of
 // the step's subset into slot 0), concatenated in `order`.  Workgroups take
 // items from a global counter (zeroed by the step's prep kernel) until none
-// is left.  MB, NZB, MANY: the TOF form that serves every member (see tof_form;
+// is left.  MB, NZB, PLANES: the TOF form that serves every member (see tof_form;
 // each form of the line body also serves fewer bins, shorter axes, fewer planes).
-// (MANY with 80 voxels a pass would not fit the registers beside the loop.)
-template <int MB, int NZB, bool MANY>
+template <int MB, int NZB, int PLANES>
 __global__ void __launch_bounds__(64 * MAX_WAVES) k_line_batched(const BMember *__restrict__ mem,
                                                                      const int *__restrict__ order, int n_mem,
                                                                      int step, int *__restrict__ counter) {
@@ -1033,7 +1070,7 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) k_line_batched(const BMember *
         const int view = __builtin_amdgcn_readfirstlane(snap ? jv : m.views[st.subset * m.views_stride + jv]);
         const int64_t g_off = snap ? (int64_t)(jv % m.n_sub) * m.g_slot : 0;
         if (m.is_tof) {
-            line_tof_body<M_GRAD, MB, NZB, MANY, MB == 1 ? 4 : 2>(pa, view * n_rad + k, smem, wave, g_off);
+            line_tof_body<M_GRAD, MB, NZB, PLANES, MB == 1 ? 4 : 2>(pa, view * n_rad + k, smem, wave, g_off);
         } else {
             line_nt_body<M_GRAD>(pa, view * n_rad + k, smem, 64 * wave + lane_here(), g_off);
         }
@@ -1051,7 +1088,7 @@ size_t nt_lds(const pet_geom_s *g) {
     return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0));
 }
 
-template <int MODE, int MB, int NZB, bool MANY>
+template <int MODE, int MB, int NZB, int PLANES>
 hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s) {
     const bool x = MODE != M_BACK, z = MODE != M_FWD;
     if (MODE == M_BACK) a.q_units = g->q_units_back;
@@ -1060,16 +1097,27 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
     // units, all views, 96 x 96 x 32, 255 -> 225 us with 64 registers.  Fewer waves for
     // even rounds of many units are slower (41 on 7 waves 367 us against 347 on 8; 17
     // on 6: 173 against 162): less is in flight.
-    const int waves = z ? TOF_BLOCK / 64 : std::min(TOF_BLOCK / 64, std::max(4, g->n_units));
+    // With an adjoint: four waves where the LDS then takes three workgroups or more per
+    // CU (few units, or no image sheet) and the lines fill the chip, so that one
+    // workgroup's phases overlap the others': gradients (backprojections) of 96 x 96 x 32
+    // voxels and five units 101 -> 90 (72 -> 61) us, of 96 x 96 x 5 and three units 51 ->
+    // 36 (39 -> 28).  With nine units a gradient's LDS leaves room for two (124 -> 157),
+    // a backprojection's for four (90 -> 75); with units in several groups it is
+    // slower (29 units, backprojection 276 -> 303), and with 85 lines (23 -> 28, 18 -> 22).
+    int waves = TOF_BLOCK / 64;
+    if (!z)
+        waves = std::min(waves, std::max(4, g->n_units));
+    else if (grid.x > FEW_LINES && a.q_units >= g->n_units && tof_lds_bytes(g, x, a.q_units, 4) <= CU_LDS_BYTES / 3)
+        waves = 4;
     const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : 0, z ? waves : 0);
     static size_t granted = 64 * 1024;
     if (lds > granted) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, MANY>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_line_tof<MODE, MB, NZB, PLANES>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e == hipSuccess) granted = lds;
         (void)hipGetLastError();
     }
-    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, MANY>), grid, dim3(64 * waves), lds, s, a);
+    hipLaunchKernelGGL((k_line_tof<MODE, MB, NZB, PLANES>), grid, dim3(64 * waves), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1084,15 +1132,19 @@ hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStr
         return hipGetLastError();
     } else if constexpr (MODE == M_OBJ) {
         return launch_tof_walk(g, M_OBJ, grid, a, s);
+    } else if constexpr (MODE == M_EM) {
+        ProjArgs em = a;
+        em.em = 1;
+        return launch_mode<M_GRAD>(g, grid, em, s);
     } else {
         if (MODE == M_GRAD && a.partial) return launch_tof_walk(g, M_GRAD, grid, a, s);
         hipError_t e = hipSuccess;
-        tof_form(a.tof.n_tof, a.nz, a.gather_planes == 2, [&](auto mb, auto nzb, auto many) {
-            // (without an adjoint the last two make no difference)
+        tof_form(a.tof.n_tof, a.nz, a.gather_planes, [&](auto mb, auto nzb, auto planes) {
+            // (without an adjoint the last two make no difference, without a forward the first)
             if constexpr (MODE == M_FWD)
-                e = launch_tof<MODE, mb.value, STAGE_ZB, false>(g, grid, a, s);
+                e = launch_tof<MODE, mb.value, STAGE_ZB, 2>(g, grid, a, s);
             else
-                e = launch_tof<MODE, mb.value, nzb.value, many.value != 0>(g, grid, a, s);
+                e = launch_tof<MODE, MODE == M_BACK ? 2 : mb.value, nzb.value, planes.value>(g, grid, a, s);
         });
         return e;
     }
@@ -1142,12 +1194,20 @@ hipError_t launch_line_kernel_impl(const pet_geom_s *g, int mode, dim3 grid, con
 
 }  // namespace
 
+// (The batched kernel comes in passes of 48 and 80 voxels only.)
+template <typename F>
+static void batch_form(const BatchForm &f, F &&launch) {
+    tof_form(f.n_tof, f.nz, f.planes, [&](auto mb, auto nzb, auto planes) {
+        launch(mb, Int<(nzb.value <= 3 ? 3 : STAGE_ZB)>(), planes);
+    });
+}
+
 hipError_t prime_line_batched(const BatchForm &f, size_t lds) {
     hipError_t e = hipSuccess;
-    tof_form(f.n_tof, f.nz, f.gather_two, [&](auto mb, auto nzb, auto many) {
+    batch_form(f, [&](auto mb, auto nzb, auto planes) {
         static size_t granted = 64 * 1024;
         if (lds <= granted) return;
-        e = hipFuncSetAttribute((const void *)k_line_batched<mb.value, many.value ? 3 : nzb.value, many.value != 0>,
+        e = hipFuncSetAttribute((const void *)k_line_batched<mb.value, nzb.value, planes.value>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e == hipSuccess) granted = lds;
     });
@@ -1156,9 +1216,9 @@ hipError_t prime_line_batched(const BatchForm &f, size_t lds) {
 
 hipError_t launch_line_batched(const BatchForm &f, const BMember *mem, const int *order, int n_mem, int step,
                                int *counter, int blocks, int waves, size_t lds, hipStream_t s) {
-    tof_form(f.n_tof, f.nz, f.gather_two, [&](auto mb, auto nzb, auto many) {
-        hipLaunchKernelGGL((k_line_batched<mb.value, many.value ? 3 : nzb.value, many.value != 0>), dim3(blocks), dim3(64 * waves), lds, s,
-                           mem, order, n_mem, step, counter);
+    batch_form(f, [&](auto mb, auto nzb, auto planes) {
+        hipLaunchKernelGGL((k_line_batched<mb.value, nzb.value, planes.value>), dim3(blocks), dim3(64 * waves), lds, s, mem,
+                           order, n_mem, step, counter);
     });
     return hipGetLastError();
 }
