@@ -57,8 +57,8 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.n_gchunk = g->n_gchunk;
     a.gather_planes = g->gather_planes;
     a.kappa = (float)g->kappa;
-    a.inv_kappa = 1.0 / g->kappa;
-    a.rho0 = g->ring0 + 1.0;
+    a.rho = g->rho;
+    a.least_weight = (float)(g->d.nz + 2 * PADZ) * 0x1p-23f;
     a.pitch2 = (float)(g->d.ring_pitch_mm * g->d.ring_pitch_mm);
     a.k_max = (float)g->d.max_ring_diff;
     a.units = g->units;

@@ -84,6 +84,52 @@ bool make_psf_axis(double sigma_vox, int axis, PsfAxis &k) {
     return true;
 }
 
+// Positions of the voxels in rings, shifted by one, for the axial gather
+// (line_sheets.h): z / kappa + ring0 + 1 in 32 bits.
+//
+// A voxel exactly one voxel away from a direct plane (ring difference 0, at the same
+// place in every row) does not see it, but its weight, 1 - kappa times their
+// distance in rings, may come out as 1e-7.  Its position is then moved by as many
+// units in the last place, few, as make the form's weight zero or less.  (With
+// rings three voxels apart the slices between them got a sensitivity of 1e-7, and
+// an OSEM image was off by its own size.)
+std::vector<float> gather_positions(int nz, int n_rings, double kappa_d, double ring0, int form) {
+    const float kappa = (float)kappa_d;
+    // weight of ring r at shifted position t, as the form computes it
+    auto weight = [&](float t, int r) {
+        if (form == 2) {
+            const int c = r + 1 - (int)std::floor(t);  // ring below (0) or above (1) the voxel
+            const float f = t - std::floor(t);
+            return c == 0 ? std::fmaf(-kappa, f, 1.f) : c == 1 ? std::fmaf(kappa, f, 1.f - kappa) : 0.f;
+        }
+        if (form == 3) {
+            const float u = t + GATHER_THREE, f = u - std::floor(u);
+            const int c = r + 2 - (int)std::floor(u);  // ring below (-1), at (0) or above (1) the nearest
+            return c == 0    ? std::fmaf(-kappa, std::fabs(f - 0.5f), 1.f)
+                   : c == -1 ? std::fmaf(-kappa, f, std::fmaf(-0.5f, kappa, 1.f))
+                   : c == 1  ? std::fmaf(kappa, f, std::fmaf(-1.5f, kappa, 1.f))
+                             : 0.f;
+        }
+        return std::fmaf(-kappa, std::fabs(t - (float)(r + 1)), 1.f);
+    };
+    std::vector<float> rho(nz);
+    for (int z = 0; z < nz; ++z) {
+        const float t0 = (float)(z / kappa_d + (ring0 + 1.0));
+        std::vector<int> missed;  // rings exactly one voxel away
+        for (int r = 0; r < n_rings; ++r)
+            if (std::fabs(std::fabs((r - ring0) * kappa_d - z) - 1.0) < 1e-9) missed.push_back(r);
+        rho[z] = t0;
+        for (int step = 0; step <= 32 && !missed.empty(); ++step) {
+            const float t = t0 + (float)((step & 1 ? 1 : -1) * ((step + 1) / 2)) * (std::nextafter(std::fabs(t0), 1e30f) - std::fabs(t0));
+            if (std::all_of(missed.begin(), missed.end(), [&](int r) { return weight(t, r) <= 0.f; })) {
+                rho[z] = t;
+                break;
+            }
+        }
+    }
+    return rho;
+}
+
 }  // namespace
 
 extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) {
@@ -343,6 +389,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     g->gather_planes = gather_form((float)g->kappa);
     for (const SegP &sg : gsegs)
         if (sg.np > GATHER_PLANES) g->gather_planes = GATHER_SOME;
+    const std::vector<float> hrho = gather_positions(d.nz, d.kind == PET_SCANNER_CYLINDER ? d.n_rings : 1, g->kappa, g->ring0, g->gather_planes);
     g->rows_max = rows_max;
     // non-TOF: one thread per plane, in as many waves as the planes need (up to
     // 16; more resident waves hide the LDS latency of the sample loop)
@@ -500,6 +547,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
               alloc((void **)&g->gsegs, sizeof(SegP) * gsegs.size()) &&
               alloc((void **)&g->gather, sizeof(GatherSeg) * hgather.size()) &&
               alloc((void **)&g->gchunk, sizeof(GatherChunk) * hchunks.size()) &&
+              alloc((void **)&g->rho, sizeof(float) * hrho.size()) &&
               alloc((void **)&g->views_dev, sizeof(int) * hviews.size()) &&
               alloc((void **)&g->line_order, sizeof(int) * horder.size()) &&
               alloc((void **)&g->T0, sizeof(float) * g->t0_elems) && alloc((void **)&g->T1, sizeof(float) * g->t1_elems) &&
@@ -527,6 +575,7 @@ extern "C" pet_status pet_geom_create(const pet_geom_desc *desc, pet_geom *out) 
     if (e == hipSuccess) e = hipMemcpy(g->gsegs, gsegs.data(), sizeof(SegP) * gsegs.size(), hipMemcpyHostToDevice);
     g->n_gseg = (int)gsegs.size();
     if (e == hipSuccess) e = hipMemcpy(g->gather, hgather.data(), sizeof(GatherSeg) * hgather.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(g->rho, hrho.data(), sizeof(float) * hrho.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->gchunk, hchunks.data(), sizeof(GatherChunk) * hchunks.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->views_dev, hviews.data(), sizeof(int) * hviews.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(g->line_order, horder.data(), sizeof(int) * horder.size(), hipMemcpyHostToDevice);
@@ -591,7 +640,7 @@ extern "C" pet_status pet_geom_destroy(pet_geom g) {
     }
     void *ptrs[] = {g->lines, g->planes, g->units, g->etab, g->walk_order, g->views_dev, g->line_order, g->T0, g->T1, g->G0, g->G1, g->g, g->xtmp,
                     g->grad, g->hess, g->num, g->sensi, g->partial, g->dscratch, g->fscratch, g->psf_a, g->psf_b,
-                    g->check_counts, g->wtab, g->ctab, g->gsegs, g->gather, g->gchunk};
+                    g->check_counts, g->wtab, g->ctab, g->gsegs, g->gather, g->gchunk, g->rho};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete g;

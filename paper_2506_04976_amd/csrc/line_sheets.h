@@ -176,7 +176,6 @@ __device__ __forceinline__ float gather_two(const float *Qs, const GatherSeg &G,
 // than 3/2 rings (2/3 <= kappa; the nearest plane's weight is positive up to
 // kappa = 2).  t is shifted by GATHER_THREE more than in the other forms, so that
 // its truncation is the nearest plane.
-constexpr float GATHER_THREE = 1.5f;
 __device__ __forceinline__ float gather_three(const float *Qs, const GatherSeg &G, float t, float kappa) {
     const float tc = __builtin_amdgcn_fmed3f(t, 0.5f, G.hi + 2.5f);
     const float f = __builtin_amdgcn_fractf(tc);
@@ -240,7 +239,7 @@ __device__ __forceinline__ auto gather_planes(const float *Qs, const GatherSeg &
 // Shifted position of voxel z before the segment's part, in the form's shift.
 template <int PLANES>
 __device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
-    return (float)fma((double)z, a.inv_kappa, a.rho0 + (PLANES == 3 ? (double)GATHER_THREE : 0.0));
+    return a.rho[min(z, a.nz - 1)] + (PLANES == 3 ? GATHER_THREE : 0.f);
 }
 
 // Backprojection of one chunk of planes of a non-TOF line from their factors
@@ -264,9 +263,16 @@ __device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
 // bins' weights, a function of the row and the segment's length.  Where every
 // row of a wave lies far enough inside the bins for all segments, that sum is
 // one constant; elsewhere it is evaluated per share.
+//
+// Cells whose sum is no larger than `least` stay zero.  In a sensitivity that is the
+// rounding of one share of the line's largest factor, which a cell may get that its
+// planes miss by nothing (a voxel exactly one voxel away from them): its zeros are then
+// exact, as an OSEM step takes them to be.  (With rings three voxels apart
+// the slices between them got a sensitivity of 1e-7, and the image was off by its own
+// size.)
 template <int PLANES, bool FOLD, typename Fold>
 __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, int nrow, const float *Qs,
-                                             const GatherChunk &ch, int64_t g_off, const Fold &fold, int tid) {
+                                             const GatherChunk &ch, int64_t g_off, const Fold &fold, float least, int tid) {
     const int nz = a.nz, rz = a.rz;
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
     const int other_stride = ((L.axis ? a.nx : a.ny) + 2 * PADA) * rz;
@@ -298,7 +304,7 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
             if (FOLD) acc *= (double)fold.inside();
         }
         const float val = (float)acc;
-        if (val != 0.f) spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), z + PADZ, rz, val);
+        if (!(fabsf(val) <= least)) spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), z + PADZ, rz, val);
         r += dr;
         z += dz;
         if (z >= nz) {

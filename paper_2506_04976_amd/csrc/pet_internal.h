@@ -82,6 +82,7 @@ constexpr int GATHER_ZEROS = 3;
 // Planes of a segment that may reach a voxel, the forms of the gather: two, three or
 // any number, and the one for factors that are not finite (see line_sheets.h)
 constexpr int GATHER_SOME = 4, GATHER_MANY = 0;
+constexpr float GATHER_THREE = 1.5f;  // what the positions of the form of three are shifted by besides
 inline int gather_form(float kappa) { return kappa >= 1.f ? 2 : kappa >= 0.6667f ? 3 : GATHER_SOME; }
 
 // ---- TOF line kernels --------------------------------------------------------
@@ -153,7 +154,8 @@ struct ProjArgs {
     int n_gchunk;
     int gather_planes;          // form of the gather: 2 or 3 planes (segments whole) or GATHER_SOME
     float kappa;                // ring pitch / vz
-    double inv_kappa, rho0;     // shifted position of voxel z before the segment's part: z inv_kappa + rho0
+    const float *rho;           // shifted position of each voxel before the segment's part (gather_positions)
+    float least_weight;         // rounding of an axial position (voxels)
     float pitch2, k_max;        // squared ring pitch, largest ring difference
     int em;                     // TOF M_GRAD: the EM ratio's factors instead of the gradient's
     // TOF line kernels: units; bins per block of 16 matrix rows; units whose
@@ -292,6 +294,7 @@ struct pet_geom_s {
     pet::GatherChunk *gchunk = nullptr;
     int n_gchunk = 0, gather_planes = 0, q_floats = 0;  // chunks; form; LDS floats of the largest one's factors
     double kappa = 1.0, ring0 = 0.0;    // ring pitch / vz; position of voxel 0 in rings, negated
+    float *rho = nullptr;               // shifted positions of the voxels
     int rows_max = 0;
     pet::TofUnit *units = nullptr;      // TOF line kernels
     float4 *etab = nullptr;

@@ -85,7 +85,8 @@ template <int MODE>
 __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, float *smem, int tid, int64_t g_off = 0) {
     constexpr bool NEED_X = MODE != M_BACK && MODE != M_COUNT;
     constexpr bool NEED_Z = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
-    __shared__ int s_special;  // some factor is not finite
+    __shared__ int s_special;      // some factor is not finite
+    __shared__ unsigned s_most;    // the largest finite one (a sensitivity's)
     const LineP L = scalar_ref(a.lines[line]);
     const int nrow = L.i_hi - L.i_lo + 1;
     const int rz = a.rz;
@@ -106,7 +107,7 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
             // (the zeros around the segments; the previous chunk's cells are done)
             if (ic > 0) __syncthreads();
             for (int k = tid; k < ch.n_q; k += nb) Qs[k] = 0.f;
-            if (tid == 0) s_special = 0;
+            if (tid == 0) s_special = s_most = 0;
         }
         if (NEED_Z || (NEED_X && ic == 0)) __syncthreads();
 
@@ -119,6 +120,7 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         const int rem = a.n_planes - full;
         int lg_c = 0;
         while (rem > 0 && lg_c < 6 && (rem << (lg_c + 1)) <= nb) ++lg_c;
+        float most = 0.f;
         for (int base = ch.p0, end; base < ch.p1; base = end) {
             const int lg = base >= full ? lg_c : 0, cc = 1 << lg;
             end = min(base >= full ? ch.p1 : min(ch.p1, full), base + (nb >> lg));
@@ -190,23 +192,29 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
             if (NEED_Z) {
                 Qs[P.q] = Q;
                 if (!(fabsf(Q) < INFINITY)) s_special = 1;
+                if (MODE == M_BACK) most = fabsf(Q) < INFINITY ? fmaxf(most, fabsf(Q)) : most;
             }
         }
         if (!NEED_Z) continue;
+        if (MODE == M_BACK && !a.sino) {
+            for (int o = 32; o; o >>= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
+            if ((tid & 63) == 0) atomicMax(&s_most, __float_as_uint(most));
+        }
         __syncthreads();
         if (nrow <= 0) continue;
         const int form = s_special ? GATHER_MANY : a.gather_planes;  // (uniform)
         const LineFold F(a, L);
+        const float least = MODE == M_BACK && !a.sino ? a.least_weight * __uint_as_float(s_most) : 0.f;
         auto cells = [&](auto fold) {
             constexpr bool FOLD = fold.value != 0;
             if (form == 2)
-                gather_cells<2, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+                gather_cells<2, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
             else if (form == 3)
-                gather_cells<3, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+                gather_cells<3, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
             else if (form == GATHER_SOME)
-                gather_cells<GATHER_SOME, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+                gather_cells<GATHER_SOME, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
             else
-                gather_cells<GATHER_MANY, FOLD>(a, L, nrow, Qs, ch, g_off, F, tid);
+                gather_cells<GATHER_MANY, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
         };
         if (MODE == M_BACK && a.tof_fold)
             cells(Int<MODE == M_BACK>());
@@ -577,7 +585,7 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
         const int lane = lane_here(), pl = lane & 15, g = lane >> 4;
         float *srow = k.stage + g * STAGE_COLS;
         // in the gather, this lane's rows are 4 g + h of the block
-        const float lam_g = fmaf((float)(L.i_lo + 16 * k.rb + 4 * g), L.dlam, L.lam0);
+        const float row0 = (float)(L.i_lo + 16 * k.rb + 4 * g);
         // the columns of this lane's planes (opaque: formed once per unit)
         float *col[4];
 #pragma unroll
@@ -602,7 +610,8 @@ __device__ __forceinline__ void tof_back_rows(const ProjArgs &a, const LineP &L,
             __builtin_amdgcn_sched_barrier(0);
             if (h == 3 && u + 1 < k.u1) products(u + 1);
             __builtin_amdgcn_sched_barrier(0);
-            const float lam = fmaf((float)h, L.dlam, lam_g);
+            // (as gather_cells: the sensitivity and what is divided by it have the same shares)
+            const float lam = fmaf(row0 + (float)h, L.dlam, L.lam0);
             auto segment = [&](const GatherSeg &G, float slope) {
                 decltype(gather_planes<PLANES>(srow, G, 0.f, kappa)) v[NZB];
 #pragma unroll

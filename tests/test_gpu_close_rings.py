@@ -58,3 +58,42 @@ def test_adjoints(kappa, size, name):
     yb = prob.ybar(x.astype(np.float64), 1)
     scale = np.linalg.norm(prob.back(prob.a[1] * (1 + prob.y[1] / yb), 1))
     assert off(prob.data_grad(x.astype(np.float64), 1), scale) <= 1e-5
+
+
+@pytest.mark.parametrize("name", ["mini_nontof", "mini_tof"])
+@pytest.mark.parametrize("kappa", [1.0 / 3.0, 0.75, 1.0, 1.5, 2.0, 3.0, 5.0])
+def test_unseen_voxels(kappa, name):
+    # Rings centred on the image, with voxels a whole number of voxels away from
+    # the planes: a voxel that no LOR sees has a sensitivity of exactly zero (an
+    # OSEM step divides by it), and weakly seen ones the same shares in the
+    # sensitivity and in what is divided by it.
+    import paper_2506_04976_amd as pm
+    nz = 15
+    rings = max(2, int(nz / kappa))
+    cfg = configs.get(name, nz=nz, vz=2.0, n_rings=rings, ring_pitch=2.0 * kappa, max_ring_diff=min(3, rings - 1),
+                      nx=14, ny=18, n_views=12, n_crystals=24, n_rad=15, n_subsets=2)
+    print(f"\n[unseen voxels] {name} kappa {kappa:.3f}", flush=True)
+    geom, dev = pm.Geometry(cfg), torch.device("cuda:0")
+    rng = np.random.default_rng(3)
+    lors = (cfg["n_views"], cfg["n_rad"], configs.n_planes(cfg))
+    x = rng.uniform(0.2, 1.0, (nz, cfg["ny"], cfg["nx"])).astype(np.float32)
+    mult = rng.uniform(0.5, 1.0, lors).astype(np.float32)
+    add = rng.uniform(0.5, 1.0, lors + (cfg["n_tof"],)).astype(np.float32)
+    y = rng.poisson(3.0, lors + (cfg["n_tof"],)).astype(np.uint8)
+
+    def t(a):
+        return torch.from_numpy(np.ascontiguousarray(a).ravel()).to(dev)
+
+    prob = recon.Problem(cfg, y, add, mult, beta=1.0, gamma=2.0, eps=1.0)
+    sens = torch.full((geom.n_vox,), float("nan"), device=dev)
+    for i in range(2):
+        pm.pet_back(geom, i, None, t(mult), sens)
+        # (beyond what FP64 itself makes of an exact zero)
+        ref = prob.sens_subset(i).ravel()
+        np.testing.assert_array_equal(sens.cpu().numpy() > 0, ref > 1e-12 * ref.max())
+    want = recon.osem_epoch(prob, x.astype(np.float64), [0, 1]).ravel()
+    dense, sparse = t(x), t(x)
+    pm.pet_osem_epoch(geom, dense, t(y), t(add), t(mult), [0, 1])
+    pm.pet_osem_epoch_counts(geom, pm.Counts(geom, t(y), t(add), t(mult)), sparse, t(mult), [0, 1])
+    for got in (dense, sparse):  # (images after an epoch, as in the other tests of this path)
+        assert np.linalg.norm(got.cpu().double().numpy() - want) <= 1e-4 * np.linalg.norm(want)

@@ -5,8 +5,8 @@ dealt to several waves) and of more than the chip holds (small workgroups), one 
 several units of planes, one block of bins and two.
 
 Tolerance: as for the other forms of these kernels, backprojections of nonnegative
-sinograms to a relative L2 error of 1e-5, gradients to 1e-5 of the norm of their
-summands' magnitudes.
+sinograms to a relative L2 error of 1e-5, gradients and EM ratios (an OSEM update
+against its oracle) to 1e-5 of the norm of their summands' magnitudes.
 """
 
 import numpy as np
@@ -54,3 +54,9 @@ def test_adjoints(nz, bins, lines):
     yb = prob.ybar(xo, 0)
     scale = np.linalg.norm(prob.back(prob.a[0] * (1 + prob.y[0] / yb), 0))
     assert np.linalg.norm(out.cpu().double().numpy() - prob.data_grad(xo, 0).ravel()) <= 1e-5 * scale
+    xe = t(x)
+    pm.pet_osem_epoch(geom, xe, t(y), t(add), t(mult), [0])
+    want = xo * prob.back(prob.a[0] * prob.y[0] / yb, 0) / prob.back(prob.a[0] * np.ones_like(yb), 0)
+    sees = prob.back(prob.a[0] * np.ones_like(yb), 0) > 0
+    got = xe.cpu().double().numpy().reshape(xo.shape)
+    assert np.linalg.norm((got - want)[sees]) <= 2e-5 * np.linalg.norm(want[sees])
