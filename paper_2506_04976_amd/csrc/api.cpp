@@ -61,6 +61,12 @@ ProjArgs base_args(pet_geom g, int subset) {
     a.least_weight = (float)(g->d.nz + 2 * PADZ) * 0x1p-23f;
     a.pitch2 = (float)(g->d.ring_pitch_mm * g->d.ring_pitch_mm);
     a.k_max = (float)g->d.max_ring_diff;
+    a.q_floats = g->q_floats;
+    if (g->d.n_tof > 1) {
+        a.fold_full = (float)std::erf((double)a.tof.erf_clamp);
+        a.fold_in = a.tof.tb[g->d.n_tof - 1] * (1.f - 1e-5f) + a.tof.half_bin * (1.f - 1e-5f) -
+                    a.tof.erf_clamp / a.tof.inv_sqrt2_sigma;
+    }
     a.units = g->units;
     a.n_units = g->n_units;
     a.bins_blk = g->bins_blk;

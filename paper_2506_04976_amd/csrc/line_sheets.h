@@ -260,9 +260,9 @@ __device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
 // the loop takes 71 and 121, the scatter 87 and 191.
 //
 // fold (a TOF geometry's mult alone): every sample carries the sum of its TOF
-// bins' weights, a function of the row and the segment's length.  Where every
+// bins' weights, a function of the row and the ring difference.  Where every
 // row of a wave lies far enough inside the bins for all segments, that sum is
-// one constant; elsewhere it is evaluated per share.
+// one constant; elsewhere it comes from the rows' table in LDS (line_nt_body).
 //
 // Cells whose sum is no larger than `least` stay zero.  In a sensitivity that is the
 // rounding of one share of the line's largest factor, which a cell may get that its
@@ -270,8 +270,10 @@ __device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
 // exact, as an OSEM step takes them to be.  (With rings three voxels apart
 // the slices between them got a sensitivity of 1e-7, and the image was off by its own
 // size.)
+//
+// Rows [r0, r1) of the line.
 template <int PLANES, bool FOLD, typename Fold>
-__device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, int nrow, const float *Qs,
+__device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, int r0, int r1, const float *Qs,
                                              const GatherChunk &ch, int64_t g_off, const Fold &fold, float least, int tid) {
     const int nz = a.nz, rz = a.rz;
     float *Gout = (L.axis ? a.G1 : a.G0) + g_off;
@@ -280,7 +282,8 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
     const float kappa = a.kappa;
     const int dr = (int)blockDim.x / nz, dz = (int)blockDim.x - dr * nz;
     int r = tid / nz, z = tid - r * nz;
-    while (r < nrow) {
+    r += r0;
+    while (r < r1) {
         const float lam = fmaf((float)(L.i_lo + r), L.dlam, L.lam0);
         const float rho = gather_rho<PLANES>(a, z);
         double acc = 0.0;
@@ -297,14 +300,17 @@ __device__ __forceinline__ void gather_cells(const ProjArgs &a, const LineP &L, 
             run(ch.s0, ch.s_neg, lam, each);
             run(ch.s_neg, ch.s1, 1.f - lam, each);
         };
+        float drop = least;
         if (FOLD && !__all(fold.constant(lam))) {
-            both([&](auto v, float k) { return v * fold.weight(lam, k); });
+            const float *w = fold.table + (r - r0) * fold.n_k;
+            both([&](auto v, float k) { return v * w[(int)k]; });
+            drop *= w[0];  // (the largest)
         } else {
             both([](auto v, float) { return v; });
             if (FOLD) acc *= (double)fold.inside();
         }
         const float val = (float)acc;
-        if (!(fabsf(val) <= least)) spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), z + PADZ, rz, val);
+        if (!(fabsf(val) <= drop)) spread_cell(Gout, sheet_row(L, L.i_lo + r, other_stride, rz), z + PADZ, rz, val);
         r += dr;
         z += dz;
         if (z >= nz) {

@@ -79,6 +79,9 @@ struct GatherChunk {
 };
 constexpr int GATHER_PLANES = 1024;
 constexpr int GATHER_ZEROS = 3;
+// LDS floats of the folded TOF weights of a block of rows (at least 64 rows: a TOF
+// segment has at most 64 planes, and so does the range of ring differences)
+constexpr int FOLD_FLOATS = 4096;
 // Planes of a segment that may reach a voxel, the forms of the gather: two, three or
 // any number, and the one for factors that are not finite (see line_sheets.h)
 constexpr int GATHER_SOME = 4, GATHER_MANY = 0;
@@ -157,6 +160,10 @@ struct ProjArgs {
     const float *rho;           // shifted position of each voxel before the segment's part (gather_positions)
     float least_weight;         // rounding of an axial position (voxels)
     float pitch2, k_max;        // squared ring pitch, largest ring difference
+    int q_floats;               // LDS floats of the largest chunk's factors
+    // sum of all TOF bins' weights where no end of theirs reaches, and the distance from
+    // the LOR centre up to which that is so (a margin for its rounding)
+    float fold_full, fold_in;
     int em;                     // TOF M_GRAD: the EM ratio's factors instead of the gradient's
     // TOF line kernels: units; bins per block of 16 matrix rows; units whose
     // factors are in LDS together and the floats of each; cubics of the halved

@@ -49,6 +49,8 @@ __device__ __forceinline__ int lane_here() {
 struct LineFold {
     float lo, hi, inv_s, c, full;
     float lt2, pitch2, t_in, len_max;
+    const float *table = nullptr;  // weights of the rows of a block, n_k each
+    int n_k;
 
     __device__ __forceinline__ LineFold(const ProjArgs &a, const LineP &L) {
         const TofTable &T = a.tof;
@@ -56,13 +58,13 @@ struct LineFold {
         hi = T.tb[T.n_tof - 1] + T.half_bin;
         inv_s = T.inv_sqrt2_sigma;
         c = T.erf_clamp;
-        full = erff(c);
+        full = a.fold_full;
         lt2 = L.lt2;
         pitch2 = a.pitch2;
-        // |t| up to which both ends are clamped (a margin for its rounding), and
-        // the longest |u| of the line
-        t_in = fminf(hi, -lo) * (1.f - 1e-5f) - c / inv_s;
+        // (|t| up to which both ends are clamped, and the longest |u| of the line)
+        t_in = a.fold_in;
         len_max = sqrtf(fmaf(a.k_max * a.k_max, pitch2, lt2)) * (1.f + 1e-5f);
+        n_k = (int)a.k_max + 1;
     }
     // the samples of the row lie where the sum is `inside` in every segment
     __device__ __forceinline__ bool constant(float lam) const { return fabsf(lam - 0.5f) * len_max <= t_in; }
@@ -100,6 +102,26 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
 
     double kl = 0.0;
     const int nb = blockDim.x;
+    // Folded TOF weights per row and ring difference, in blocks of rows (one block
+    // unless the ring differences are many); none where all rows lie inside the bins.
+    // Evaluated per share, two error functions each, they cost a sensitivity of 97 x
+    // 88 x 27 voxels, 19 bins and 231 planes 33.8 us (scatter, once per sample: 23.8;
+    // this table: 19.2).
+    LineFold F(a, L);
+    float *fold_table = Qs + a.q_floats;
+    int fold_rows = INT_MAX;
+    auto fill_fold = [&](int r0) {
+        if (fold_rows == INT_MAX) return;
+        for (int e = tid; e < min(fold_rows, nrow - r0) * F.n_k; e += nb) {
+            const int r = e / F.n_k;
+            fold_table[e] = F.weight(fmaf((float)(L.i_lo + r0 + r), L.dlam, L.lam0), (float)(e - r * F.n_k));
+        }
+    };
+    if (MODE == M_BACK && a.tof_fold) {
+        if (!F.constant(fmaf((float)L.i_lo, L.dlam, L.lam0)) || !F.constant(fmaf((float)L.i_hi, L.dlam, L.lam0)))
+            fold_rows = FOLD_FLOATS / F.n_k;  // (uniform)
+        fill_fold(0);
+    }
     for (int ic = 0; ic < (MODE == M_COUNT ? 1 : a.n_gchunk); ++ic) {
         GatherChunk ch{0, 0, 0, 0, a.n_planes, 0};
         if (MODE != M_COUNT) ch = a.gchunk[ic];
@@ -203,23 +225,31 @@ __device__ __forceinline__ double line_nt_body(const ProjArgs &a, int line, floa
         __syncthreads();
         if (nrow <= 0) continue;
         const int form = s_special ? GATHER_MANY : a.gather_planes;  // (uniform)
-        const LineFold F(a, L);
         const float least = MODE == M_BACK && !a.sino ? a.least_weight * __uint_as_float(s_most) : 0.f;
-        auto cells = [&](auto fold) {
+        auto cells = [&](auto fold, int r0, int r1) {
             constexpr bool FOLD = fold.value != 0;
             if (form == 2)
-                gather_cells<2, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
+                gather_cells<2, FOLD>(a, L, r0, r1, Qs, ch, g_off, F, least, tid);
             else if (form == 3)
-                gather_cells<3, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
+                gather_cells<3, FOLD>(a, L, r0, r1, Qs, ch, g_off, F, least, tid);
             else if (form == GATHER_SOME)
-                gather_cells<GATHER_SOME, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
+                gather_cells<GATHER_SOME, FOLD>(a, L, r0, r1, Qs, ch, g_off, F, least, tid);
             else
-                gather_cells<GATHER_MANY, FOLD>(a, L, nrow, Qs, ch, g_off, F, least, tid);
+                gather_cells<GATHER_MANY, FOLD>(a, L, r0, r1, Qs, ch, g_off, F, least, tid);
         };
-        if (MODE == M_BACK && a.tof_fold)
-            cells(Int<MODE == M_BACK>());
-        else
-            cells(Int<0>());
+        if (MODE == M_BACK && a.tof_fold) {
+            F.table = fold_table;
+            for (int r0 = 0; r0 < nrow; r0 = fold_rows < nrow - r0 ? r0 + fold_rows : nrow) {
+                if (r0 > 0 || (ic > 0 && fold_rows < nrow)) {
+                    __syncthreads();
+                    fill_fold(r0);
+                    __syncthreads();
+                }
+                cells(Int<MODE == M_BACK>(), r0, fold_rows < nrow - r0 ? r0 + fold_rows : nrow);
+            }
+        } else {
+            cells(Int<0>(), 0, nrow);
+        }
     }
     return kl;
 }
@@ -467,8 +497,7 @@ static_assert(TOF_STAGE_FLOATS == STAGE_COLS * STAGE_ROWS, "LDS layout of the TO
 // Voxels along z of one pass of the adjoint: at most STAGE_ZB groups of 16.
 constexpr int STAGE_ZB = 5;
 static_assert(16 * STAGE_ZB <= STAGE_COLS, "the finished cells leave through the staged rows");
-// Lines of a launch up to which its workgroups share the chip with no others (two
-// to a CU).
+// Lines of a launch up to which a CU has two workgroups at most.
 constexpr unsigned FEW_LINES = 512;
 // Groups of four bins whose weights a wave of the adjoint keeps for a pair of
 // segments of the same length.
@@ -1087,14 +1116,30 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) k_line_batched(const BMember *
     }
 }
 
-// LDS of the non-TOF line kernel: the image sheet (modes that project) and the
-// planes' factors (modes that backproject).
+// LDS of the non-TOF line kernel: the image sheet (modes that project), the planes'
+// factors (modes that backproject) and the folded TOF weights of a block of rows.
 template <int MODE>
 size_t nt_lds(const pet_geom_s *g) {
     if (MODE == M_COUNT) return 0;
     const size_t sheet = ((size_t)g->rows_max * (g->d.nz + 2 * PADZ) + 3) & ~(size_t)3;
     const bool x = MODE != M_BACK, q = MODE == M_BACK || MODE == M_GRAD || MODE == M_EM || MODE == M_HVP;
-    return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0));
+    return sizeof(float) * ((x ? sheet : 0) + (q ? (size_t)g->q_floats : 0) +
+                            (MODE == M_BACK && g->d.n_tof > 1 ? (size_t)FOLD_FLOATS : 0));
+}
+
+// Threads of a non-TOF line.  With a forward projection as many as planes (the sums'
+// order depends on it); a backprojection's work are the cells of the line's sheet:
+// eight per thread (two planes at most) where the lines fill the chip, two where they
+// leave it idle.  (Sensitivity of 96 x 96 x 32 voxels and 32 planes 45 us with 64
+// threads, 36 with 448; of 97 x 88 x 27 and 231 planes, 350 lines, 22 with 384, 19
+// with 1024; backprojection of 128 x 128 x 48 and 1037 planes 106 us with 1024, 102
+// with 512.)
+template <int MODE>
+int nt_threads(const pet_geom_s *g, unsigned lines) {
+    if (MODE != M_BACK) return g->nt_threads;
+    const bool few = lines <= FEW_LINES;
+    const int work = std::max(g->rows_max * g->d.nz / (few ? 2 : 8), g->n_planes / 2);
+    return std::max(64, std::min((work + 63) / 64 * 64, few ? NT_BLOCK : NT_BLOCK / 2));
 }
 
 template <int MODE, int MB, int NZB, int PLANES>
@@ -1133,7 +1178,7 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
 template <int MODE>
 hipError_t launch_mode(const pet_geom_s *g, dim3 grid, const ProjArgs &a, hipStream_t s) {
     if (g->d.n_tof == 1) {
-        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(g->nt_threads), nt_lds<MODE>(g), s, a);
+        hipLaunchKernelGGL((k_line_nt<MODE>), grid, dim3(nt_threads<MODE>(g, grid.x)), nt_lds<MODE>(g), s, a);
         return hipGetLastError();
     }
     if constexpr (MODE == M_COUNT) {
@@ -1181,12 +1226,12 @@ void set_lds_attr(size_t need) {
 hipError_t launch_back_fold(const pet_geom_s *g, dim3 grid, const ProjArgs &a0, hipStream_t s) {
     ProjArgs a = a0;
     a.tof_fold = 1;
-    hipLaunchKernelGGL((k_line_nt<M_BACK>), grid, dim3(g->nt_threads), nt_lds<M_BACK>(g), s, a);
+    hipLaunchKernelGGL((k_line_nt<M_BACK>), grid, dim3(nt_threads<M_BACK>(g, grid.x)), nt_lds<M_BACK>(g), s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_line_kernel_impl(const pet_geom_s *g, int mode, dim3 grid, const ProjArgs &a, hipStream_t s) {
-    set_lds_attr(nt_lds<M_GRAD>(g));
+    set_lds_attr(std::max(nt_lds<M_GRAD>(g), nt_lds<M_BACK>(g)));
     switch (mode) {
         case M_FWD: return launch_mode<M_FWD>(g, grid, a, s);
         case M_BACK:

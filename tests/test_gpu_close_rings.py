@@ -97,3 +97,23 @@ def test_unseen_voxels(kappa, name):
     pm.pet_osem_epoch_counts(geom, pm.Counts(geom, t(y), t(add), t(mult)), sparse, t(mult), [0, 1])
     for got in (dense, sparse):  # (images after an epoch, as in the other tests of this path)
         assert np.linalg.norm(got.cpu().double().numpy() - want) <= 1e-4 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("rings,diff", [(1, 0), (3, 0), (12, 7), (64, 63)])
+def test_sensitivity_at_the_ends_of_the_bins(rings, diff):
+    # bins that end inside the image: the sum of their weights differs from row to
+    # row and between the ring differences (blocks of 64 rows with 64 of them)
+    import paper_2506_04976_amd as pm
+    cfg = configs.get("mini_tof", nx=70, ny=66, vx=2.0, vy=2.0, nz=6, vz=3.0, n_rings=rings, ring_pitch=18.0 / rings,
+                      max_ring_diff=diff, n_views=9, n_crystals=18, n_rad=5, radius=150.0, n_tof=5, tof_bin=24.0,
+                      tof_sigma=11.0, n_subsets=1)
+    print(f"\n[ends of the bins] {rings} rings, differences to {diff}", flush=True)
+    geom, dev = pm.Geometry(cfg), torch.device("cuda:0")
+    lors = (cfg["n_views"], cfg["n_rad"], configs.n_planes(cfg))
+    mult = np.random.default_rng(2).uniform(0.5, 1.0, lors).astype(np.float32)
+    blank = np.zeros(lors + (cfg["n_tof"],), np.uint8)
+    prob = recon.Problem(cfg, blank, blank, mult, beta=1.0, gamma=2.0, eps=1.0)
+    out = torch.full((geom.n_vox,), float("nan"), device=dev)
+    pm.pet_back(geom, 0, None, torch.from_numpy(mult.ravel()).to(dev), out)
+    ref = prob.sens_subset(0).ravel()
+    assert np.linalg.norm(out.cpu().double().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
