@@ -497,8 +497,9 @@ static_assert(TOF_STAGE_FLOATS == STAGE_COLS * STAGE_ROWS, "LDS layout of the TO
 // Voxels along z of one pass of the adjoint: at most STAGE_ZB groups of 16.
 constexpr int STAGE_ZB = 5;
 static_assert(16 * STAGE_ZB <= STAGE_COLS, "the finished cells leave through the staged rows");
+constexpr unsigned CUS = 256;
 // Lines of a launch up to which a CU has two workgroups at most.
-constexpr unsigned FEW_LINES = 512;
+constexpr unsigned FEW_LINES = 2 * CUS;
 // Groups of four bins whose weights a wave of the adjoint keeps for a pair of
 // segments of the same length.
 constexpr int KEEP_KK = 3;
@@ -1151,18 +1152,22 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
     // units, all views, 96 x 96 x 32, 255 -> 225 us with 64 registers.  Fewer waves for
     // even rounds of many units are slower (41 on 7 waves 367 us against 347 on 8; 17
     // on 6: 173 against 162): less is in flight.
-    // With an adjoint: four waves where the LDS then takes three workgroups or more per
-    // CU (few units, or no image sheet) and the lines fill the chip, so that one
-    // workgroup's phases overlap the others': gradients (backprojections) of 96 x 96 x 32
-    // voxels and five units 101 -> 90 (72 -> 61) us, of 96 x 96 x 5 and three units 51 ->
-    // 36 (39 -> 28).  With nine units a gradient's LDS leaves room for two (124 -> 157),
-    // a backprojection's for four (90 -> 75); with units in several groups it is
-    // slower (29 units, backprojection 276 -> 303), and with 85 lines (23 -> 28, 18 -> 22).
+    // With an adjoint: fewer waves, and more workgroups on a CU, so that one workgroup's
+    // phases overlap the others', where the lines fill the chip with them and the LDS
+    // takes three workgroups of four waves (four with more units than eight waves take
+    // at once).  Four waves from three lines per CU: gradients (backprojections) of
+    // 96 x 96 x 32 voxels and five units 101 -> 90 (72 -> 61) us, of 96 x 96 x 5 and
+    // three units 51 -> 36 (39 -> 28), 784 lines of 13 units 52 -> 42; but 576 lines 44
+    // -> 56, 85 lines 23 -> 28, and 29 units with room for three workgroups 98 -> 119.
+    // Two waves for one or two units, from six lines per CU: 1896 lines of one unit 61
+    // -> 42 (four: 49), 10191 of two 308 -> 220 (228); three units 565 -> 482 (405).
+    // Units in several groups are slower so (29, backprojection, 276 -> 303).
     int waves = TOF_BLOCK / 64;
     if (!z)
         waves = std::min(waves, std::max(4, g->n_units));
-    else if (grid.x > FEW_LINES && a.q_units >= g->n_units && tof_lds_bytes(g, x, a.q_units, 4) <= CU_LDS_BYTES / 3)
-        waves = 4;
+    else if (grid.x >= 3 * CUS && a.q_units >= g->n_units &&
+             tof_lds_bytes(g, x, a.q_units, 4) <= CU_LDS_BYTES / (g->n_units > waves ? 4 : 3))
+        waves = g->n_units <= 2 && grid.x >= 6 * CUS ? 2 : 4;
     const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : 0, z ? waves : 0);
     static size_t granted = 64 * 1024;
     if (lds > granted) {
