@@ -44,8 +44,10 @@ struct pet_batch_s {
 namespace {
 
 size_t batch_lds(const pet_batch_s *b, int waves) {
+    // (the TOF adjoint reads up to a tile of planes, 16 of 32 bins, and two groups of
+    // bins past the last unit's factors: at least two waves' staged rows lie there)
     size_t m = 0;
-    for (int r = 0; r < b->n; ++r) m = std::max(m, b->lds_base[r] + (size_t)waves * b->lds_per_wave[r]);
+    for (int r = 0; r < b->n; ++r) m = std::max(m, b->lds_base[r] + (size_t)std::max(waves, 2) * b->lds_per_wave[r]);
     return m;
 }
 

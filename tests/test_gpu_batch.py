@@ -228,3 +228,26 @@ def test_batch_c4_sized_members_match_individual_runs():
         assert err <= 1e-5, m.cfg["name"]
         assert st2.k == st1.k == E * m.cfg["n_subsets"]
     b.close()
+
+
+@pytest.mark.parametrize("nz, rings", [(9, 5), (64, 13)])
+def test_batch_of_one_wave_with_two_blocks_of_bins(nz, rings):
+    # one wave per workgroup, 32 bins (the most), 16 planes a unit at most and more: the
+    # adjoint's tiles reach past the last unit's factors
+    import paper_2506_04976_amd as pm
+    E = 2
+    cfg = configs.get("mini_tof", nz=nz, vz=2.0, n_rings=rings, ring_pitch=2.0 * nz / rings, max_ring_diff=1, n_tof=32,
+                      tof_bin=9.0, tof_sigma=9.0, tof_nsigma=1.0)
+    _say(f"[batch one wave] {nz} slices")
+    m = Member(cfg, 1.0)
+    (g, st, x1), run = m.runner(), m.runner()
+    orders, taus, upd = m.schedule(E)
+    for e in range(E):
+        pm.pet_svrg_epoch(g, st, x1, orders[e], taus[e], upd[e])
+    b = pm.Batch([run])
+    b.set_launch(64, 1)
+    b.epochs([[int(v) for e in range(E) for v in orders[e]]], [[v for e in range(E) for v in taus[e]]],
+             [[v for e in range(E) for v in upd[e]]])
+    torch.cuda.synchronize()
+    b.close()
+    assert _rel(run[2], x1) <= 1e-5
