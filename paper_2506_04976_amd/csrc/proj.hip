@@ -809,110 +809,112 @@ __device__ __forceinline__ void line_tof_body(const ProjArgs &a, int line, float
             bool bad = false;  // a factor that is not finite
             // (TILES tiles of 16 planes at a time)
             for (int t0 = 0; t0 < (TILES == 4 ? 1 : npb); t0 += TILES) {
-            const int nt0 = min(TILES, npb - t0);
-            f32x4 D[MB][TILES];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int pb = 0; pb < TILES; ++pb) D[mb][pb] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (NEED_X) {
-                float zA[TILES], zB[TILES];
-#pragma unroll
-                for (int pb = 0; pb < TILES; ++pb) {
-                    const int idx = 16 * (t0 + pb) + pl;
-                    const PlaneP P = a.planes[p0 + min(idx, np - 1)];
-                    zA[pb] = idx < np ? P.zs * L.dlam : 0.f;
-                    zB[pb] = idx < np ? (float)fma((double)L.lam0, P.zs, P.zb + (double)PADZ) : 0.f;
-                }
-                auto rows = [&](auto tiles) {
-                    tof_fwd_rows<MB, tiles.value, TILES>(a, tab, X, j_lo, j_hi, L.i_lo, lane, tp, zA, zB, D);
-                };
-                if (nt0 == 1)
-                    rows(Int<1>());
-                else if (nt0 == 2 || TILES == 2)
-                    rows(Int<2>());
-                else if (nt0 == 3)
-                    rows(Int<(TILES > 2 ? 3 : 2)>());
-                else
-                    rows(Int<TILES>());
-            }
-            // (this lane's bins of plane idx = 16 (t0 + pb) + pl: mb bins_blk + 4 g + r)
-            const int i0 = 16 * t0, i1 = min(np, 16 * (t0 + nt0));
-            bool special = false;
-            if (MODE == M_FWD) {
-                float top = 0.f;  // (NaN and inf stay)
+                const int nt0 = min(TILES, npb - t0);
+                f32x4 D[MB][TILES];
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int pb = 0; pb < TILES; ++pb)
+                    for (int pb = 0; pb < TILES; ++pb) D[mb][pb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (NEED_X) {
+                    float zA[TILES], zB[TILES];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) top += fabsf(D[mb][pb][r]);
-                special = __any(!(top < INFINITY));
-            }
-            if (MODE == M_FWD && special) {
-                // (without the products of zero weights)
-                slow(i0, i1, [&](int e, int idx, int b, float *) {
-                    const float sum = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b);
-                    a.out[base + e] = fmaf(a.mult ? a.mult[lor0 + idx] : 1.f, sum * tp.ell, a.add ? a.add[base + e] : 0.f);
-                });
-                continue;
-            }
-            float top = 0.f;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int b0 = mb * a.bins_blk + 4 * g;
-                const int nb = min(a.bins_blk - 4 * g, nt - b0);  // this lane's bins of the block (at most 4 used)
-                // (two tiles' loads in flight together)
-#pragma unroll
-                for (int ph = 0; ph < TILES; ph += 2) {
-                    if (ph < nt0) {
-                float v[TILES][4], yv[TILES][4], m[TILES];
-#pragma unroll
-                for (int pb = ph; pb < ph + 2; ++pb) {
-                    const int idx = 16 * (t0 + pb) + pl;
-                    const bool has = idx < np;
-                    const int n = has ? nb : 0;
-                    const int off = idx * nt + b0;
-                    m[pb] = 0.f;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[pb][r] = yv[pb][r] = 0.f;
-                    if (n <= 0) continue;
-                    m[pb] = a.mult ? a.mult[lor0 + idx] : 1.f;
-                    if constexpr (MODE == M_BACK) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[pb][r] = 1.f;
-                        if (a.sino) load_bins(a.sino + base + off, n, v[pb]);
-                    } else if constexpr (MODE == M_HVP) {
-                        load_bins(a.ybar + base + off, n, v[pb]);
-                    } else {
-                        if (a.add) load_bins(a.add + base + off, n, v[pb]);
+                    for (int pb = 0; pb < TILES; ++pb) {
+                        const int idx = 16 * (t0 + pb) + pl;
+                        const PlaneP P = a.planes[p0 + min(idx, np - 1)];
+                        zA[pb] = idx < np ? P.zs * L.dlam : 0.f;
+                        zB[pb] = idx < np ? (float)fma((double)L.lam0, P.zs, P.zb + (double)PADZ) : 0.f;
                     }
-                    if constexpr (MODE != M_BACK && MODE != M_FWD) load_counts(a.y, a.y_dtype, base + off, n, yv[pb]);
+                    auto rows = [&](auto tiles) {
+                        tof_fwd_rows<MB, tiles.value, TILES>(a, tab, X, j_lo, j_hi, L.i_lo, lane, tp, zA, zB, D);
+                    };
+                    if (nt0 == 1)
+                        rows(Int<1>());
+                    else if (nt0 == 2 || TILES == 2)
+                        rows(Int<2>());
+                    else if (nt0 == 3)
+                        rows(Int<(TILES > 2 ? 3 : 2)>());
+                    else
+                        rows(Int<TILES>());
                 }
+                // (this lane's bins of plane idx = 16 (t0 + pb) + pl: mb bins_blk + 4 g + r)
+                const int i0 = 16 * t0, i1 = min(np, 16 * (t0 + nt0));
+                bool special = false;
+                if (MODE == M_FWD) {
+                    float top = 0.f;  // (NaN and inf stay)
 #pragma unroll
-                for (int pb = ph; pb < ph + 2; ++pb) {
-                    const int idx = 16 * (t0 + pb) + pl;
-                    const bool has = idx < np;
+                    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (r >= nb || pb >= nt0) continue;
-                        const float s = D[mb][pb][r] * tp.ell;
-                        float Q = 0.f;
-                        if constexpr (MODE == M_FWD) v[pb][r] = fmaf(m[pb], s, v[pb][r]);
-                        if constexpr (NEED_Z) Q = tof_factor<MODE>(a.em, m[pb], s, v[pb][r], yv[pb][r], tp.ell);
-                        if (NEED_Z) {
-                            if (!has) Q = 0.f;
-                            top += fabsf(Q);
-                            F[((t0 + pb) * nt + b0 + r) * 16 + pl] = Q;
+                        for (int pb = 0; pb < TILES; ++pb)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) top += fabsf(D[mb][pb][r]);
+                    special = __any(!(top < INFINITY));
+                }
+                if (MODE == M_FWD && special) {
+                    // (without the products of zero weights)
+                    slow(i0, i1, [&](int e, int idx, int b, float *) {
+                        const float sum = tof_fwd_guarded(a, tab, X, L, nrow, tp, a.planes[p0 + idx], b);
+                        a.out[base + e] = fmaf(a.mult ? a.mult[lor0 + idx] : 1.f, sum * tp.ell, a.add ? a.add[base + e] : 0.f);
+                    });
+                    continue;
+                }
+                float top = 0.f;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int b0 = mb * a.bins_blk + 4 * g;
+                    const int nb = min(a.bins_blk - 4 * g, nt - b0);  // this lane's bins of the block (at most 4 used)
+                    // (two tiles' loads in flight together)
+#pragma unroll
+                    for (int ph = 0; ph < TILES; ph += 2) {
+                        if (ph < nt0) {
+                            float v[TILES][4], yv[TILES][4], m[TILES];
+#pragma unroll
+                            for (int pb = ph; pb < ph + 2; ++pb) {
+                                const int idx = 16 * (t0 + pb) + pl;
+                                const bool has = idx < np;
+                                const int n = has ? nb : 0;
+                                const int off = idx * nt + b0;
+                                m[pb] = 0.f;
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) v[pb][r] = yv[pb][r] = 0.f;
+                                if (n <= 0) continue;
+                                m[pb] = a.mult ? a.mult[lor0 + idx] : 1.f;
+                                if constexpr (MODE == M_BACK) {
+#pragma unroll
+                                    for (int r = 0; r < 4; ++r) v[pb][r] = 1.f;
+                                    if (a.sino) load_bins(a.sino + base + off, n, v[pb]);
+                                } else if constexpr (MODE == M_HVP) {
+                                    load_bins(a.ybar + base + off, n, v[pb]);
+                                } else {
+                                    if (a.add) load_bins(a.add + base + off, n, v[pb]);
+                                }
+                                if constexpr (MODE != M_BACK && MODE != M_FWD)
+                                    load_counts(a.y, a.y_dtype, base + off, n, yv[pb]);
+                            }
+#pragma unroll
+                            for (int pb = ph; pb < ph + 2; ++pb) {
+                                const int idx = 16 * (t0 + pb) + pl;
+                                const bool has = idx < np;
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) {
+                                    if (r >= nb || pb >= nt0) continue;
+                                    const float s = D[mb][pb][r] * tp.ell;
+                                    float Q = 0.f;
+                                    if constexpr (MODE == M_FWD) v[pb][r] = fmaf(m[pb], s, v[pb][r]);
+                                    if constexpr (NEED_Z)
+                                        Q = tof_factor<MODE>(a.em, m[pb], s, v[pb][r], yv[pb][r], tp.ell);
+                                    if (NEED_Z) {
+                                        if (!has) Q = 0.f;
+                                        top += fabsf(Q);
+                                        F[((t0 + pb) * nt + b0 + r) * 16 + pl] = Q;
+                                    }
+                                }
+                                if constexpr (MODE == M_FWD)
+                                    if (has) store_bins(a.out + base + idx * nt + b0, nb, v[pb]);
+                            }
                         }
                     }
-                    if constexpr (MODE == M_FWD)
-                        if (has) store_bins(a.out + base + idx * nt + b0, nb, v[pb]);
                 }
-                }
-                }
-            }
-            bad |= !(top < INFINITY);
+                bad |= !(top < INFINITY);
             }
             if (NEED_Z && __any(bad)) {
                 // (the products also take a bin's sum from rows, and its factor to
