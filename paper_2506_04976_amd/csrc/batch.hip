@@ -209,18 +209,17 @@ __device__ __forceinline__ void member_step(const BMember &m, const BStep &st, i
                 const int64_t u = ((int64_t)jz * m.ny + jy) * m.nx + jx;
                 const float xj = m.x[u];
                 const float wk = m.w[(dz + 1) * 9 + (dy + 1) * 3 + (dx + 1)] * ki * (m.kappa ? m.kappa[u] : 1.f);
+                // (the terms of rdp_pair: products of quotients, which stay in range where
+                // a voxel that no LOR sees runs to 1e19 and more between zeros)
                 const float d = xi - xj;
-                const float ad = fabsf(d);
-                const float phi = xi + xj + m.gamma * ad + m.eps;
-                const float rphi = 1.f / phi;
-                g = fmaf(wk * d * (2.f * phi - (d + m.gamma * ad)), rphi * rphi, g);
-                if (upd) {
-                    const float c = 2.f * xj + m.eps;
-                    h = fmaf(2.f * wk * c * c, rphi * rphi * rphi, h);
-                }
+                const float rphi = 1.f / (xi + xj + m.gamma * fabsf(d) + m.eps);
+                const float a = d * rphi, b = (2.f * xj + m.eps) * rphi;
+                g = fmaf(wk, fmaf(a, b, a), g);
+                if (upd) h = fmaf(wk, b * b * rphi, h);
             }
         }
     }
+    h *= 2.f;
     const float bg = m.beta * g;
     float Dv;
     if (upd) {
