@@ -36,8 +36,8 @@ PEAK_HBM_GBPS = 8000.0
 # calibrated FETCH_SIZE / WRITE_SIZE counter runs, and its VALU issue fraction
 # (SQ counters), valid for the kernel source with this hash only (reported as
 # null otherwise).
-MEASURED_TRAFFIC = {"c2_tof": (203.3e6, "bafd195b0bc06ac0")}
-MEASURED_VALU = {"c2_tof": (0.83, "bafd195b0bc06ac0")}
+MEASURED_TRAFFIC = {"c2_tof": (203.3e6, "c5aba4e12bac5ac5")}
+MEASURED_VALU = {"c2_tof": (0.84, "c5aba4e12bac5ac5")}
 
 
 def log(msg):

@@ -253,8 +253,8 @@ __device__ __forceinline__ float gather_rho(const ProjArgs &a, int z) {
 // two-word LDS read; 17 with three planes.  A scatter instead adds two shares per
 // sample with FP64 LDS atomics into a sheet of doubles, which took 77 KB and left
 // one workgroup per CU: backprojection of a 10-view subset of the 128x128x71,
-// 2204-plane geometry 397 us (now 146), its fused gradient 603 (303), the TOF
-// sensitivity over all 252 views 7.6 ms (3.4).  The forms' lines: with kappa just
+// 2204-plane geometry 397 us (now 142), its fused gradient 603 (299), the TOF
+// sensitivity over all 252 views 7.6 ms (3.2).  The forms' lines: with kappa just
 // below 1, the loop of gather_many takes 65.7 us for a gradient of 96 x 96 x 32
 // voxels at kappa 0.9, three fixed planes 51.6, the scatter 76; at kappa 0.6 and 0.2
 // the loop takes 71 and 121, the scatter 87 and 191.

@@ -294,11 +294,11 @@ __global__ void __launch_bounds__(NT_BLOCK, 8) k_line_nt(ProjArgs a) {
 // table position times the slope there.  The forward adds the position up in parts
 // (TofPos); the adjoint forms it in one multiply-add.
 //
-// What bounds it: vector instructions (57% of the cycles of a subset gradient of
+// What bounds it: vector instructions (61% of the cycles of a subset gradient of
 // 128 x 128 x 71 voxels, 2204 planes and 13 bins; 12 per gathered cell and unit,
-// 6 to 8 per sample), then the matrix cores (151 us of the 784) and the data's
-// loads.  A wave per segment with FP64 LDS adds per sample took 1026 us for it;
-// 945 -> 612 us with 161 x 161 x 33 voxels and 25 bins, and a forward projection
+// 6 to 8 per sample), then the matrix cores (18% of its 755 us) and the data's
+// loads.  A wave per segment with FP64 LDS adds per sample took 1016 us for it;
+// 934 -> 496 us with 161 x 161 x 33 voxels and 25 bins, and a forward projection
 // of 96 x 96 x 32 voxels 694 -> 225 us.
 //
 // Lane layouts of the 16x16x4 instruction: A[m][k] in lane 16 k + m, B[k][n] in
