@@ -1161,13 +1161,15 @@ hipError_t launch_tof(const pet_geom_s *g, dim3 grid, ProjArgs a, hipStream_t s)
     // 96 x 96 x 32 voxels and five units 101 -> 90 (72 -> 61) us, of 96 x 96 x 5 and
     // three units 51 -> 36 (39 -> 28), 784 lines of 13 units 52 -> 42; but 576 lines 44
     // -> 56, 85 lines 23 -> 28, and 29 units with room for three workgroups 98 -> 119.
+    // Where units and blocks of rows are four at most there is nothing for more waves, so
+    // from FEW_LINES on: 735 lines, 58 x 52 x 7 voxels, three units 27 -> 21, four 34 -> 24.
     // Two waves for one or two units, from six lines per CU: 1896 lines of one unit 61
     // -> 42 (four: 49), 10191 of two 308 -> 220 (228); three units 565 -> 482 (405).
     // Units in several groups are slower so (29, backprojection, 276 -> 303).
     int waves = TOF_BLOCK / 64;
     if (!z)
         waves = std::min(waves, std::max(4, g->n_units));
-    else if (grid.x >= 3 * CUS && a.q_units >= g->n_units &&
+    else if (grid.x >= (g->n_units <= 4 && g->rows_max <= 64 ? FEW_LINES : 3 * CUS) && a.q_units >= g->n_units &&
              tof_lds_bytes(g, x, a.q_units, 4) <= CU_LDS_BYTES / (g->n_units > waves ? 4 : 3))
         waves = g->n_units <= 2 && grid.x >= 6 * CUS ? 2 : 4;
     const size_t lds = tof_lds_bytes(g, x, z ? a.q_units : 0, z ? waves : 0);
